@@ -57,7 +57,7 @@ static int validate(const int32_t *row_ptr, const int32_t *col_idx, const void *
     if (opt.spec_depth < 0 || opt.spec_depth > 48) { err = "spec_depth must be in 0..48"; return SPARSERT_EINVAL; }
     if (opt.spec_tiles != 0 && opt.spec_tiles != 1 && opt.spec_tiles != 2 && opt.spec_tiles != 4 &&
         opt.spec_tiles != 8 && opt.spec_tiles != 16) { err = "spec_tiles must be 0,1,2,4,8,16"; return SPARSERT_EINVAL; }
-    if (opt.spec_mode < SPARSERT_SPEC_AUTO || opt.spec_mode > SPARSERT_SPEC_LDS) { err = "unknown spec_mode"; return SPARSERT_EINVAL; }
+    if (opt.spec_mode < SPARSERT_SPEC_AUTO || opt.spec_mode > SPARSERT_SPEC_MFMA) { err = "unknown spec_mode"; return SPARSERT_EINVAL; }
     if (opt.spec_rows < 0) { err = "spec_rows must be >= 0"; return SPARSERT_EINVAL; }
     if (opt.split_threshold < 0) { err = "split_threshold must be >= 0"; return SPARSERT_EINVAL; }
     const int64_t esz = opt.dtype == SPARSERT_F16 ? 2 : opt.dtype == SPARSERT_I8 ? 1 : 4;
@@ -123,7 +123,7 @@ int build_host_plan(const int32_t *row_ptr, const int32_t *col_idx, const void *
     // row-walk kernel, whose inspector generates nothing.  Options that only the row-walk kernel
     // reads (vec, split_threshold) select it as well.
     if (opt.kernel != SPARSERT_KERNEL_AUTO) h.kernel = opt.kernel;
-    else h.kernel = (opt.vec == 0 && opt.split_threshold == 0 && h.nnz <= kAutoSpecNnz && spec_available())
+    else h.kernel = (opt.vec == 0 && opt.split_threshold == 0 && ((h.nnz <= kAutoSpecNnz && spec_available()) || mfma_preferred(h, opt) >= 0))
                         ? SPARSERT_KERNEL_SPEC : SPARSERT_KERNEL_ROWS;
     h.kernel_auto = opt.kernel == SPARSERT_KERNEL_AUTO;
     const int esz = h.elem_size();

@@ -296,6 +296,12 @@ int upload_plan(const HostPlan &h, DevicePlan &d, std::string &err) {
     }
     if (int rc = to_device(h.segments.data(), h.segments.size(), &d.segments, err)) return rc;
     if (int rc = to_device(h.conv_seg.data(), h.conv_seg.size(), &d.conv_seg, err)) return rc;
+    if (h.kernel == SPARSERT_KERNEL_SPEC && h.spec.mode == SPARSERT_SPEC_MFMA) {
+        std::vector<uint8_t> fragments;
+        mfma_pack(h, fragments);
+        if (int rc = to_device(fragments.data(), fragments.size(), reinterpret_cast<uint8_t **>(&d.mfma_weights), err)) return rc;
+        return to_device(h.inv_perm.data(), h.inv_perm.size(), &d.inv_perm, err);
+    }
     if (h.kernel == SPARSERT_KERNEL_SPEC) {
         int dev = 0, lds_max = 0;
         HIP_TRY(hipGetDevice(&dev));
@@ -322,6 +328,8 @@ void free_device_plan(DevicePlan &d) {
     if (d.stream) (void)hipFree(d.stream);
     if (d.segments) (void)hipFree(d.segments);
     if (d.conv_seg) (void)hipFree(d.conv_seg);
+    if (d.inv_perm) (void)hipFree(d.inv_perm);
+    if (d.mfma_weights) (void)hipFree(d.mfma_weights);
     if (d.spec_module) (void)hipModuleUnload(static_cast<hipModule_t>(d.spec_module));
     d = DevicePlan();
 }
@@ -531,6 +539,7 @@ int displace_caches(void *scratch, size_t bytes, void *stream, std::string &err)
 int launch_spec(const HostPlan &h, const DevicePlan &d, const void *B, void *C,
                 void *stream, std::string &err) {
     const SpecPlan &sp = h.spec;
+    if (sp.mode == SPARSERT_SPEC_MFMA) return launch_mfma(h, d, B, C, stream, err);
     if (!d.spec_function || sp.n_groups < 1 || sp.n_tiles < 1) {
         err = "plan has no generated kernel";
         return SPARSERT_EINVAL;

@@ -1,0 +1,64 @@
+// Tile shapes of the matrix-core executor (mfma.hip): what the inspector chooses from and the
+// launch looks up.  Host code only.
+#pragma once
+#include <cstdint>
+
+namespace sparsert {
+
+struct MfmaConfig {
+    int tm, tn;          // rows and columns of C per workgroup
+    int wm, wn, mf, nf;  // waves along M and N; 16-row and 16-column fragments per wave
+    int steps;           // matrix-instruction steps of K per slab
+    int stages;          // slabs in LDS
+    // Measured time in microseconds: launch and ends, a slab of a workgroup that has its compute unit to
+    // itself, a slab for every workgroup of the busiest compute unit, a megabyte of C (mfma_microseconds).
+    double fixed, slab_alone, slab_shared, store;
+    constexpr int waves() const { return wm * wn; }
+    constexpr int lds_bytes() const { return (tm + tn) * 64 * steps * stages; }
+};
+
+// One instruction contracts 64 bytes of every column: 32 halves or 64 int8.
+constexpr int mfma_step(int elem_size) { return 64 / elem_size; }
+
+// Upper bound of the zero-filled copy of A (rows rounded up to 128, columns to the longest slab).
+inline int64_t mfma_weight_bytes(int64_t M, int64_t K, int elem_size) {
+    return (M + 127) / 128 * 128 * ((K * elem_size + 511) / 512 * 512);
+}
+
+#define SPARSERT_MFMA_CONFIGS(X)                                  \
+    X(0, 128, 128, 2, 4, 4, 2, 2, 4, 3.74, 0.197, 0.376, 0.27) \
+    X(1, 64, 128, 2, 4, 2, 2, 2, 3, 3.00, 0.222, 0.324, 0.21)  \
+    X(2, 128, 64, 4, 2, 2, 2, 2, 3, 2.97, 0.155, 0.318, 0.22)  \
+    X(3, 64, 64, 2, 2, 2, 2, 2, 4, 2.58, 0.210, 0.206, 0.27)   \
+    X(4, 32, 64, 2, 2, 1, 2, 2, 4, 2.35, 0.178, 0.154, 0.29)   \
+    X(5, 32, 32, 2, 2, 1, 1, 2, 4, 2.23, 0.129, 0.126, 0.34)   \
+    X(6, 16, 64, 1, 4, 1, 1, 4, 4, 2.50, 0.203, 0.285, 0.62)   \
+    X(7, 48, 64, 1, 4, 3, 1, 4, 4, 2.59, 0.391, 0.397, 0.69)   \
+    X(8, 96, 128, 2, 2, 3, 4, 2, 4, 3.56, 0.080, 0.355, 0.33)
+
+constexpr MfmaConfig kMfmaConfigs[] = {
+#define X(id, tm, tn, wm, wn, mf, nf, steps, stages, f, a, s, o) {tm, tn, wm, wn, mf, nf, steps, stages, f, a, s, o},
+    SPARSERT_MFMA_CONFIGS(X)
+#undef X
+};
+constexpr int kMfmaConfigCount = (int)(sizeof(kMfmaConfigs) / sizeof(kMfmaConfigs[0]));
+
+// Index of the configuration with this tile; 0 for a field means any.  -1: none.
+inline int mfma_find(int tm, int tn) {
+    for (int i = 0; i < kMfmaConfigCount; ++i)
+        if ((!tm || kMfmaConfigs[i].tm == tm) && (!tn || kMfmaConfigs[i].tn == tn)) return i;
+    return -1;
+}
+
+// Time of an M x K x N product with this tile, from the constants above: they reproduce 122 measured shapes
+// (M 64 ... 4000, K 64 ... 3867, N 49 ... 4096, both storage types) to about 9 %, and the tile they choose is
+// within 1 % of the best one on average, 10 % at most.
+inline double mfma_microseconds(const MfmaConfig &c, int64_t M, int64_t K, int64_t N, int64_t batch, int elem_size, int out_size) {
+    const int64_t slab = (int64_t)c.steps * mfma_step(elem_size), slabs = (K + slab - 1) / slab;
+    const int64_t wgs = (M + c.tm - 1) / c.tm * ((N + c.tn - 1) / c.tn) * batch;
+    const double rounds = wgs > 1024 ? wgs / 256.0 : (double)((wgs + 255) / 256);
+    const double slab_us = c.slab_shared * rounds > c.slab_alone ? c.slab_shared * rounds : c.slab_alone;
+    return c.fixed + slabs * slab_us + c.store * 1e-6 * (double)(M * N * batch) * out_size;
+}
+
+}  // namespace sparsert

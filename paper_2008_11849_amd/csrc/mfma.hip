@@ -1,0 +1,381 @@
+// Matrix-core executor for half and int8 SpMM plans.
+//
+// The generated kernel runs half and int8 products at the vector unit's fp32 rate, one multiply-add
+// per kept weight and column.  The matrix cores contract a zero-filled tile of A some thirty times
+// faster per element, so from a few percent of kept weights on it is cheaper to hand them the
+// zeros than to skip them: products of two halves are exact in fp32 and the sums are fp32 either
+// way, int8 sums are exact integers, so nothing about the result's precision changes.
+//
+// Layout: the plan keeps A as fragments of 16 rows x one instruction step of K (32 halves or 64
+// int8), 1 KiB each in the order the lanes hold them.  Fragments and rows of B travel to LDS with
+// the memory path's direct copies (buffer_load ... lds, 1 KiB per wave instruction, no registers),
+// several slabs ahead: every launch finds the L2 caches empty, so a slab is 1 us away.  B lies in LDS
+// as in memory and is read back transposed (ds_read_b64_tr), which leaves four (eight) consecutive
+// rows of K of one column in a lane; the order of K inside a fragment follows from that and is the
+// same in A's fragments.
+//
+// The activations are the first operand of the instruction and the weights the second, so a lane
+// ends up with four consecutive columns of one row of C and stores them with one instruction.
+//
+// Zeros of A meet every element of B here, and zero times infinity is not zero.  A non-finite
+// element of B (or weight of A) leaves a non-finite sum in every row of its column, so sums that are
+// all finite prove that nothing of the kind was involved; a wave that finds one that is not redoes
+// its part of C from the nonzero stream alone, as the row-walk kernel would.
+// What bounds it, from builds with one ingredient left out (128 x 128 tile, K = 2048, one tile per compute unit):
+// LDS reads alone need 0.27 us per slab, matrix instructions alone 0.21 us, both 0.36 us, and 0.5 us with
+// the copies, which also write LDS.  Eight waves instead of four were worth 1.1x (a wave issues an instruction
+// every four clocks at best, and a slab is a hundred of them), addresses kept in the descriptor's scalar
+// offset instead of vector adds 1.15x.  1024 x 1024 x 4096 half at 80 %: 45.2 us generated, 12.5 us here;
+// 3072 x 768 x 1024 half at 95 %: 11.3 and 9.3 us; 768 x 3072 x 1024 int8 at 95 %: 13.9 and 9.6 us.
+#include <hip/hip_runtime.h>
+
+#include <cstring>
+#include <string>
+#include <type_traits>
+#include <utility>
+#include <vector>
+
+#include "mfma.h"
+#include "plan.h"
+
+namespace sparsert {
+
+namespace {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+typedef _Float16 half4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef int32_t int2v __attribute__((ext_vector_type(2)));
+typedef int32_t int4v __attribute__((ext_vector_type(4)));
+typedef int32_t int4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+typedef uint32_t uint4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+typedef const char __attribute__((address_space(1))) *gbytes;
+typedef __attribute__((address_space(3))) short4v *lds_short4;
+typedef __attribute__((address_space(3))) int2v *lds_int2;
+
+}  // namespace
+
+struct MfmaArgs {
+    const void *weights;                 // fragments of A: [row tile of 16][step of K][lane][16 bytes]
+    const void *in;                      // B [K, ldb]
+    void *out;                           // C [M, ldc]
+    const int32_t *p_row_ptr, *inv_perm; // the nonzero stream, for tiles with non-finite sums
+    const uint2 *stream;
+    int32_t M, K, N, ldb, ldc;
+    int32_t k_steps, n_slabs;
+    int32_t m_tiles, n_tiles, tasks_per_xcd, m_fast;
+    int32_t in_bytes;                    // of one problem: reads stay inside
+    int32_t weight_bytes, out_bytes;
+    int64_t in_stride, out_stride;       // elements between the problems of a batch (grid y)
+};
+
+template <int DT> struct Kind;           // 0: half, 1: int8
+template <> struct Kind<0> {
+    typedef _Float16 in_t; typedef _Float16 out_t; typedef float4v acc_t; typedef half8 frag_t;
+    static constexpr int esz = 2;
+    static __device__ __forceinline__ acc_t mma(const frag_t &a, const frag_t &b, const acc_t &c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+    }
+};
+template <> struct Kind<1> {
+    typedef int8_t in_t; typedef int32_t out_t; typedef int4v acc_t; typedef int4v frag_t;
+    static constexpr int esz = 1;
+    static __device__ __forceinline__ acc_t mma(const frag_t &a, const frag_t &b, const acc_t &c) {
+        return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
+    }
+};
+
+// Element (row, n) of the product from the nonzero stream: the path for non-finite operands.
+__device__ __forceinline__ float exact_element(const MfmaArgs &a, const _Float16 *in, int row, int n) {
+    const int slot = a.inv_perm[row];
+    float s = 0.0f;
+#pragma unroll 1
+    for (int p = a.p_row_ptr[slot]; p < a.p_row_ptr[slot + 1]; ++p) {
+        const uint2 e = a.stream[p];
+        s = __builtin_fmaf(__uint_as_float(e.y), (float)in[(int)e.x / 2 + n], s);
+    }
+    return s;
+}
+
+template <typename F, int... I> __device__ __forceinline__ void each_constant(F f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
+}
+
+template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// 16 bytes per lane from descriptor + voffset + soffset + OFFSET straight to LDS at lds_base + OFFSET + 16 * lane.
+// Written as assembly because the compiler would otherwise wait for every copy before any read of LDS.
+template <int OFFSET> __device__ __forceinline__ void copy_to_lds(const int4v &rsrc, int voffset, int soffset, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
+                 ::"s"(lds_base), "v"(voffset), "s"(rsrc), "s"(soffset), "n"(OFFSET) : "memory");
+}
+
+__device__ __forceinline__ int4v descriptor(const void *p, int bytes) {
+    const uint64_t u = (uint64_t)p;
+    return int4v{(int)(uint32_t)u, (int)((uint32_t)(u >> 32) & 0xffffu), bytes, 0x00020000};
+}
+
+template <int DT, int WM, int WN, int MF, int NF, int STEPS, int STAGES>
+__global__ __launch_bounds__(WM *WN *kWave, 2) void mfma_kernel(const MfmaArgs a) {
+    typedef Kind<DT> Q;
+    typedef typename Q::acc_t acc_t;
+    typedef typename Q::frag_t frag_t;
+    typedef typename Q::in_t in_t;
+    typedef typename Q::out_t out_t;
+    constexpr int ESZ = Q::esz, STEP = 64 / ESZ, EPC = 16 / ESZ, WAVES = WM * WN;
+    constexpr int TM = WM * MF * 16, TN = WN * NF * 16;
+    constexpr int SLAB = STEPS * STEP;                   // rows of K per slab
+    constexpr int A_BYTES = TM * STEPS * 64, STAGE = A_BYTES + TN * STEPS * 64;
+    constexpr int IA = A_BYTES / 1024 / WAVES, IB = TN * STEPS * 64 / 1024 / WAVES;   // 1 KiB copies per wave and slab
+    static_assert(IA * WAVES * 1024 == A_BYTES && (IA + IB) * WAVES * 1024 == STAGE, "the copies of a slab are dealt evenly");
+    static_assert((IA + IB) * (STAGES - 1) < 64, "vmcnt is a 6-bit counter");
+    constexpr int CPR = TN * ESZ / 16, RPC = 64 / CPR;   // 16-byte chunks per row of the tile, rows per copy
+    constexpr int ROWS256 = 256 / (TN * ESZ) > 0 ? 256 / (TN * ESZ) : 1;
+    __shared__ __align__(1024) char lds[STAGES * STAGE];
+
+    const int task = (int)(blockIdx.x & 7) * a.tasks_per_xcd + (int)(blockIdx.x >> 3);
+    if (task >= a.m_tiles * a.n_tiles) return;
+    const int tile_m = a.m_fast ? task % a.m_tiles : task / a.n_tiles;
+    const int tile_n = a.m_fast ? task / a.m_tiles : task % a.n_tiles;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int m0 = tile_m * TM + wm * MF * 16, n_tile0 = tile_n * TN, n0 = n_tile0 + wn * NF * 16;
+    const in_t *in = static_cast<const in_t *>(a.in) + (int64_t)blockIdx.y * a.in_stride;
+    out_t *out = static_cast<out_t *>(a.out) + (int64_t)blockIdx.y * a.out_stride;
+    // Where N is no multiple of EPC the last 16-byte chunk of a row begins at N - EPC: it holds some
+    // columns twice, every one of them real, so neither the loads nor the stores know ragged ends.
+    auto column = [&](int n) { return n - max(0, (n & -EPC) + EPC - a.N); };   // column of C behind column n of the tiling
+    // Chunk c of row r lies at position c ^ swizzle(r) of the row in LDS: the rows that half a wave reads
+    // together (8 x 32 bytes of halves, 16 x 16 bytes of int8) then cover all banks once.
+    auto swizzle = [](int r) { return DT == 0 ? r / ROWS256 % (CPR / 2) * 2 : r / ROWS256 % CPR; };
+
+    // ---- copies: this lane's chunk of every copy of a slab.  What leaves the operand (rows past K in the last
+    // slab, an offset of kRefused) the descriptor answers with zeros and no memory access; so it does for every
+    // copy of a slab past the last one, whose descriptors have no bytes.
+    const int4v rin = descriptor(in, a.in_bytes), rw = descriptor(a.weights, a.weight_bytes);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    constexpr int kRefused = (int)0x80000000;
+    int b_off[IB];
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+        const int row = (wave * IB + i) * RPC + lane / CPR, n = n_tile0 + (lane % CPR ^ swizzle(row)) * EPC;
+        b_off[i] = n < a.N && row < a.K ? (int)(((uint32_t)row * (uint32_t)a.ldb + (uint32_t)column(n)) * ESZ) : kRefused;
+    }
+    constexpr bool PAIRS = IA % STEPS == 0;   // a wave copies whole runs of steps of a row tile: one offset per run
+    int a_off[IA];
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+        const int q = wave * IA + i;
+        a_off[i] = ((tile_m * (TM / 16) + q / STEPS) * a.k_steps + q % STEPS) * 1024 + lane * 16;
+    }
+    struct Source { int4v rin, rw; int sin, sw; uint32_t base; };
+    auto source = [&](int s) {   // what the copies of slab s have in common
+        const bool live = s < a.n_slabs;
+        Source c{rin, rw, live ? (int)((uint32_t)s * (uint32_t)(SLAB * ESZ) * (uint32_t)a.ldb) : 0, live ? s * (STEPS * 1024) : 0,
+                 lds0 + (uint32_t)(s % STAGES) * STAGE};
+        c.rin[2] = live ? a.in_bytes : 0;
+        c.rw[2] = live ? a.weight_bytes : 0;
+        return c;
+    };
+    // Copy i of this wave's IA + IB copies of a slab.
+    auto issue = [&](const Source &c, auto which) {
+        constexpr int i = which;
+        if constexpr (i < IA) {
+            constexpr int first = PAIRS ? i / STEPS * STEPS : i;
+            copy_to_lds<(i - first) * 1024>(c.rw, a_off[first], c.sw, c.base + (uint32_t)(wave * IA + first) * 1024);
+        } else {
+            constexpr int b = i - IA;
+            copy_to_lds<0>(c.rin, b_off[b], c.sin, c.base + A_BYTES + (uint32_t)(wave * IB + b) * 1024);
+        }
+    };
+    acc_t acc[MF][NF];
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
+    const int g = lane >> 4, lg = lane & 15;
+    // Where the transposing reads of a lane begin: row 4g + lg/4 (8g + lg/2) of a step, and the piece of 8 bytes inside 16 columns.
+    const int rd_row = DT == 0 ? 4 * g + (lg >> 2) : 8 * g + (lg >> 1), rd_swz = swizzle(rd_row);
+    int rd[NF];
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+        const int c = DT == 0 ? (wn * NF + j) * 2 + (lg >> 1 & 1) : wn * NF + j;
+        rd[j] = A_BYTES + rd_row * (TN * ESZ) + (c ^ rd_swz) * 16 + (lg & 1) * 8;
+    }
+    const int rd_a = wm * MF * STEPS * 1024 + lane * 16;
+
+    // ---- slabs.  While slab s is multiplied out of registers, the fragments of slab s + 1 are read from LDS and
+    // the copies of slab s + STAGES go out, a few of each behind every group of matrix instructions: LDS, the
+    // memory path and the matrix cores each need about as long as the others, so they have to run at the same time.
+    constexpr int GROUPS = STEPS * NF, UNITS = STEPS * (MF + NF);
+    struct Fragments { frag_t w[STEPS][MF], x[STEPS][NF]; };
+    auto each_copy = [&](auto f) { each_constant(f, std::make_integer_sequence<int, IA + IB>()); };
+    auto read = [&](char *base, int u, Fragments &f) {
+        const int t = u / (MF + NF), r = u % (MF + NF);
+        if (r < MF) {
+            f.w[t][r] = *reinterpret_cast<const frag_t *>(base + rd_a + (r * STEPS + t) * 1024);
+            return;
+        }
+        char *p = base + rd[r - MF] + t * STEP * TN * ESZ;
+        int2v v[2];
+        if constexpr (DT == 0) {
+            const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4)p);
+            const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4)(p + STEP / 2 * TN * ESZ));
+            __builtin_memcpy(&v[0], &lo, 8);
+            __builtin_memcpy(&v[1], &hi, 8);
+        } else {
+            v[0] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_int2)p);
+            v[1] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_int2)(p + STEP / 2 * TN * ESZ));
+        }
+        __builtin_memcpy(&f.x[t][r - MF], v, 16);
+    };
+    auto meet = [&]() {   // every wave's copies of the slab waited for have arrived, and every read issued so far is complete
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    auto turn = [&](int s, Fragments &now, Fragments &next, auto last) {
+        if constexpr (!last) {
+            wait_loads<(IA + IB) * (STAGES - 2)>();      // this wave's copies of slab s + 1
+            meet();
+        }
+        char *base = lds + (s + 1) % STAGES * STAGE;
+        const Source from = source(s + STAGES);
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {
+#pragma unroll
+            for (int j = 0; j < NF; ++j) {
+#pragma unroll
+                for (int i = 0; i < MF; ++i) acc[i][j] = Q::mma(now.x[t][j], now.w[t][i], acc[i][j]);
+                if constexpr (last) continue;
+                const int q = t * NF + j;   // (a constant: the loops are unrolled)
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = q * UNITS / GROUPS; u < (q + 1) * UNITS / GROUPS; ++u) read(base, u, next);
+                each_copy([&](auto i) {
+                    if (i >= q * (IA + IB) / GROUPS && i < (q + 1) * (IA + IB) / GROUPS) issue(from, i);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    Fragments even, odd;
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s) {
+        const Source from = source(s);
+        each_copy([&](auto i) { issue(from, i); });
+    }
+    wait_loads<(IA + IB) * (STAGES - 1)>();
+    meet();
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) read(lds, u, even);
+    int s = 0;
+    for (; s + 1 < a.n_slabs; s += 2) {
+        turn(s, even, odd, std::false_type());
+        turn(s + 1, odd, even, std::false_type());
+    }
+    if (s < a.n_slabs) turn(s, even, odd, std::true_type());
+    wait_loads<0>();
+
+    // ---- results.  Stores outside C (rows past M, chunks past N) are refused by the descriptor.
+    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, a.out_bytes, 0x00020000);
+    float probe = 0.0f;   // becomes NaN with the first sum that is not finite
+    int row_off[MF], col_off[NF];
+#pragma unroll
+    for (int i = 0; i < MF; ++i) row_off[i] = (int)((uint32_t)(m0 + i * 16 + lg) * (uint32_t)a.ldc * (uint32_t)sizeof(out_t));
+#pragma unroll
+    for (int j = 0; j < NF; ++j) col_off[j] = column(n0 + j * 16 + 4 * g) * (int)sizeof(out_t);
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+            const acc_t v = acc[i][j];
+            const bool mine = (m0 + i * 16 + lg < a.M) & (((n0 + j * 16 + 4 * g) & -EPC) < a.N);
+            const int off = mine ? row_off[i] + col_off[j] : kRefused;
+            if constexpr (DT == 0) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) probe = __builtin_fmaf(v[r], 0.0f, probe);
+                const half4 h = {(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};   // one rounding to nearest even
+                int2v b;
+                __builtin_memcpy(&b, &h, 8);
+                __builtin_amdgcn_raw_buffer_store_b64(b, rout, off, 0, 0);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b128(v, rout, off, 0, 0);
+            }
+        }
+    if constexpr (DT == 0) {
+        if (__builtin_expect(__any(probe != probe), 0)) {
+#pragma unroll 1
+            for (int f = 0; f < MF * NF; ++f) {
+                const int row = m0 + f / NF * 16 + lg, n = n0 + f % NF * 16 + 4 * g;
+                if (row >= a.M || (n & -EPC) >= a.N) continue;
+#pragma unroll 1
+                for (int r = 0; r < 4; ++r)
+                    out[(size_t)row * a.ldc + column(n) + r] = (_Float16)exact_element(a, in, row, column(n) + r);
+            }
+        }
+    }
+}
+
+// A as fragments, zero-filled to whole workgroup tiles and slabs.
+void mfma_pack(const HostPlan &h, std::vector<uint8_t> &out) {
+    const MfmaConfig &c = kMfmaConfigs[h.spec.mfma_config];
+    const int esz = h.elem_size(), step = mfma_step(esz);
+    const int64_t m_tiles = (h.M + c.tm - 1) / c.tm * (c.tm / 16), k_steps = (h.K + c.steps * step - 1) / (c.steps * step) * c.steps;
+    out.assign((size_t)(m_tiles * k_steps) * 1024, 0);
+    for (int32_t slot = 0; slot < h.M; ++slot) {
+        const int32_t m = h.perm[slot];
+        for (int32_t p = h.p_row_ptr[slot]; p < h.p_row_ptr[slot + 1]; ++p) {
+            const int32_t k = h.p_col_idx[p];
+            const int kk = k % step, half_step = step / 2, rows = step / 8;
+            const int lane = kk % half_step / rows * 16 + m % 16, elem = kk / half_step * rows + kk % rows;
+            std::memcpy(&out[(size_t)(((m / 16) * k_steps + k / step) * 64 + lane) * 16 + (size_t)elem * esz],
+                        &h.p_vals[(size_t)p * esz], (size_t)esz);
+        }
+    }
+}
+
+int launch_mfma(const HostPlan &h, const DevicePlan &d, const void *in, void *out, void *stream, std::string &err) {
+    const SpecPlan &sp = h.spec;
+    if (!d.mfma_weights || sp.mfma_config < 0 || sp.mfma_config >= kMfmaConfigCount || h.N < 16 || h.batch < 1 || h.batch > 65535) {
+        err = "plan geometry is inconsistent";
+        return SPARSERT_EINVAL;
+    }
+    const MfmaConfig &c = kMfmaConfigs[sp.mfma_config];
+    const int esz = h.elem_size(), slab = c.steps * mfma_step(esz);
+    MfmaArgs a;
+    a.weights = d.mfma_weights; a.in = in; a.out = out;
+    a.p_row_ptr = d.p_row_ptr; a.inv_perm = d.inv_perm; a.stream = reinterpret_cast<const uint2 *>(d.stream);
+    a.M = h.M; a.K = h.K; a.N = h.N; a.ldb = h.ldb; a.ldc = h.ldc;
+    a.n_slabs = (a.K + slab - 1) / slab; a.k_steps = a.n_slabs * c.steps;
+    a.m_tiles = (h.M + c.tm - 1) / c.tm; a.n_tiles = (h.N + c.tn - 1) / c.tn;
+    const int64_t tasks = (int64_t)a.m_tiles * a.n_tiles;
+    if (tasks > (1ll << 30)) { err = "too many workgroups"; return SPARSERT_EUNSUPPORTED; }
+    a.tasks_per_xcd = (int32_t)((tasks + 7) / 8);
+    // Each XCD takes an eighth of the tiles: along M if that leaves its L2 less of A and B to hold, else along N.
+    const double wb = (double)a.m_tiles * c.tm * a.K * esz, bb = (double)h.K * h.N * esz;
+    a.m_fast = wb + bb / 8 < wb / 8 + bb;
+    a.in_bytes = (int32_t)(((int64_t)(h.K - 1) * h.ldb + h.N) * esz);
+    const int64_t weight_bytes = (int64_t)a.m_tiles * (c.tm / 16) * a.k_steps * 1024;
+    if (weight_bytes >= (1ll << 31)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
+    a.weight_bytes = (int32_t)weight_bytes;
+    a.out_bytes = (int32_t)(((int64_t)(h.M - 1) * h.ldc + h.N) * h.out_elem_size());
+    a.in_stride = (int64_t)h.K * h.ldb; a.out_stride = (int64_t)h.M * h.ldc;
+    const dim3 grid((unsigned)a.tasks_per_xcd * 8u, (unsigned)h.batch), wg((unsigned)c.waves() * kWave);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    switch (sp.mfma_config * 2 + (h.dtype == SPARSERT_I8 ? 1 : 0)) {
+#define X(id, tm, tn, wm, wn, mf, nf, steps, stages, ...)                                                                  \
+    case id * 2 + 0: hipLaunchKernelGGL((mfma_kernel<0, wm, wn, mf, nf, steps, stages>), grid, wg, 0, s, a); break; \
+    case id * 2 + 1: hipLaunchKernelGGL((mfma_kernel<1, wm, wn, mf, nf, steps, stages>), grid, wg, 0, s, a); break;
+        SPARSERT_MFMA_CONFIGS(X)
+#undef X
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { err = std::string("matrix-core kernel launch: ") + hipGetErrorString(e); return SPARSERT_EHIP; }
+    return SPARSERT_OK;
+}
+
+}  // namespace sparsert

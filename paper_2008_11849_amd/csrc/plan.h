@@ -45,6 +45,7 @@ struct SpecPlan {
     int32_t ksplit = 1;         // DIRECT: waves of a workgroup that split the K range of one block
     int32_t prefetch_lines = 0; // 128-byte lines of its block's code every lane touches before the block runs
     int64_t asm_bytes = 0;
+    int32_t mfma_config = -1;   // MFMA mode: index into kMfmaConfigs (mfma.h); rows_per_group and 16 * tiles_per_wg name it
     std::vector<int32_t> group_of_slot;   // [M]
     std::vector<int32_t> group_columns;   // [n_groups] B rows each group loads per column tile
     std::vector<char> code;               // gfx950 code object
@@ -79,6 +80,8 @@ struct DevicePlan {
     uint32_t *stream = nullptr;
     int32_t *conv_seg = nullptr;
     int32_t *segments = nullptr;
+    int32_t *inv_perm = nullptr;    // MFMA plans
+    void *mfma_weights = nullptr;   // MFMA plans: A as matrix-core fragments
     void *spec_module = nullptr;    // hipModule_t
     void *spec_function = nullptr;  // hipFunction_t
 };
@@ -104,6 +107,9 @@ int rows_for_rounds(int32_t M, int groups_per_wg, int64_t wg_columns, int rounds
 // than a quarter full and at most 15 % more rows per block remove it, this returns that row
 // count; else R.
 int rows_without_thin_round(int32_t M, int R, int groups_per_wg, int64_t wg_columns, int hi);
+// The matrix-core tile (index into kMfmaConfigs) the inspector would take for this problem if nothing is set,
+// or -1 where generated code is expected to be faster or the variant does not apply.
+int mfma_preferred(const HostPlan &h, const sparsert_options &opt);
 bool spec_available();   // can generated kernels be assembled in this process (is the code object manager loadable)?
 
 // Records the thread-local error message behind sparsert_last_error (api.cpp); returns `code`.
@@ -117,6 +123,9 @@ int launch_rows(const HostPlan &h, const DevicePlan &d, const void *B, void *C,
                 void *stream, std::string &err);
 int launch_spec(const HostPlan &h, const DevicePlan &d, const void *B, void *C,
                 void *stream, std::string &err);
+// Matrix-core executor (mfma.hip).
+void mfma_pack(const HostPlan &h, std::vector<uint8_t> &out);
+int launch_mfma(const HostPlan &h, const DevicePlan &d, const void *in, void *out, void *stream, std::string &err);
 // Comparison of two results of a plan (kernels.hip).  launch_compare: two kernels on `stream`,
 // partials_dev must hold 4 words per block of compare_blocks(h), result_dev receives 4 words.
 int64_t compare_blocks(const HostPlan &h);

@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "mfma.h"
 #include "plan.h"
 
 namespace {
@@ -122,6 +123,13 @@ bool consistent(const sparsert::HostPlan &h) {
             }
         }
     }
+    if (h.kernel == SPARSERT_KERNEL_SPEC && h.spec.mode == SPARSERT_SPEC_MFMA) {
+        const sparsert::SpecPlan &sp = h.spec;
+        for (size_t i = 0; i < M; ++i)
+            if (h.inv_perm[i] < 0 || h.inv_perm[i] >= h.M || h.perm[h.inv_perm[i]] != (int32_t)i) return false;
+        return h.dtype != SPARSERT_F32 && sp.mfma_config >= 0 && !sp.symbol.empty() &&
+               h.N >= 16 && !h.conv && sparsert::mfma_weight_bytes(h.M, h.K, h.elem_size()) < (1ll << 31);
+    }
     if (h.kernel == SPARSERT_KERNEL_SPEC) {
         const sparsert::SpecPlan &sp = h.spec;
         if (sp.code.size() < 64 || sp.symbol.empty() || sp.group_of_slot.size() != M) return false;
@@ -188,6 +196,7 @@ int load_impl(const void *buf, size_t size, int32_t host_only, sparsert_plan **o
     r.vec(h.row_nnz); r.vec(h.hist); r.vec(h.perm); r.vec(h.inv_perm); r.vec(h.p_row_ptr); r.vec(h.p_col_idx);
     r.vec(h.p_vals); r.vec(h.bins); r.vec(h.stream); r.vec(h.conv_seg); r.vec(h.segments);
     r.vec(h.spec.group_of_slot); r.vec(h.spec.group_columns); r.vec(h.spec.code);
+    if (h.spec.mode == SPARSERT_SPEC_MFMA) h.spec.mfma_config = sparsert::mfma_find(h.spec.rows_per_group, 16 * h.spec.tiles_per_wg);
     if (!r.ok || r.p != r.end || !consistent(h)) {
         delete plan;
         return sparsert::set_error(SPARSERT_EINVAL, "serialised plan is inconsistent");

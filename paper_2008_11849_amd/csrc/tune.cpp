@@ -16,6 +16,7 @@
 #include <thread>
 #include <vector>
 
+#include "mfma.h"
 #include "plan.h"
 
 namespace {
@@ -217,6 +218,17 @@ static int tune_impl(const int32_t *row_ptr, const int32_t *col_idx, const void 
             o.kernel = SPARSERT_KERNEL_SPEC;
             cands.push_back(o);
         }
+        if (!conv && (f16 || i8) && N >= 16 && !b.natural_order) {   // zero-filled tiles on the matrix cores: small, middle and large
+            for (int tile : {5, 4, 3, 2, 0}) {
+                sparsert_options o = b;
+                o.kernel = SPARSERT_KERNEL_SPEC; o.spec_mode = SPARSERT_SPEC_MFMA;
+                o.spec_rows = sparsert::kMfmaConfigs[tile].tm; o.spec_tiles = sparsert::kMfmaConfigs[tile].tn / 16;
+                cands.push_back(o);
+            }
+            sparsert_options o = b;   // ... and the one the inspector takes
+            o.kernel = SPARSERT_KERNEL_SPEC; o.spec_mode = SPARSERT_SPEC_MFMA;
+            cands.push_back(o);
+        }
         add_direct(1);
         if (!conv && f16 && N % 2 == 0) add_direct(2);
         if (!conv && i8 && N % 4 == 0) add_direct(4);
@@ -243,7 +255,7 @@ static int tune_impl(const int32_t *row_ptr, const int32_t *col_idx, const void 
         const int64_t vt = (N + 63) / 64 * std::max(1, b.batch);
         std::vector<sparsert_options> rows_family, spec_family;
         for (const sparsert_options &o : cands)
-            if (o.kernel != SPARSERT_KERNEL_SPEC) rows_family.push_back(o);
+            if (o.kernel != SPARSERT_KERNEL_SPEC || o.spec_mode == SPARSERT_SPEC_MFMA) rows_family.push_back(o);   // nothing to assemble
         auto direct = [&](int ks, int t) {
             sparsert_options o = b;
             o.kernel = SPARSERT_KERNEL_SPEC; o.spec_mode = SPARSERT_SPEC_DIRECT;
@@ -397,7 +409,7 @@ static int tune_impl(const int32_t *row_ptr, const int32_t *col_idx, const void 
     }
     // Last candidate: the winner's configuration with its blocks formed by similarity (row swizzle).
     if (key(best_t) > 0.0f && best->host.kernel == SPARSERT_KERNEL_SPEC && best->host.spec.rows_per_group > 1 &&
-        !b.natural_order) {
+        best->host.spec.mode != SPARSERT_SPEC_MFMA && !b.natural_order) {
         const sparsert::SpecPlan &w = best->host.spec;
         sparsert_options o = b;
         o.kernel = SPARSERT_KERNEL_SPEC; o.spec_mode = w.mode; o.spec_rows = w.rows_per_group;
@@ -416,7 +428,7 @@ static int tune_impl(const int32_t *row_ptr, const int32_t *col_idx, const void 
     }
     // ... and the winner with its waves prefetching their code: kept if it is worth at least 1.5 %
     // under the condition the ranking uses (it costs time while the code is still in the L2)
-    if (key(best_t) > 0.0f && best->host.kernel == SPARSERT_KERNEL_SPEC) {
+    if (key(best_t) > 0.0f && best->host.kernel == SPARSERT_KERNEL_SPEC && best->host.spec.mode != SPARSERT_SPEC_MFMA) {
         const sparsert::SpecPlan &w = best->host.spec;
         sparsert_options o = b;
         o.kernel = SPARSERT_KERNEL_SPEC; o.spec_mode = w.mode; o.spec_rows = w.rows_per_group;

@@ -19,7 +19,7 @@ F32, F16, I8 = 0, 1, 2
 _DTYPE_OF = {np.dtype(np.float32): F32, np.dtype(np.float16): F16, np.dtype(np.int8): I8}
 _NP_OF = {F32: np.float32, F16: np.float16, I8: np.int8}
 KERNEL_AUTO, KERNEL_ROWS, KERNEL_SPEC = 0, 1, 2
-SPEC_AUTO, SPEC_DIRECT, SPEC_LDS = 0, 1, 2
+SPEC_AUTO, SPEC_DIRECT, SPEC_LDS, SPEC_MFMA = 0, 1, 2, 3
 (FIELD_INFO, FIELD_ROW_NNZ, FIELD_HIST, FIELD_PERM, FIELD_INV_PERM, FIELD_P_ROW_PTR,
  FIELD_P_COL_IDX, FIELD_P_VALS, FIELD_BINS, FIELD_STREAM, FIELD_CONV_SEG,
  FIELD_SEGMENTS, FIELD_SPEC_GROUPS, FIELD_SPEC_COLUMNS, FIELD_SPEC_CODE, FIELD_KERNEL_NAME) = range(16)
