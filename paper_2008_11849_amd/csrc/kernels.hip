@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstring>
 #include <mutex>
 #include <type_traits>
@@ -285,65 +286,7 @@ bool on_plan_device(const DevicePlan &d) {
     return hipGetDevice(&dev) == hipSuccess && dev == d.device;
 }
 
-int upload_plan(const HostPlan &h, DevicePlan &d, std::string &err) {
-    HIP_TRY(hipGetDevice(&d.device));
-    if (int rc = to_device(h.p_row_ptr.data(), h.p_row_ptr.size(), &d.p_row_ptr, err)) return rc;
-    if (int rc = to_device(h.perm.data(), h.perm.size(), &d.perm, err)) return rc;
-    {   // the executor may read up to 16 {word, value} pairs past the last nonzero
-        std::vector<uint32_t> padded(h.stream);
-        padded.resize(h.stream.size() + 32, 0u);
-        if (int rc = to_device(padded.data(), padded.size(), &d.stream, err)) return rc;
-    }
-    if (int rc = to_device(h.segments.data(), h.segments.size(), &d.segments, err)) return rc;
-    if (int rc = to_device(h.conv_seg.data(), h.conv_seg.size(), &d.conv_seg, err)) return rc;
-    if (h.kernel == SPARSERT_KERNEL_SPEC && h.spec.mode == SPARSERT_SPEC_MFMA) {
-        std::vector<uint8_t> fragments;
-        mfma_pack(h, fragments);
-        if (int rc = to_device(fragments.data(), fragments.size(), reinterpret_cast<uint8_t **>(&d.mfma_weights), err)) return rc;
-        return to_device(h.inv_perm.data(), h.inv_perm.size(), &d.inv_perm, err);
-    }
-    if (h.kernel == SPARSERT_KERNEL_SPEC) {
-        int dev = 0, lds_max = 0;
-        HIP_TRY(hipGetDevice(&dev));
-        HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-        if (h.spec.lds_bytes > lds_max) {
-            err = "the generated kernel needs more LDS per workgroup than this device has";
-            return SPARSERT_EUNSUPPORTED;
-        }
-        hipModule_t mod = nullptr;
-        hipFunction_t fn = nullptr;
-        hipError_t e1 = hipModuleLoadData(&mod, h.spec.code.data());
-        if (e1 != hipSuccess) { err = std::string("loading the generated kernel: ") + hipGetErrorString(e1); return SPARSERT_ECOMPILE; }
-        d.spec_module = mod;
-        hipError_t e2 = hipModuleGetFunction(&fn, mod, h.spec.symbol.c_str());
-        if (e2 != hipSuccess) { err = std::string("generated kernel symbol: ") + hipGetErrorString(e2); return SPARSERT_ECOMPILE; }
-        d.spec_function = fn;
-    }
-    return SPARSERT_OK;
-}
-
-void free_device_plan(DevicePlan &d) {
-    if (d.p_row_ptr) (void)hipFree(d.p_row_ptr);
-    if (d.perm) (void)hipFree(d.perm);
-    if (d.stream) (void)hipFree(d.stream);
-    if (d.segments) (void)hipFree(d.segments);
-    if (d.conv_seg) (void)hipFree(d.conv_seg);
-    if (d.inv_perm) (void)hipFree(d.inv_perm);
-    if (d.mfma_weights) (void)hipFree(d.mfma_weights);
-    if (d.spec_module) (void)hipModuleUnload(static_cast<hipModule_t>(d.spec_module));
-    d = DevicePlan();
-}
-
-template <typename T, int V, bool CONV>
-static int launch_one(const RowsArgs &a, int images, hipStream_t s, std::string &err) {
-    const unsigned grid = (unsigned)a.tasks_per_xcd * 8u;
-    hipLaunchKernelGGL((rows_kernel<T, V, CONV>), dim3(grid, (unsigned)images), dim3(kGy * kWave), 0, s, a);
-    HIP_TRY(hipGetLastError());
-    return SPARSERT_OK;
-}
-
-int launch_rows(const HostPlan &h, const DevicePlan &d, const void *in, void *out,
-                void *stream, std::string &err) {
+static int prepare_rows(const HostPlan &h, DevicePlan &d, std::string &err) {
     // Host-side shape checks: the kernel assumes exactly these relations.
     const int64_t nvc = h.N / h.vec;
     if (h.vec < 1 || h.N % h.vec || h.ldb < h.N || h.ldc < h.N || h.ldb % h.vec || h.ldc % h.vec || h.gy != kGy || h.lanes_per_tile < 1 || h.lanes_per_tile > kWave ||
@@ -359,7 +302,7 @@ int launch_rows(const HostPlan &h, const DevicePlan &d, const void *in, void *ou
     a.p_row_ptr = d.p_row_ptr; a.perm = d.perm;
     a.stream = reinterpret_cast<const uint2 *>(d.stream);
     a.segments = d.segments; a.conv_seg = d.conv_seg;
-    a.in = in; a.out = out;
+    a.in = nullptr; a.out = nullptr;   // of the call
     a.M = h.M; a.N = h.N; a.ldc = h.ldc;
     a.n_vec_cols = (int32_t)nvc; a.lanes_per_tile = h.lanes_per_tile; a.n_tiles = h.n_tiles;
     a.n_split = h.n_split; a.n_wg_rows = h.n_wg_rows;
@@ -371,29 +314,99 @@ int launch_rows(const HostPlan &h, const DevicePlan &d, const void *in, void *ou
     a.out_image_elems = (int64_t)h.M * h.ldc;
     const int images = h.batch;
     if (images < 1 || images > 65535) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool f16 = h.dtype == SPARSERT_F16;
-    if (h.dtype == SPARSERT_I8) {
-        if (h.conv && h.vec != 1) { err = "conv plans use vec = 1"; return SPARSERT_EINVAL; }
-        if (h.conv) return launch_one<int8_t, 1, true>(a, images, s, err);
-        if (h.vec == 1) return launch_one<int8_t, 1, false>(a, images, s, err);
-        if (h.vec == 4) return launch_one<int8_t, 4, false>(a, images, s, err);
-        err = "unsupported vec for this dtype";
-        return SPARSERT_EINVAL;
-    }
+    const void *kernel = nullptr;
+    const bool f16 = h.dtype == SPARSERT_F16, i8 = h.dtype == SPARSERT_I8;
     if (h.conv) {
         if (h.vec != 1) { err = "conv plans use vec = 1"; return SPARSERT_EINVAL; }
-        return f16 ? launch_one<_Float16, 1, true>(a, images, s, err) : launch_one<float, 1, true>(a, images, s, err);
+        kernel = i8 ? (const void *)rows_kernel<int8_t, 1, true> : f16 ? (const void *)rows_kernel<_Float16, 1, true> : (const void *)rows_kernel<float, 1, true>;
+    } else if (i8) {
+        kernel = h.vec == 1 ? (const void *)rows_kernel<int8_t, 1, false> : h.vec == 4 ? (const void *)rows_kernel<int8_t, 4, false> : nullptr;
+    } else {
+        switch (h.vec) {
+        case 1: kernel = f16 ? (const void *)rows_kernel<_Float16, 1, false> : (const void *)rows_kernel<float, 1, false>; break;
+        case 2: kernel = f16 ? (const void *)rows_kernel<_Float16, 2, false> : (const void *)rows_kernel<float, 2, false>; break;
+        case 4: kernel = f16 ? (const void *)rows_kernel<_Float16, 4, false> : (const void *)rows_kernel<float, 4, false>; break;
+        case 8: kernel = f16 ? (const void *)rows_kernel<_Float16, 8, false> : nullptr; break;
+        }
     }
-    switch (h.vec) {
-    case 1: return f16 ? launch_one<_Float16, 1, false>(a, images, s, err) : launch_one<float, 1, false>(a, images, s, err);
-    case 2: return f16 ? launch_one<_Float16, 2, false>(a, images, s, err) : launch_one<float, 2, false>(a, images, s, err);
-    case 4: return f16 ? launch_one<_Float16, 4, false>(a, images, s, err) : launch_one<float, 4, false>(a, images, s, err);
-    case 8:
-        if (f16) return launch_one<_Float16, 8, false>(a, images, s, err);
-        [[fallthrough]];
-    default: err = "unsupported vec for this dtype"; return SPARSERT_EINVAL;
+    if (!kernel) { err = "unsupported vec for this dtype"; return SPARSERT_EINVAL; }
+    static_assert(sizeof(RowsArgs) <= sizeof(d.launch.args), "room for the arguments");
+    hipFunction_t fn = nullptr;
+    HIP_TRY(hipGetFuncBySymbol(&fn, kernel));
+    d.launch.function = fn;
+    d.launch.grid[0] = (uint32_t)a.tasks_per_xcd * 8u; d.launch.grid[1] = (uint32_t)images; d.launch.grid[2] = 1;
+    d.launch.threads = kGy * kWave;
+    d.launch.arg_bytes = sizeof(a); d.launch.in_at = offsetof(RowsArgs, in); d.launch.out_at = offsetof(RowsArgs, out);
+    std::memcpy(d.launch.args, &a, sizeof(a));
+    return SPARSERT_OK;
+}
+
+static int prepare_spec(const HostPlan &h, DevicePlan &d, std::string &err) {
+    const SpecPlan &sp = h.spec;
+    int lds_max = 0;
+    HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, d.device));
+    if (sp.lds_bytes > lds_max) {
+        err = "the generated kernel needs more LDS per workgroup than this device has";
+        return SPARSERT_EUNSUPPORTED;
     }
+    hipModule_t mod = nullptr;
+    hipFunction_t fn = nullptr;
+    hipError_t e1 = hipModuleLoadData(&mod, sp.code.data());
+    if (e1 != hipSuccess) { err = std::string("loading the generated kernel: ") + hipGetErrorString(e1); return SPARSERT_ECOMPILE; }
+    d.spec_module = mod;
+    hipError_t e2 = hipModuleGetFunction(&fn, mod, sp.symbol.c_str());
+    if (e2 != hipSuccess) { err = std::string("generated kernel symbol: ") + hipGetErrorString(e2); return SPARSERT_ECOMPILE; }
+    if (!fn || sp.n_groups < 1 || sp.n_tiles < 1) { err = "plan has no generated kernel"; return SPARSERT_EINVAL; }
+    const int tpw = sp.tiles_per_wg;
+    if (tpw < 1 || tpw > 16 || (tpw & (tpw - 1))) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
+    const bool lds = sp.mode == SPARSERT_SPEC_LDS;
+    if (lds && (sp.n_blocks % tpw || sp.lds_bytes < 1 || sp.lds_bytes > 160 * 1024)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
+    if (sp.ksplit > 1 && (lds || sp.ksplit != tpw || sp.n_blocks != sp.n_groups * sp.ksplit)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
+    const unsigned gx = (lds || sp.ksplit > 1) ? (unsigned)sp.n_tiles : (unsigned)((sp.n_tiles + tpw - 1) / tpw);
+    const unsigned gy = lds ? (unsigned)(sp.n_blocks / tpw) : (unsigned)sp.n_groups;
+    // (that the workgroup's registers fit a compute unit was checked when the plan was generated;
+    // a loaded plan carries the symbol's own register count in its code object and is checked by the loader)
+    const unsigned gz = (unsigned)h.batch;   // the generated prologue offsets the operand and the result by problem
+    if (gz < 1 || gz > 65535) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
+    d.launch.function = fn;
+    d.launch.grid[0] = gx; d.launch.grid[1] = gy; d.launch.grid[2] = gz;
+    d.launch.threads = (uint32_t)(tpw * kWave);
+    d.launch.arg_bytes = 16; d.launch.in_at = 0; d.launch.out_at = 8;   // kernarg: B, C
+    return SPARSERT_OK;
+}
+
+int upload_plan(const HostPlan &h, DevicePlan &d, std::string &err) {
+    HIP_TRY(hipGetDevice(&d.device));
+    if (int rc = to_device(h.p_row_ptr.data(), h.p_row_ptr.size(), &d.p_row_ptr, err)) return rc;
+    if (int rc = to_device(h.perm.data(), h.perm.size(), &d.perm, err)) return rc;
+    {   // the executor may read up to 16 {word, value} pairs past the last nonzero
+        std::vector<uint32_t> padded(h.stream);
+        padded.resize(h.stream.size() + 32, 0u);
+        if (int rc = to_device(padded.data(), padded.size(), &d.stream, err)) return rc;
+    }
+    if (int rc = to_device(h.segments.data(), h.segments.size(), &d.segments, err)) return rc;
+    if (int rc = to_device(h.conv_seg.data(), h.conv_seg.size(), &d.conv_seg, err)) return rc;
+    if (h.kernel != SPARSERT_KERNEL_SPEC) return prepare_rows(h, d, err);
+    if (h.spec.mode == SPARSERT_SPEC_MFMA) {
+        std::vector<uint8_t> fragments;
+        mfma_pack(h, fragments);
+        if (int rc = to_device(fragments.data(), fragments.size(), reinterpret_cast<uint8_t **>(&d.mfma_weights), err)) return rc;
+        if (int rc = to_device(h.inv_perm.data(), h.inv_perm.size(), &d.inv_perm, err)) return rc;
+        return prepare_mfma(h, d, err);
+    }
+    return prepare_spec(h, d, err);
+}
+
+void free_device_plan(DevicePlan &d) {
+    if (d.p_row_ptr) (void)hipFree(d.p_row_ptr);
+    if (d.perm) (void)hipFree(d.perm);
+    if (d.stream) (void)hipFree(d.stream);
+    if (d.segments) (void)hipFree(d.segments);
+    if (d.conv_seg) (void)hipFree(d.conv_seg);
+    if (d.inv_perm) (void)hipFree(d.inv_perm);
+    if (d.mfma_weights) (void)hipFree(d.mfma_weights);
+    if (d.spec_module) (void)hipModuleUnload(static_cast<hipModule_t>(d.spec_module));
+    d = DevicePlan();
 }
 
 // ---------------------------------------------------------------- comparing two results of a plan
@@ -536,32 +549,21 @@ int displace_caches(void *scratch, size_t bytes, void *stream, std::string &err)
     return SPARSERT_OK;
 }
 
-int launch_spec(const HostPlan &h, const DevicePlan &d, const void *B, void *C,
-                void *stream, std::string &err) {
-    const SpecPlan &sp = h.spec;
-    if (sp.mode == SPARSERT_SPEC_MFMA) return launch_mfma(h, d, B, C, stream, err);
-    if (!d.spec_function || sp.n_groups < 1 || sp.n_tiles < 1) {
-        err = "plan has no generated kernel";
-        return SPARSERT_EINVAL;
-    }
-    struct { const void *B; void *C; } args = {B, C};
-    size_t size = sizeof(args);
-    void *config[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &args, HIP_LAUNCH_PARAM_BUFFER_SIZE, &size,
-                      HIP_LAUNCH_PARAM_END};
-    const int tpw = sp.tiles_per_wg;
-    if (tpw < 1 || tpw > 16 || (tpw & (tpw - 1))) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
-    const bool lds = sp.mode == SPARSERT_SPEC_LDS;
-    if (lds && (sp.n_blocks % tpw || sp.lds_bytes < 1 || sp.lds_bytes > 160 * 1024)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
-    if (sp.ksplit > 1 && (lds || sp.ksplit != tpw || sp.n_blocks != sp.n_groups * sp.ksplit)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
-    const unsigned gx = (lds || sp.ksplit > 1) ? (unsigned)sp.n_tiles : (unsigned)((sp.n_tiles + tpw - 1) / tpw);
-    const unsigned gy = lds ? (unsigned)(sp.n_blocks / tpw) : (unsigned)sp.n_groups;
-    // (that the workgroup's registers fit a compute unit was checked when the plan was generated;
-    // a loaded plan carries the symbol's own register count in its code object and is checked by the loader)
-    const unsigned gz = (unsigned)h.batch;   // the generated prologue offsets the operand and the result by problem
-    if (gz < 1 || gz > 65535) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
-    HIP_TRY(hipModuleLaunchKernel(static_cast<hipFunction_t>(d.spec_function), gx, gy, gz, tpw * kWave, 1, 1,
-                                  0, static_cast<hipStream_t>(stream), nullptr, config));
+// A call: the plan's arguments with the call's two addresses in them.
+static int launch(const DevicePlan &d, const void *in, void *out, void *stream, std::string &err) {
+    const DevicePlan::Launch &l = d.launch;
+    alignas(16) unsigned char args[sizeof(l.args)];
+    std::memcpy(args, l.args, sizeof(args));
+    std::memcpy(args + l.in_at, &in, sizeof(in));
+    std::memcpy(args + l.out_at, &out, sizeof(out));
+    size_t size = l.arg_bytes;
+    void *config[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, args, HIP_LAUNCH_PARAM_BUFFER_SIZE, &size, HIP_LAUNCH_PARAM_END};
+    HIP_TRY(hipModuleLaunchKernel(static_cast<hipFunction_t>(l.function), l.grid[0], l.grid[1], l.grid[2], l.threads, 1, 1, 0,
+                                  static_cast<hipStream_t>(stream), nullptr, config));
     return SPARSERT_OK;
 }
+
+int launch_rows(const HostPlan &, const DevicePlan &d, const void *in, void *out, void *stream, std::string &err) { return launch(d, in, out, stream, err); }
+int launch_spec(const HostPlan &, const DevicePlan &d, const void *in, void *out, void *stream, std::string &err) { return launch(d, in, out, stream, err); }
 
 }  // namespace sparsert

@@ -29,6 +29,7 @@
 // 3072 x 768 x 1024 half at 95 %: 11.3 and 9.3 us; 768 x 3072 x 1024 int8 at 95 %: 13.9 and 9.6 us.
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstring>
 #include <string>
 #include <type_traits>
@@ -338,7 +339,7 @@ void mfma_pack(const HostPlan &h, std::vector<uint8_t> &out) {
     }
 }
 
-int launch_mfma(const HostPlan &h, const DevicePlan &d, const void *in, void *out, void *stream, std::string &err) {
+int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err) {
     const SpecPlan &sp = h.spec;
     if (!d.mfma_weights || sp.mfma_config < 0 || sp.mfma_config >= kMfmaConfigCount || h.N < 16 || h.batch < 1 || h.batch > 65535) {
         err = "plan geometry is inconsistent";
@@ -347,7 +348,7 @@ int launch_mfma(const HostPlan &h, const DevicePlan &d, const void *in, void *ou
     const MfmaConfig &c = kMfmaConfigs[sp.mfma_config];
     const int esz = h.elem_size(), slab = c.steps * mfma_step(esz);
     MfmaArgs a;
-    a.weights = d.mfma_weights; a.in = in; a.out = out;
+    a.weights = d.mfma_weights; a.in = nullptr; a.out = nullptr;   // of the call
     a.p_row_ptr = d.p_row_ptr; a.inv_perm = d.inv_perm; a.stream = reinterpret_cast<const uint2 *>(d.stream);
     a.M = h.M; a.K = h.K; a.N = h.N; a.ldb = h.ldb; a.ldc = h.ldc;
     a.n_slabs = (a.K + slab - 1) / slab; a.k_steps = a.n_slabs * c.steps;
@@ -364,17 +365,23 @@ int launch_mfma(const HostPlan &h, const DevicePlan &d, const void *in, void *ou
     a.weight_bytes = (int32_t)weight_bytes;
     a.out_bytes = (int32_t)(((int64_t)(h.M - 1) * h.ldc + h.N) * h.out_elem_size());
     a.in_stride = (int64_t)h.K * h.ldb; a.out_stride = (int64_t)h.M * h.ldc;
-    const dim3 grid((unsigned)a.tasks_per_xcd * 8u, (unsigned)h.batch), wg((unsigned)c.waves() * kWave);
-    hipStream_t s = static_cast<hipStream_t>(stream);
+    const void *kernel = nullptr;
     switch (sp.mfma_config * 2 + (h.dtype == SPARSERT_I8 ? 1 : 0)) {
-#define X(id, tm, tn, wm, wn, mf, nf, steps, stages, ...)                                                                  \
-    case id * 2 + 0: hipLaunchKernelGGL((mfma_kernel<0, wm, wn, mf, nf, steps, stages>), grid, wg, 0, s, a); break; \
-    case id * 2 + 1: hipLaunchKernelGGL((mfma_kernel<1, wm, wn, mf, nf, steps, stages>), grid, wg, 0, s, a); break;
+#define X(id, tm, tn, wm, wn, mf, nf, steps, stages, ...)                                              \
+    case id * 2 + 0: kernel = (const void *)mfma_kernel<0, wm, wn, mf, nf, steps, stages>; break; \
+    case id * 2 + 1: kernel = (const void *)mfma_kernel<1, wm, wn, mf, nf, steps, stages>; break;
         SPARSERT_MFMA_CONFIGS(X)
 #undef X
     }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) { err = std::string("matrix-core kernel launch: ") + hipGetErrorString(e); return SPARSERT_EHIP; }
+    hipFunction_t fn = nullptr;
+    const hipError_t e = hipGetFuncBySymbol(&fn, kernel);
+    if (e != hipSuccess) { err = std::string("matrix-core kernel: ") + hipGetErrorString(e); return SPARSERT_EHIP; }
+    static_assert(sizeof(MfmaArgs) <= sizeof(d.launch.args), "room for the arguments");
+    d.launch.function = fn;
+    d.launch.grid[0] = (uint32_t)a.tasks_per_xcd * 8u; d.launch.grid[1] = (uint32_t)h.batch; d.launch.grid[2] = 1;
+    d.launch.threads = (uint32_t)(c.waves() * kWave);
+    d.launch.arg_bytes = sizeof(a); d.launch.in_at = offsetof(MfmaArgs, in); d.launch.out_at = offsetof(MfmaArgs, out);
+    std::memcpy(d.launch.args, &a, sizeof(a));
     return SPARSERT_OK;
 }
 

@@ -83,7 +83,14 @@ struct DevicePlan {
     int32_t *inv_perm = nullptr;    // MFMA plans
     void *mfma_weights = nullptr;   // MFMA plans: A as matrix-core fragments
     void *spec_module = nullptr;    // hipModule_t
-    void *spec_function = nullptr;  // hipFunction_t
+    // What a call launches, settled when the plan is uploaded: a call copies the kernel's arguments, writes
+    // its two pointers into them and launches.
+    struct Launch {
+        void *function = nullptr;    // hipFunction_t
+        uint32_t grid[3] = {0, 0, 0}, threads = 0;
+        uint32_t arg_bytes = 0, in_at = 0, out_at = 0;   // offsets of the operand's and the result's address
+        alignas(16) unsigned char args[160] = {};
+    } launch;
 };
 
 // Host analysis.  Returns SPARSERT_OK or an error code with `err` filled in.
@@ -125,7 +132,7 @@ int launch_spec(const HostPlan &h, const DevicePlan &d, const void *B, void *C,
                 void *stream, std::string &err);
 // Matrix-core executor (mfma.hip).
 void mfma_pack(const HostPlan &h, std::vector<uint8_t> &out);
-int launch_mfma(const HostPlan &h, const DevicePlan &d, const void *in, void *out, void *stream, std::string &err);
+int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err);   // fills d.launch
 // Comparison of two results of a plan (kernels.hip).  launch_compare: two kernels on `stream`,
 // partials_dev must hold 4 words per block of compare_blocks(h), result_dev receives 4 words.
 int64_t compare_blocks(const HostPlan &h);

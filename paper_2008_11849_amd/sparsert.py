@@ -84,6 +84,10 @@ if not os.path.exists(LIB_PATH):
     raise ImportError(f"{LIB_PATH} is missing: run `python __graft_entry__.py` to build the HIP library")
 
 _lib = ctypes.CDLL(LIB_PATH)
+try:
+    from . import _fastcall
+except ImportError as e:
+    raise ImportError("_fastcall is missing or does not load: run `python __graft_entry__.py` to build it") from e
 _vp, _i32 = ctypes.c_void_p, ctypes.c_int32
 _lib.sparsert_inspect.argtypes = [_vp, _vp, _vp, _i32, _i32, _i32, ctypes.POINTER(Options),
                                   ctypes.POINTER(_vp)]
@@ -241,14 +245,18 @@ def load(blob: bytes, host_only: bool = False) -> Plan:
     return plan
 
 
-def spmm(plan: Plan, B_dev: int, C_dev: int, stream: int = 0):
-    """sparsert_spmm: device addresses and a hipStream_t as integers."""
+def _spmm(plan: Plan, B_dev: int, C_dev: int, stream: int = 0):
     _check(_lib.sparsert_spmm(plan.handle, B_dev, C_dev, stream))
 
 
-def conv3x3(plan: Plan, X_dev: int, Y_dev: int, stream: int = 0):
-    """sparsert_conv3x3: device addresses and a hipStream_t as integers."""
+def _conv3x3(plan: Plan, X_dev: int, Y_dev: int, stream: int = 0):
     _check(_lib.sparsert_conv3x3(plan.handle, X_dev, Y_dev, stream))
+
+
+# The two calls of the latency path: plain integer arguments are marshalled in C (fastcall.c),
+# anything else ctypes takes goes through the two functions above.
+_fastcall.bind(ctypes.cast(_lib.sparsert_spmm, _vp).value, ctypes.cast(_lib.sparsert_conv3x3, _vp).value, _spmm, _conv3x3, _check)
+spmm, conv3x3 = _fastcall.spmm, _fastcall.conv3x3
 
 
 def compare_outputs(plan: Plan, a_dev: int, b_dev: int, result_dev: int, stream: int = 0):
