@@ -5,6 +5,7 @@
 #include <string>
 
 #include "plan.h"
+#include "staged_rows.h"
 
 namespace {
 thread_local std::string g_err;
@@ -143,6 +144,11 @@ int sparsert_plan_export(const sparsert_plan *plan, int32_t field, void *buf, si
     case SPARSERT_FIELD_KERNEL_NAME:
         if (h.kernel == SPARSERT_KERNEL_SPEC) {
             name = h.spec.symbol;
+        } else if (const sparsert::StagedRows s = sparsert::staged_rows_shape(h); s.V) {
+            const std::string shape = "Li" + std::to_string(s.V) + "ELi" + std::to_string(s.rows_per_wave) + "EEEvNS_10StagedArgsE";
+            name = h.dtype == SPARSERT_F16 ? "_ZN8sparsert18staged_rows_kernelIDF16_" + shape
+                                           : std::string("void sparsert::staged_rows_kernel<") + (h.dtype == SPARSERT_I8 ? "signed char" : "float") + ", " +
+                                                 std::to_string(s.V) + ", " + std::to_string(s.rows_per_wave) + ">(sparsert::StagedArgs)";
         } else if (h.dtype == SPARSERT_F16) {
             // the profiler's demangler does not know the half type and shows the symbol as it is
             name = "_ZN8sparsert11rows_kernelIDF16_Li" + std::to_string(h.vec) + "ELb" + (h.conv ? "1" : "0") + "EEEvNS_8RowsArgsE";

@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "plan.h"
+#include "staged_rows.h"
 
 namespace sparsert {
 
@@ -379,6 +380,16 @@ int upload_plan(const HostPlan &h, DevicePlan &d, std::string &err) {
     HIP_TRY(hipGetDevice(&d.device));
     if (int rc = to_device(h.p_row_ptr.data(), h.p_row_ptr.size(), &d.p_row_ptr, err)) return rc;
     if (int rc = to_device(h.perm.data(), h.perm.size(), &d.perm, err)) return rc;
+    if (staged_rows_shape(h).V) {
+        StagedPack pack;
+        staged_rows_pack(h, pack);
+        if (int rc = to_device(pack.stream.data(), pack.stream.size(), &d.stream, err)) return rc;
+        d.staged_stream_bytes = pack.stream.size() * sizeof(uint32_t);
+        if (int rc = to_device(pack.counts.data(), pack.counts.size(), &d.staged_counts, err)) return rc;
+        if (int rc = to_device(pack.starts.data(), pack.starts.size(), &d.staged_starts, err)) return rc;
+        if (int rc = to_device(pack.rows.data(), pack.rows.size(), &d.staged_rows, err)) return rc;
+        return prepare_staged_rows(h, d, err);
+    }
     {   // the executor may read up to 16 {word, value} pairs past the last nonzero
         std::vector<uint32_t> padded(h.stream);
         padded.resize(h.stream.size() + 32, 0u);
@@ -403,6 +414,9 @@ void free_device_plan(DevicePlan &d) {
     if (d.stream) (void)hipFree(d.stream);
     if (d.segments) (void)hipFree(d.segments);
     if (d.conv_seg) (void)hipFree(d.conv_seg);
+    if (d.staged_counts) (void)hipFree(d.staged_counts);
+    if (d.staged_starts) (void)hipFree(d.staged_starts);
+    if (d.staged_rows) (void)hipFree(d.staged_rows);
     if (d.inv_perm) (void)hipFree(d.inv_perm);
     if (d.mfma_weights) (void)hipFree(d.mfma_weights);
     if (d.spec_module) (void)hipModuleUnload(static_cast<hipModule_t>(d.spec_module));

@@ -36,6 +36,7 @@
 #include <utility>
 #include <vector>
 
+#include "lds_copy.h"
 #include "mfma.h"
 #include "plan.h"
 
@@ -48,7 +49,6 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half4_any __attribute__((ext_vector_type(4), aligned(2)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef int32_t int2v __attribute__((ext_vector_type(2)));
-typedef int32_t int4v __attribute__((ext_vector_type(4)));
 typedef int32_t int4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef uint32_t uint4_any __attribute__((ext_vector_type(4), aligned(1)));
@@ -103,20 +103,6 @@ __device__ __forceinline__ float exact_element(const MfmaArgs &a, const _Float16
 
 template <typename F, int... I> __device__ __forceinline__ void each_constant(F f, std::integer_sequence<int, I...>) {
     (f(std::integral_constant<int, I>()), ...);
-}
-
-template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
-// 16 bytes per lane from descriptor + voffset + soffset + OFFSET straight to LDS at lds_base + OFFSET + 16 * lane.
-// Written as assembly because the compiler would otherwise wait for every copy before any read of LDS.
-template <int OFFSET> __device__ __forceinline__ void copy_to_lds(const int4v &rsrc, int voffset, int soffset, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
-                 ::"s"(lds_base), "v"(voffset), "s"(rsrc), "s"(soffset), "n"(OFFSET) : "memory");
-}
-
-__device__ __forceinline__ int4v descriptor(const void *p, int bytes) {
-    const uint64_t u = (uint64_t)p;
-    return int4v{(int)(uint32_t)u, (int)((uint32_t)(u >> 32) & 0xffffu), bytes, 0x00020000};
 }
 
 template <int DT, int WM, int WN, int MF, int NF, int STEPS, int STAGES>

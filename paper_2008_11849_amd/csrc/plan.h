@@ -80,6 +80,9 @@ struct DevicePlan {
     uint32_t *stream = nullptr;
     int32_t *conv_seg = nullptr;
     int32_t *segments = nullptr;
+    uint8_t *staged_counts = nullptr;   // staged row-walk plans (staged_rows.hip)
+    size_t staged_stream_bytes = 0;
+    int32_t *staged_starts = nullptr, *staged_rows = nullptr;
     int32_t *inv_perm = nullptr;    // MFMA plans
     void *mfma_weights = nullptr;   // MFMA plans: A as matrix-core fragments
     void *spec_module = nullptr;    // hipModule_t
@@ -130,6 +133,14 @@ int launch_rows(const HostPlan &h, const DevicePlan &d, const void *B, void *C,
                 void *stream, std::string &err);
 int launch_spec(const HostPlan &h, const DevicePlan &d, const void *B, void *C,
                 void *stream, std::string &err);
+// Row-walk kernel with B staged through LDS (staged_rows.hip); its shape: staged_rows.h.
+struct StagedPack {
+    std::vector<uint32_t> stream;
+    std::vector<uint8_t> counts;
+    std::vector<int32_t> starts, rows;
+};
+void staged_rows_pack(const HostPlan &h, StagedPack &out);
+int prepare_staged_rows(const HostPlan &h, DevicePlan &d, std::string &err);   // fills d.launch
 // Matrix-core executor (mfma.hip).
 void mfma_pack(const HostPlan &h, std::vector<uint8_t> &out);
 int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err);   // fills d.launch

@@ -1,0 +1,89 @@
+// Which plans take the staged row-walk kernel (staged_rows.hip), and in what shape.  Host code only.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+#include "plan.h"
+
+namespace sparsert {
+
+constexpr int kStagedWaves = 16;            // waves per workgroup
+constexpr int kStagedLdsBytes = 160 * 1024;
+constexpr int kStagedTouchBytes = 256;      // corner of LDS that the stream's cache-line touches land in
+
+struct StagedRows {
+    int V = 0;             // columns per lane; 0: the plan does not take this kernel
+    int rows_per_wave = 0; // 4 or 8
+    int lanes = 0, tiles = 0, groups = 0;   // lanes that own columns, column tiles, row groups
+    int pitch = 0;         // bytes of a row of the tile in LDS
+    int chunk = 0, chunks = 0;   // rows of B per LDS buffer
+    double microseconds = 0;     // what it is expected to take
+};
+
+// The estimates below are fits to 230 products drawn from M, K <= 4096, N from 49 to 4096 and 80 % to 98 %
+// zeros (126 fp32, the rest half and int8; a quarter of them with skewed rows): 8 % to 10 % root mean square
+// for the staged kernel, 22 % for the plain one.  Microseconds.
+
+// Staged: a start, then per round of workgroups a fixed cost per chunk (barrier, first loads), the copied
+// bytes and the operands read from LDS; the longest row as one wave's serial
+// chain, whatever else runs; and the results.
+inline double staged_rows_microseconds(const HostPlan &h, const StagedRows &s, int32_t longest) {
+    static const double fit[5][6] = {{1.83, 0.913, 0.43, 4.13, 15.9, 0.335},   // fp32, V = 2, four rows
+                                     {2.18, 0.873, 2.38, 4.05, 15.6, 0.260},   // fp32, V = 2, eight rows
+                                     {2.14, 0.481, 5.69, 2.48, 18.9, 0.259},   // fp32, V = 4
+                                     {2.26, 0.941, 0.00, 4.47, 18.8, 0.367},   // half
+                                     {2.44, 0.326, 3.85, 12.7, 22.9, 0.231}};  // int8
+    const double *f = fit[h.dtype == SPARSERT_I8 ? 4 : h.dtype == SPARSERT_F16 ? 3 : s.V == 4 ? 2 : s.rows_per_wave / 8];
+    const int esz = h.elem_size(), slots = s.groups * kStagedWaves * s.rows_per_wave;
+    const double wgs = (double)s.groups * s.tiles * h.batch;
+    const double rounds = wgs > 1024 ? wgs / 256 : (double)(((int64_t)wgs + 255) / 256);
+    const double pairs = (double)h.nnz / s.groups + 0.5 * s.chunks * kStagedWaves * s.rows_per_wave * std::min(1.0, (double)h.M / slots);
+    return f[0] + rounds * (f[1] * s.chunks + 1e-6 * f[2] * h.K * s.pitch + 1e-6 * f[3] * pairs * kWave * s.V * esz)
+         + 1e-3 * f[4] * longest + 1e-6 * f[5] * h.M * h.N * (double)h.batch * h.out_elem_size();
+}
+
+// Plain: the wave loads of B (one per nonzero and column tile; part of the cost is per load, part per byte),
+// the longest chain of one wave, and the results.
+inline double plain_rows_microseconds(const HostPlan &h, int32_t longest) {
+    static const double fit[3][5] = {{2.42, 0.58, 0.69, 2.23, 0.44}, {2.78, 0.69, 0.79, 2.11, 0.50}, {2.53, 0.82, 1.11, 2.44, 0.34}};
+    const double *f = fit[h.dtype == SPARSERT_F32 ? 0 : h.dtype == SPARSERT_F16 ? 1 : 2];
+    const double chain = longest < h.split_threshold ? longest : longest / (double)kGy;
+    return f[0] + 1e-5 * (double)h.nnz * h.n_tiles * h.batch * (f[1] + f[2] * h.vec * h.elem_size() / 4.0)
+         + 1e-2 * f[3] * chain + 1e-6 * f[4] * h.M * h.N * (double)h.batch * h.out_elem_size();
+}
+
+// The staged kernel pays where many nonzeros share a workgroup's copy of B; few columns, few rows, a long K
+// with few nonzeros per chunk, or one row much longer than the rest leave it behind (1/2 to 2 times the plain
+// kernel's time over the products above), so it is taken where it is estimated to need less than 0.8 of the
+// plain kernel's time: 58 of the 230, which gain 1.53 times, 3 of them losing 5 % to 12 %.
+inline StagedRows staged_rows_shape(const HostPlan &h) {
+    StagedRows best;
+    if (h.kernel != SPARSERT_KERNEL_ROWS || h.conv) return best;
+    const int esz = h.elem_size();
+    // 4-byte accesses past the operand's end are dropped whole: the copies need rows that end on 4 bytes.
+    if ((int64_t)h.ldb * esz % 4 || (int64_t)h.N * esz % 4 || (int64_t)h.K * h.ldb * esz >= (1ll << 31)) return best;
+    int32_t longest = 0;
+    for (int32_t i = 0; i < h.M; ++i) longest = std::max(longest, h.p_row_ptr[i + 1] - h.p_row_ptr[i]);
+    static const int shapes[3][2] = {{4, 4}, {2, 4}, {2, 8}};   // V, rows per wave; the last two: fp32 only
+    for (int i = 0; i < (esz == 4 ? 3 : 1); ++i) {
+        StagedRows s;
+        s.V = shapes[i][0]; s.rows_per_wave = shapes[i][1];
+        const int nvc = (h.N + s.V - 1) / s.V;
+        s.tiles = (nvc + kWave - 1) / kWave;
+        s.lanes = (nvc + s.tiles - 1) / s.tiles;
+        const int64_t per_round = 256 / std::min<int64_t>(256, (int64_t)s.tiles * h.batch);   // row groups that fit one round of workgroups
+        s.groups = (h.M + kStagedWaves * s.rows_per_wave - 1) / (kStagedWaves * s.rows_per_wave);
+        if (s.groups < per_round) s.groups = (int)std::min<int64_t>(per_round, (h.M + kStagedWaves - 1) / kStagedWaves);
+        s.pitch = (s.lanes * s.V * esz + 15) / 16 * 16;
+        // two buffers of a chunk and one row of zeros each; a row's count of pairs of a chunk, in twos, fits a byte
+        s.chunk = std::min(510, (kStagedLdsBytes - 2048) / 2 / s.pitch - 1);
+        s.chunk = std::min(s.chunk, h.K);
+        s.chunks = (h.K + s.chunk - 1) / s.chunk;
+        s.microseconds = staged_rows_microseconds(h, s, longest);
+        if (best.V == 0 || s.microseconds < best.microseconds) best = s;
+    }
+    if (best.microseconds > 0.8 * plain_rows_microseconds(h, longest)) best.V = 0;
+    return best;
+}
+
+}  // namespace sparsert

@@ -1,0 +1,256 @@
+// Row-walk SpMM with B staged through LDS, for products that are long enough to fill the chip with it.
+//
+// The plain row-walk kernel (kernels.hip) fetches a row segment of B through the vector-memory path for
+// every nonzero and column tile, and that path delivers about 30 bytes per clock and compute unit: on
+// 4096 x 4096 at 90 % with 784 columns it was all of the 287 us.  Here a workgroup copies the column tile's
+// rows of B into LDS once, chunk by chunk (two buffers, the next chunk travels while one is worked on), for
+// all of its 64 or 128 rows of A, and every nonzero reads its operand there.  LDS, 128 bytes per clock, is
+// the bound: for the same product 87 us of operand reads (49 of 64 lanes own columns), 15 % of pairs that
+// only fill up, 25 us of copies into it; measured 142.7 us.  Half and int8 move fewer bytes per nonzero and
+// are bound by the instructions per nonzero (2048 x 2048 at 95 %, 784 columns: half 39.2 -> 25.9 us, int8
+// 41.0 -> 24.7 us).
+//
+// A wave owns up to RW rows, whose accumulators stay in registers over all chunks.  The nonzeros are laid
+// out in the order the waves meet them - row group, wave, chunk, row - so a wave walks one contiguous
+// stream of {LDS offset of the operand row, value} pairs with scalar loads, four pairs at a time and two at
+// the end of a row's share; how many twos belong to each of its rows comes packed in bytes, one word or two
+// per chunk.  A share of odd length is filled up with a zero value times a row of zeros behind the chunk,
+// never with elements of B.  (Shares in fours only: 147.6 us.)  Row groups and waves are dealt in serpentine
+// order over the rows by descending length.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstddef>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "lds_copy.h"
+#include "staged_rows.h"
+
+namespace sparsert {
+
+struct StagedArgs {
+    const uint2 *stream;          // {LDS byte offset, value bits}
+    const uint32_t *counts;       // [group][wave][chunk][RW bytes]
+    const int32_t *starts;        // [group][wave]: first stream position
+    const int32_t *rows;          // [group][wave][RW]: row of C, -1 for none
+    const void *in;
+    void *out;
+    int32_t N, ldb, ldc, in_bytes;
+    int32_t lanes, tiles, groups, tasks_per_xcd;
+    int32_t stream_bytes, pitch, chunk, chunks, buffer;   // buffer: bytes of one of the two LDS buffers
+    int64_t in_stride, out_stride;          // elements between the problems of a batch (grid y)
+};
+
+// Operands, multiply-adds and results of one storage type at V columns per lane.
+template <typename T, int V> struct StagedOps {
+    typedef float acc_t;
+    typedef T out_t;
+    typedef T opd_t __attribute__((ext_vector_type(V)));
+    static __device__ __forceinline__ void mad(float (&acc)[V], uint32_t word, const opd_t &b) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) acc[j] = __builtin_fmaf(__uint_as_float(word), (float)b[j], acc[j]);
+    }
+};
+template <> struct StagedOps<int8_t, 4> {   // the four packed columns stay in their dword; v_dot4 picks column j out
+    typedef int32_t acc_t;
+    typedef int32_t out_t;
+    typedef int32_t opd_t;
+    static __device__ __forceinline__ void mad(int32_t (&acc)[4], uint32_t word, const opd_t &b) {
+        const uint32_t a8 = word & 0xffu;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_sdot4(b, (int32_t)(a8 << (8 * j)), acc[j], false);
+    }
+};
+
+template <typename T, int V, int RW>
+__global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(const StagedArgs a) {
+    typedef StagedOps<T, V> Q;
+    typedef typename Q::opd_t opd_t;
+    typedef typename Q::out_t out_t;
+    typedef typename Q::acc_t acc_t;
+    constexpr int COPIES = kStagedLdsBytes / 2 / 1024 / kStagedWaves;   // 1 KiB copies per wave and chunk, at most
+    __shared__ __align__(1024) char lds[kStagedLdsBytes];
+    const int task = (int)(blockIdx.x & 7) * a.tasks_per_xcd + (int)(blockIdx.x >> 3);
+    if (task >= a.tiles * a.groups) return;
+    const int tile = task / a.groups, group = task - tile * a.groups;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const T *in = static_cast<const T *>(a.in) + (int64_t)blockIdx.y * a.in_stride;
+    const int col0 = tile * a.lanes * V;
+
+    // this lane's 16 bytes of every copy of a chunk; what lies past the operand arrives as zeros
+    const int4v rin = descriptor(in, a.in_bytes), rstream = descriptor(a.stream, a.stream_bytes);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    const int per_row = a.pitch >> 4;
+    int off[COPIES];
+#pragma unroll
+    for (int i = 0; i < COPIES; ++i) {
+        const int unit = (i * kStagedWaves + wave) * 64 + lane, row = unit / per_row;
+        // (rows past the chunk: zeros; the first of them is what the pairs that fill a group up refer to)
+        off[i] = row < a.chunk ? row * a.ldb * (int)sizeof(T) + col0 * (int)sizeof(T) + (unit - row * per_row) * 16 : (int)0x80000000;
+    }
+    auto issue = [&](int c) {
+        const int from = c * a.chunk * a.ldb * (int)sizeof(T);
+        const uint32_t to = lds0 + (uint32_t)(c & 1) * (uint32_t)a.buffer;
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i)
+            if ((i * kStagedWaves + wave) * 1024 < a.buffer) copy_to_lds<0>(rin, off[i], from, to + (uint32_t)(i * kStagedWaves + wave) * 1024);
+    };
+
+    acc_t acc[RW][V];
+#pragma unroll
+    for (int r = 0; r < RW; ++r)
+#pragma unroll
+        for (int j = 0; j < V; ++j) acc[r][j] = 0;
+    const int owner = group * kStagedWaves + wave;
+    // (constant address space: scalar loads, whatever the copies' assembly may touch)
+    typedef uint32_t group_t __attribute__((ext_vector_type(8), aligned(4)));   // four pairs
+    typedef const uint2 __attribute__((address_space(4))) *pairs_t;
+    typedef const uint32_t __attribute__((address_space(4))) *words_t;
+    typedef const int32_t __attribute__((address_space(4))) *ints_t;
+    pairs_t p = (pairs_t)a.stream + ((ints_t)a.starts)[owner];
+    const words_t counts = (words_t)a.counts + (size_t)owner * a.chunks * (RW / 4);
+    group_t next = *reinterpret_cast<const group_t __attribute__((address_space(4))) *>(p);
+
+    issue(0);
+    for (int c = 0; c < a.chunks; ++c) {
+        wait_loads<0>();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();   // the chunk is there, and nobody reads the other buffer any more
+        asm volatile("" ::: "memory");
+        // The stream's cache lines of the next two KiB, into the L2 cache: a scalar load that has to go beyond it
+        // takes 1 us, and waiting for LDS waits for scalar loads as well.  (The words themselves go to a corner of LDS.)
+        touch_to_lds(rstream, (int)((const char __attribute__((address_space(4))) *)p - (const char __attribute__((address_space(4))) *)a.stream) + lane * 64, lds0 + kStagedLdsBytes - kStagedTouchBytes);
+        if (c + 1 < a.chunks) issue(c + 1);
+        const char *base = lds + (c & 1) * a.buffer + lane * (int)(V * sizeof(T));
+        uint32_t cnt[RW / 4];
+#pragma unroll
+        for (int i = 0; i < RW / 4; ++i) cnt[i] = counts[c * (RW / 4) + i];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            int n = (int)(cnt[r / 4] >> (8 * (r % 4)) & 0xffu);   // twos
+#pragma unroll 1
+            for (; n > 1; n -= 2) {
+                const group_t g = next;
+                p += 4;
+                next = *reinterpret_cast<const group_t __attribute__((address_space(4))) *>(p);   // (the stream is padded by a group)
+                opd_t b[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) b[i] = *reinterpret_cast<const opd_t *>(base + g[2 * i]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) Q::mad(acc[r], g[2 * i + 1], b[i]);
+            }
+            if (n) {
+                const group_t g = next;
+                p += 2;
+                next = *reinterpret_cast<const group_t __attribute__((address_space(4))) *>(p);
+                opd_t b[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) b[i] = *reinterpret_cast<const opd_t *>(base + g[2 * i]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) Q::mad(acc[r], g[2 * i + 1], b[i]);
+            }
+        }
+    }
+
+    typedef out_t out_v __attribute__((ext_vector_type(V), aligned(sizeof(out_t))));
+    const int col = col0 + lane * V;
+    if (lane >= a.lanes || col >= a.N) return;
+    out_t *out = static_cast<out_t *>(a.out) + (int64_t)blockIdx.y * a.out_stride;
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        const int row = ((ints_t)a.rows)[owner * RW + r];
+        if (row < 0) continue;
+        out_t *dst = out + (size_t)row * a.ldc + col;
+        if (col + V <= a.N) {
+            out_v v;
+#pragma unroll
+            for (int j = 0; j < V; ++j) v[j] = (out_t)acc[r][j];   // half: one rounding to nearest even
+            *reinterpret_cast<out_v *>(dst) = v;
+        } else {
+#pragma unroll
+            for (int j = 0; j < V; ++j)
+                if (col + j < a.N) dst[j] = (out_t)acc[r][j];
+        }
+    }
+}
+
+// The nonzeros in the order the waves meet them, and what goes with it.
+void staged_rows_pack(const HostPlan &h, StagedPack &out) {
+    const StagedRows s = staged_rows_shape(h);
+    const int rw = s.rows_per_wave, owners = s.groups * kStagedWaves;
+    out.stream.reserve((size_t)h.nnz * 2 + (size_t)owners * s.chunks * rw * 3 + 32);
+    out.counts.assign((size_t)owners * s.chunks * rw, 0);
+    out.starts.assign(owners, 0);
+    out.rows.assign((size_t)owners * rw, -1);
+    std::vector<int32_t> slot_of((size_t)owners * rw, -1);
+    for (int32_t i = 0; i < h.M; ++i) {   // serpentine over the groups, then over the waves of a group
+        const int round = i / s.groups, pos = i % s.groups, g = round & 1 ? s.groups - 1 - pos : pos;
+        const int r = round / kStagedWaves, w = round % kStagedWaves, wave = r & 1 ? kStagedWaves - 1 - w : w;
+        const size_t at = ((size_t)g * kStagedWaves + wave) * rw + r;
+        slot_of[at] = i;
+        out.rows[at] = h.perm[i];
+    }
+    std::vector<int32_t> next((size_t)rw);
+    for (int o = 0; o < owners; ++o) {
+        out.starts[o] = (int32_t)(out.stream.size() / 2);
+        for (int r = 0; r < rw; ++r) next[r] = slot_of[(size_t)o * rw + r] < 0 ? 0 : h.p_row_ptr[slot_of[(size_t)o * rw + r]];
+        for (int c = 0; c < s.chunks; ++c)
+            for (int r = 0; r < rw; ++r) {
+                const int32_t slot = slot_of[(size_t)o * rw + r];
+                if (slot < 0) continue;
+                const int32_t limit = std::min<int64_t>(h.K, (int64_t)(c + 1) * s.chunk), end = h.p_row_ptr[slot + 1];
+                int n = 0;
+                const uint32_t zero_row = (uint32_t)(s.chunk * s.pitch);
+                for (; next[r] < end && h.p_col_idx[next[r]] < limit; ++next[r], ++n) {
+                    out.stream.push_back((uint32_t)(h.p_col_idx[next[r]] - c * s.chunk) * (uint32_t)s.pitch);
+                    out.stream.push_back(h.stream[2 * (size_t)next[r] + 1]);
+                }
+                if (n % 2) { ++n; out.stream.push_back(zero_row); out.stream.push_back(0); }
+                out.counts[((size_t)o * s.chunks + c) * rw + r] = (uint8_t)(n / 2);
+            }
+    }
+    out.stream.resize(out.stream.size() + 32, 0);
+}
+
+int prepare_staged_rows(const HostPlan &h, DevicePlan &d, std::string &err) {
+    const StagedRows s = staged_rows_shape(h);
+    StagedArgs a;
+    const int esz = h.elem_size();
+    a.stream = reinterpret_cast<const uint2 *>(d.stream);
+    a.counts = reinterpret_cast<const uint32_t *>(d.staged_counts);
+    a.starts = d.staged_starts; a.rows = d.staged_rows;
+    a.in = nullptr; a.out = nullptr;   // of the call
+    a.N = h.N; a.ldb = h.ldb; a.ldc = h.ldc;
+    a.in_bytes = (int32_t)(((int64_t)(h.K - 1) * h.ldb + h.N) * esz);
+    a.lanes = s.lanes; a.tiles = s.tiles; a.groups = s.groups;
+    const int64_t tasks = (int64_t)s.tiles * s.groups;
+    a.tasks_per_xcd = (int32_t)((tasks + 7) / 8);
+    a.stream_bytes = (int32_t)d.staged_stream_bytes;
+    a.pitch = s.pitch; a.chunk = s.chunk; a.chunks = s.chunks;
+    a.buffer = ((s.chunk + 1) * s.pitch + 1023) / 1024 * 1024;
+    a.in_stride = (int64_t)h.K * h.ldb; a.out_stride = (int64_t)h.M * h.ldc;
+    if (s.V == 0 || tasks > (1ll << 28) || 2 * a.buffer > kStagedLdsBytes - kStagedTouchBytes || d.staged_stream_bytes >= (1ull << 31) || s.chunk > 510 || s.lanes > kWave || s.pitch < s.lanes * s.V * esz ||
+        (int64_t)s.groups * kStagedWaves * s.rows_per_wave < h.M || (int64_t)s.tiles * s.lanes * s.V < h.N) {
+        err = "plan geometry is inconsistent";
+        return SPARSERT_EINVAL;
+    }
+    const void *kernel = nullptr;
+    if (h.dtype == SPARSERT_I8) kernel = (const void *)staged_rows_kernel<int8_t, 4, 4>;
+    else if (h.dtype == SPARSERT_F16) kernel = (const void *)staged_rows_kernel<_Float16, 4, 4>;
+    else if (s.V == 4) kernel = (const void *)staged_rows_kernel<float, 4, 4>;
+    else kernel = s.rows_per_wave == 8 ? (const void *)staged_rows_kernel<float, 2, 8> : (const void *)staged_rows_kernel<float, 2, 4>;
+    hipFunction_t fn = nullptr;
+    const hipError_t e = hipGetFuncBySymbol(&fn, kernel);
+    if (e != hipSuccess) { err = std::string("staged row-walk kernel: ") + hipGetErrorString(e); return SPARSERT_EHIP; }
+    static_assert(sizeof(StagedArgs) <= sizeof(d.launch.args), "room for the arguments");
+    d.launch.function = fn;
+    d.launch.grid[0] = (uint32_t)a.tasks_per_xcd * 8u; d.launch.grid[1] = (uint32_t)h.batch; d.launch.grid[2] = 1;
+    d.launch.threads = kStagedWaves * kWave;
+    d.launch.arg_bytes = sizeof(a); d.launch.in_at = offsetof(StagedArgs, in); d.launch.out_at = offsetof(StagedArgs, out);
+    std::memcpy(d.launch.args, &a, sizeof(a));
+    return SPARSERT_OK;
+}
+
+}  // namespace sparsert
