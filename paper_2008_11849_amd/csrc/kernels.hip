@@ -31,6 +31,10 @@ template <typename T> struct VecOf<T, 1> { typedef T type; };
 // Global (address space 1) byte pointer: keeps the loads on the global path with a
 // scalar base and a 32-bit per-lane offset.
 typedef const char __attribute__((address_space(1))) *gbytes;
+// The plan's arrays: constant address space, so that wave-uniform reads are scalar loads.
+typedef const int32_t __attribute__((address_space(4))) *const_ints;
+typedef uint32_t pair_t __attribute__((ext_vector_type(2)));   // {word, value bits}
+typedef const pair_t __attribute__((address_space(4))) *const_pairs;
 
 // Arithmetic of one storage type at V columns per lane: what an operand fetch yields, how a
 // nonzero is accumulated, and how the accumulators are stored.
@@ -123,16 +127,16 @@ __device__ __forceinline__ typename Ops<T, V>::opd_t fetch(gbytes in, uint32_t l
 // the only per-lane part of an address.  The stream is padded by 2*U pairs, so pair loads
 // never need a guard.
 template <typename T, int V, bool CONV>
-__device__ __forceinline__ void walk(const uint2 *__restrict__ stream, int p0, int p1,
+__device__ __forceinline__ void walk(const_pairs stream, int p0, int p1,
                                      gbytes in, uint32_t lane_off, typename Ops<T, V>::acc_t (&acc)[V]) {
     typedef typename Ops<T, V>::opd_t opd_t;
     constexpr int U = 8;
     int p = p0;
-    uint2 e[U];
+    pair_t e[U];
 #pragma unroll
     for (int i = 0; i < U; ++i) e[i] = stream[p + i];
     for (; p + U <= p1; p += U) {
-        uint2 en[U];
+        pair_t en[U];
         opd_t b[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) en[i] = stream[p + U + i];
@@ -165,13 +169,12 @@ struct RowsArgs {
     const int32_t *conv_seg;
     const void *in;   // B [K,N] or X [Cin,H,W]
     void *out;        // C [M,N] or Y [Cout,H,W]
-    int32_t M, N, ldc;
-    int32_t n_vec_cols, lanes_per_tile, n_tiles;
-    int32_t n_split, n_wg_rows;
-    int32_t n_tasks, tasks_per_xcd;
+    int64_t in_image_bytes;   // distance between the operands of a batch (grid y)
+    int32_t M, ldc;
+    int32_t n_vec_cols;
+    int16_t lanes_per_tile, stream_stores;   // the latter: every wave store of C covers whole 128-byte lines
+    int32_t n_split, n_tasks;
     int32_t H, W;
-    int32_t stream_stores;   // every wave store of C covers whole 128-byte lines
-    int64_t in_image_bytes, out_image_elems;   // distance between the problems of a batch (grid y)
 };
 
 template <typename T, int V, bool CONV>
@@ -179,11 +182,16 @@ __global__ __launch_bounds__(kGy *kWave) void rows_kernel(const RowsArgs a) {
     // Workgroups are handed to the 8 XCDs round-robin.  Remap so that each XCD works on a
     // contiguous run of tasks; tasks are ordered column-tile major, so the B column slab
     // of a tile is pulled into as few of the per-XCD L2s as possible.
+    // (All arguments in one go: left alone they arrive in several batches, each waited for.)
+    asm volatile("" ::"s"(a.p_row_ptr), "s"(a.perm), "s"(a.stream), "s"(a.in), "s"(a.out), "s"(a.M), "s"(a.n_vec_cols), "s"(a.n_split), "s"(a.H), "s"(a.ldc), "s"(a.in_image_bytes));
+    const const_ints row_ptr = (const_ints)a.p_row_ptr, perm = (const_ints)a.perm, segments = (const_ints)a.segments;
+    const const_pairs stream = (const_pairs)a.stream;
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-    const int task = xcd * a.tasks_per_xcd + idx;
+    const int task = xcd * ((a.n_tasks + 7) >> 3) + idx;
     if (task >= a.n_tasks) return;
-    const int tile = task / a.n_wg_rows;
-    const int wg_row = task - tile * a.n_wg_rows;
+    const int n_wg_rows = a.n_split + (a.M - a.n_split + kGy - 1) / kGy;
+    const int tile = task / n_wg_rows;
+    const int wg_row = task - tile * n_wg_rows;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & (kWave - 1);
 
@@ -219,25 +227,27 @@ __global__ __launch_bounds__(kGy *kWave) void rows_kernel(const RowsArgs a) {
     const bool split = wg_row < a.n_split;
     if (split) {
         slot = wg_row;
-        p0 = a.segments[slot * (kGy + 1) + wave];
-        p1 = a.segments[slot * (kGy + 1) + wave + 1];
+        p0 = segments[slot * (kGy + 1) + wave];
+        p1 = segments[slot * (kGy + 1) + wave + 1];
     } else {
         slot = a.n_split + (wg_row - a.n_split) * kGy + wave;
         if (slot >= a.M) return;  // whole wave leaves; no barrier follows on this path
-        p0 = a.p_row_ptr[slot];
-        p1 = a.p_row_ptr[slot + 1];
+        p0 = row_ptr[slot];
+        p1 = row_ptr[slot + 1];
     }
+    const int row = perm[slot];
+    asm volatile("" ::"s"(p0), "s"(p1), "s"(row));   // (the row with the others, not where it is needed)
 
     if constexpr (CONV) {
         // The slot's nonzeros are grouped by tap (Section 3.6: the padding test is resolved
         // ahead of time): one lane mask per group instead of a test per multiply-add.
-        const int32_t *seg = a.conv_seg + slot * 10;
+        const const_ints seg = (const_ints)a.conv_seg + slot * 10;
         for (int t = 0; t < 9; ++t) {
             const int q0 = max(p0, seg[t]), q1 = min(p1, seg[t + 1]);
-            if (q0 < q1 && ((tap_ok >> t) & 1u)) walk<T, 1, true>(a.stream, q0, q1, in, lane_off, acc);
+            if (q0 < q1 && ((tap_ok >> t) & 1u)) walk<T, 1, true>(stream, q0, q1, in, lane_off, acc);
         }
     } else {
-        walk<T, V, false>(a.stream, p0, p1, in, lane_off, acc);
+        walk<T, V, false>(stream, p0, p1, in, lane_off, acc);
     }
 
     if (split) {
@@ -257,9 +267,8 @@ __global__ __launch_bounds__(kGy *kWave) void rows_kernel(const RowsArgs a) {
         }
     }
     if (owns) {
-        const int row = a.perm[slot];
         typedef typename Ops<T, V>::out_t out_t;
-        out_t *out = static_cast<out_t *>(a.out) + (int64_t)blockIdx.y * a.out_image_elems;
+        out_t *out = static_cast<out_t *>(a.out) + (int64_t)blockIdx.y * ((int64_t)a.M * a.ldc);
         Ops<T, V>::store(out + (size_t)row * a.ldc + col, acc, a.stream_stores != 0);
     }
 }
@@ -304,15 +313,13 @@ static int prepare_rows(const HostPlan &h, DevicePlan &d, std::string &err) {
     a.stream = reinterpret_cast<const uint2 *>(d.stream);
     a.segments = d.segments; a.conv_seg = d.conv_seg;
     a.in = nullptr; a.out = nullptr;   // of the call
-    a.M = h.M; a.N = h.N; a.ldc = h.ldc;
-    a.n_vec_cols = (int32_t)nvc; a.lanes_per_tile = h.lanes_per_tile; a.n_tiles = h.n_tiles;
-    a.n_split = h.n_split; a.n_wg_rows = h.n_wg_rows;
-    a.n_tasks = (int32_t)n_tasks; a.tasks_per_xcd = (int32_t)((n_tasks + 7) / 8);
+    a.M = h.M; a.ldc = h.ldc;
+    a.n_vec_cols = (int32_t)nvc; a.lanes_per_tile = (int16_t)h.lanes_per_tile;
+    a.n_split = h.n_split; a.n_tasks = (int32_t)n_tasks;
     a.H = h.H; a.W = h.W;
     a.stream_stores = ((int64_t)h.ldc * h.out_elem_size()) % 128 == 0 &&
                       ((int64_t)h.lanes_per_tile * h.vec * h.out_elem_size()) % 128 == 0;
     a.in_image_bytes = (h.conv ? (int64_t)h.Cin * h.H * h.W : (int64_t)h.K * h.ldb) * h.elem_size();
-    a.out_image_elems = (int64_t)h.M * h.ldc;
     const int images = h.batch;
     if (images < 1 || images > 65535) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
     const void *kernel = nullptr;
@@ -335,7 +342,7 @@ static int prepare_rows(const HostPlan &h, DevicePlan &d, std::string &err) {
     hipFunction_t fn = nullptr;
     HIP_TRY(hipGetFuncBySymbol(&fn, kernel));
     d.launch.function = fn;
-    d.launch.grid[0] = (uint32_t)a.tasks_per_xcd * 8u; d.launch.grid[1] = (uint32_t)images; d.launch.grid[2] = 1;
+    d.launch.grid[0] = (uint32_t)((n_tasks + 7) / 8) * 8u; d.launch.grid[1] = (uint32_t)images; d.launch.grid[2] = 1;
     d.launch.threads = kGy * kWave;
     d.launch.arg_bytes = sizeof(a); d.launch.in_at = offsetof(RowsArgs, in); d.launch.out_at = offsetof(RowsArgs, out);
     std::memcpy(d.launch.args, &a, sizeof(a));

@@ -66,11 +66,7 @@ struct MfmaArgs {
     const int32_t *p_row_ptr, *inv_perm; // the nonzero stream, for tiles with non-finite sums
     const uint2 *stream;
     int32_t M, K, N, ldb, ldc;
-    int32_t k_steps, n_slabs;
-    int32_t m_tiles, n_tiles, tasks_per_xcd, m_fast;
-    int32_t in_bytes;                    // of one problem: reads stay inside
-    int32_t weight_bytes, out_bytes;
-    int64_t in_stride, out_stride;       // elements between the problems of a batch (grid y)
+    int32_t m_fast;                      // consecutive tasks: along M
 };
 
 template <int DT> struct Kind;           // 0: half, 1: int8
@@ -123,15 +119,23 @@ __global__ __launch_bounds__(WM *WN *kWave, 2) void mfma_kernel(const MfmaArgs a
     constexpr int ROWS256 = 256 / (TN * ESZ) > 0 ? 256 / (TN * ESZ) : 1;
     __shared__ __align__(1024) char lds[STAGES * STAGE];
 
-    const int task = (int)(blockIdx.x & 7) * a.tasks_per_xcd + (int)(blockIdx.x >> 3);
-    if (task >= a.m_tiles * a.n_tiles) return;
-    const int tile_m = a.m_fast ? task % a.m_tiles : task / a.n_tiles;
-    const int tile_n = a.m_fast ? task / a.m_tiles : task % a.n_tiles;
+    // All arguments in one go: left alone they arrive in four batches, each waited for.
+    asm volatile("" ::"s"(a.weights), "s"(a.in), "s"(a.out), "s"(a.M), "s"(a.K), "s"(a.N), "s"(a.ldb), "s"(a.ldc), "s"(a.m_fast));
+    const int m_tiles = (a.M + TM - 1) / TM, n_tiles = (a.N + TN - 1) / TN, tasks = m_tiles * n_tiles;
+    const int n_slabs = (a.K + SLAB - 1) / SLAB, k_steps = n_slabs * STEPS;
+    const int task = (int)(blockIdx.x & 7) * ((tasks + 7) >> 3) + (int)(blockIdx.x >> 3);
+    if (task >= tasks) return;
+    const uint32_t fast_tiles = a.m_fast ? m_tiles : n_tiles;
+    const int slow = (int)((uint32_t)task / fast_tiles), fast = task - slow * (int)fast_tiles;
+    const int tile_m = a.m_fast ? fast : slow, tile_n = a.m_fast ? slow : fast;
+    // of one problem: reads and writes stay inside
+    const int in_bytes = ((a.K - 1) * a.ldb + a.N) * ESZ, weight_bytes = m_tiles * (TM / 16) * k_steps * 1024;
+    const int out_bytes = (int)(((uint32_t)(a.M - 1) * (uint32_t)a.ldc + (uint32_t)a.N) * (uint32_t)sizeof(out_t));
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int m0 = tile_m * TM + wm * MF * 16, n_tile0 = tile_n * TN, n0 = n_tile0 + wn * NF * 16;
-    const in_t *in = static_cast<const in_t *>(a.in) + (int64_t)blockIdx.y * a.in_stride;
-    out_t *out = static_cast<out_t *>(a.out) + (int64_t)blockIdx.y * a.out_stride;
+    const in_t *in = static_cast<const in_t *>(a.in) + (int64_t)blockIdx.y * ((int64_t)a.K * a.ldb);
+    out_t *out = static_cast<out_t *>(a.out) + (int64_t)blockIdx.y * ((int64_t)a.M * a.ldc);
     // Where N is no multiple of EPC the last 16-byte chunk of a row begins at N - EPC: it holds some
     // columns twice, every one of them real, so neither the loads nor the stores know ragged ends.
     auto column = [&](int n) { return n - max(0, (n & -EPC) + EPC - a.N); };   // column of C behind column n of the tiling
@@ -142,7 +146,7 @@ __global__ __launch_bounds__(WM *WN *kWave, 2) void mfma_kernel(const MfmaArgs a
     // ---- copies: this lane's chunk of every copy of a slab.  What leaves the operand (rows past K in the last
     // slab, an offset of kRefused) the descriptor answers with zeros and no memory access; so it does for every
     // copy of a slab past the last one, whose descriptors have no bytes.
-    const int4v rin = descriptor(in, a.in_bytes), rw = descriptor(a.weights, a.weight_bytes);
+    const int4v rin = descriptor(in, in_bytes), rw = descriptor(a.weights, weight_bytes);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     constexpr int kRefused = (int)0x80000000;
     int b_off[IB];
@@ -156,15 +160,15 @@ __global__ __launch_bounds__(WM *WN *kWave, 2) void mfma_kernel(const MfmaArgs a
 #pragma unroll
     for (int i = 0; i < IA; ++i) {
         const int q = wave * IA + i;
-        a_off[i] = ((tile_m * (TM / 16) + q / STEPS) * a.k_steps + q % STEPS) * 1024 + lane * 16;
+        a_off[i] = ((tile_m * (TM / 16) + q / STEPS) * k_steps + q % STEPS) * 1024 + lane * 16;
     }
     struct Source { int4v rin, rw; int sin, sw; uint32_t base; };
     auto source = [&](int s) {   // what the copies of slab s have in common
-        const bool live = s < a.n_slabs;
+        const bool live = s < n_slabs;
         Source c{rin, rw, live ? (int)((uint32_t)s * (uint32_t)(SLAB * ESZ) * (uint32_t)a.ldb) : 0, live ? s * (STEPS * 1024) : 0,
                  lds0 + (uint32_t)(s % STAGES) * STAGE};
-        c.rin[2] = live ? a.in_bytes : 0;
-        c.rw[2] = live ? a.weight_bytes : 0;
+        c.rin[2] = live ? in_bytes : 0;
+        c.rw[2] = live ? weight_bytes : 0;
         return c;
     };
     // Copy i of this wave's IA + IB copies of a slab.
@@ -260,15 +264,15 @@ __global__ __launch_bounds__(WM *WN *kWave, 2) void mfma_kernel(const MfmaArgs a
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) read(lds, u, even);
     int s = 0;
-    for (; s + 1 < a.n_slabs; s += 2) {
+    for (; s + 1 < n_slabs; s += 2) {
         turn(s, even, odd, std::false_type());
         turn(s + 1, odd, even, std::false_type());
     }
-    if (s < a.n_slabs) turn(s, even, odd, std::true_type());
+    if (s < n_slabs) turn(s, even, odd, std::true_type());
     wait_loads<0>();
 
     // ---- results.  Stores outside C (rows past M, chunks past N) are refused by the descriptor.
-    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, a.out_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, out_bytes, 0x00020000);
     float probe = 0.0f;   // becomes NaN with the first sum that is not finite
     int row_off[MF], col_off[NF];
 #pragma unroll
@@ -337,20 +341,13 @@ int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err) {
     a.weights = d.mfma_weights; a.in = nullptr; a.out = nullptr;   // of the call
     a.p_row_ptr = d.p_row_ptr; a.inv_perm = d.inv_perm; a.stream = reinterpret_cast<const uint2 *>(d.stream);
     a.M = h.M; a.K = h.K; a.N = h.N; a.ldb = h.ldb; a.ldc = h.ldc;
-    a.n_slabs = (a.K + slab - 1) / slab; a.k_steps = a.n_slabs * c.steps;
-    a.m_tiles = (h.M + c.tm - 1) / c.tm; a.n_tiles = (h.N + c.tn - 1) / c.tn;
-    const int64_t tasks = (int64_t)a.m_tiles * a.n_tiles;
+    const int64_t m_tiles = (h.M + c.tm - 1) / c.tm, tasks = m_tiles * ((h.N + c.tn - 1) / c.tn);
     if (tasks > (1ll << 30)) { err = "too many workgroups"; return SPARSERT_EUNSUPPORTED; }
-    a.tasks_per_xcd = (int32_t)((tasks + 7) / 8);
     // Each XCD takes an eighth of the tiles: along M if that leaves its L2 less of A and B to hold, else along N.
-    const double wb = (double)a.m_tiles * c.tm * a.K * esz, bb = (double)h.K * h.N * esz;
+    const double wb = (double)m_tiles * c.tm * a.K * esz, bb = (double)h.K * h.N * esz;
     a.m_fast = wb + bb / 8 < wb / 8 + bb;
-    a.in_bytes = (int32_t)(((int64_t)(h.K - 1) * h.ldb + h.N) * esz);
-    const int64_t weight_bytes = (int64_t)a.m_tiles * (c.tm / 16) * a.k_steps * 1024;
-    if (weight_bytes >= (1ll << 31)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
-    a.weight_bytes = (int32_t)weight_bytes;
-    a.out_bytes = (int32_t)(((int64_t)(h.M - 1) * h.ldc + h.N) * h.out_elem_size());
-    a.in_stride = (int64_t)h.K * h.ldb; a.out_stride = (int64_t)h.M * h.ldc;
+    const int64_t weight_bytes = m_tiles * (c.tm / 16) * ((a.K + slab - 1) / slab * c.steps) * 1024;
+    if (weight_bytes >= (1ll << 31) || ((int64_t)(h.K - 1) * h.ldb + h.N) * esz >= (1ll << 31)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
     const void *kernel = nullptr;
     switch (sp.mfma_config * 2 + (h.dtype == SPARSERT_I8 ? 1 : 0)) {
 #define X(id, tm, tn, wm, wn, mf, nf, steps, stages, ...)                                              \
@@ -364,7 +361,7 @@ int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err) {
     if (e != hipSuccess) { err = std::string("matrix-core kernel: ") + hipGetErrorString(e); return SPARSERT_EHIP; }
     static_assert(sizeof(MfmaArgs) <= sizeof(d.launch.args), "room for the arguments");
     d.launch.function = fn;
-    d.launch.grid[0] = (uint32_t)a.tasks_per_xcd * 8u; d.launch.grid[1] = (uint32_t)h.batch; d.launch.grid[2] = 1;
+    d.launch.grid[0] = (uint32_t)((tasks + 7) / 8) * 8u; d.launch.grid[1] = (uint32_t)h.batch; d.launch.grid[2] = 1;
     d.launch.threads = (uint32_t)(c.waves() * kWave);
     d.launch.arg_bytes = sizeof(a); d.launch.in_at = offsetof(MfmaArgs, in); d.launch.out_at = offsetof(MfmaArgs, out);
     std::memcpy(d.launch.args, &a, sizeof(a));

@@ -12,6 +12,9 @@ namespace sparsert {
 constexpr int kWave = 64;       // lanes per wavefront on gfx950
 constexpr int kGy = 4;          // waves per workgroup (one per SIMD of a CU)
 constexpr int kBins = 33;       // bin(0)=0, bin(x)=1+floor(log2 x), x < 2^31
+// Room for a kernel's arguments.  The host spends 2.65 us to 2.8 us on a launch whose arguments take 16 to 96
+// bytes and 3.45 us on one that takes 128, so kernels derive what they can instead of being handed it.
+constexpr int kArgBytes = 96;
 constexpr int kFullTasks = 2048;  // wave tasks wanted before widening per-lane vectors
 constexpr int32_t kAutoSpecNnz = 4 << 20;   // SPARSERT_KERNEL_AUTO generates code up to this many nonzeros (about 4 s of assembling per million)
 
@@ -92,7 +95,7 @@ struct DevicePlan {
         void *function = nullptr;    // hipFunction_t
         uint32_t grid[3] = {0, 0, 0}, threads = 0;
         uint32_t arg_bytes = 0, in_at = 0, out_at = 0;   // offsets of the operand's and the result's address
-        alignas(16) unsigned char args[160] = {};
+        alignas(16) unsigned char args[kArgBytes] = {};
     } launch;
 };
 

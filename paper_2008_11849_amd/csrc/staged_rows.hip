@@ -37,11 +37,13 @@ struct StagedArgs {
     const int32_t *rows;          // [group][wave][RW]: row of C, -1 for none
     const void *in;
     void *out;
-    int32_t N, ldb, ldc, in_bytes;
-    int32_t lanes, tiles, groups, tasks_per_xcd;
-    int32_t stream_bytes, pitch, chunk, chunks, buffer;   // buffer: bytes of one of the two LDS buffers
-    int64_t in_stride, out_stride;          // elements between the problems of a batch (grid y)
+    int32_t M, K, N, ldb, ldc;
+    int32_t lanes, tiles, groups;
+    int32_t stream_bytes, pitch, chunk, chunks;
 };
+
+// Bytes of one of the two LDS buffers: a chunk's rows and one row of zeros, in whole copies.
+__host__ __device__ constexpr int staged_buffer_bytes(int chunk, int pitch) { return ((chunk + 1) * pitch + 1023) & ~1023; }
 
 // Operands, multiply-adds and results of one storage type at V columns per lane.
 template <typename T, int V> struct StagedOps {
@@ -72,17 +74,17 @@ __global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(con
     typedef typename Q::acc_t acc_t;
     constexpr int COPIES = kStagedLdsBytes / 2 / 1024 / kStagedWaves;   // 1 KiB copies per wave and chunk, at most
     __shared__ __align__(1024) char lds[kStagedLdsBytes];
-    const int task = (int)(blockIdx.x & 7) * a.tasks_per_xcd + (int)(blockIdx.x >> 3);
+    const int task = (int)(blockIdx.x & 7) * ((a.tiles * a.groups + 7) >> 3) + (int)(blockIdx.x >> 3);
     if (task >= a.tiles * a.groups) return;
     const int tile = task / a.groups, group = task - tile * a.groups;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const T *in = static_cast<const T *>(a.in) + (int64_t)blockIdx.y * a.in_stride;
+    const T *in = static_cast<const T *>(a.in) + (int64_t)blockIdx.y * ((int64_t)a.K * a.ldb);
     const int col0 = tile * a.lanes * V;
 
     // this lane's 16 bytes of every copy of a chunk; what lies past the operand arrives as zeros
-    const int4v rin = descriptor(in, a.in_bytes), rstream = descriptor(a.stream, a.stream_bytes);
+    const int4v rin = descriptor(in, ((a.K - 1) * a.ldb + a.N) * (int)sizeof(T)), rstream = descriptor(a.stream, a.stream_bytes);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
-    const int per_row = a.pitch >> 4;
+    const int per_row = a.pitch >> 4, buffer = staged_buffer_bytes(a.chunk, a.pitch);
     int off[COPIES];
 #pragma unroll
     for (int i = 0; i < COPIES; ++i) {
@@ -92,10 +94,10 @@ __global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(con
     }
     auto issue = [&](int c) {
         const int from = c * a.chunk * a.ldb * (int)sizeof(T);
-        const uint32_t to = lds0 + (uint32_t)(c & 1) * (uint32_t)a.buffer;
+        const uint32_t to = lds0 + (uint32_t)(c & 1) * (uint32_t)buffer;
 #pragma unroll
         for (int i = 0; i < COPIES; ++i)
-            if ((i * kStagedWaves + wave) * 1024 < a.buffer) copy_to_lds<0>(rin, off[i], from, to + (uint32_t)(i * kStagedWaves + wave) * 1024);
+            if ((i * kStagedWaves + wave) * 1024 < buffer) copy_to_lds<0>(rin, off[i], from, to + (uint32_t)(i * kStagedWaves + wave) * 1024);
     };
 
     acc_t acc[RW][V];
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(con
         // takes 1 us, and waiting for LDS waits for scalar loads as well.  (The words themselves go to a corner of LDS.)
         touch_to_lds(rstream, (int)((const char __attribute__((address_space(4))) *)p - (const char __attribute__((address_space(4))) *)a.stream) + lane * 64, lds0 + kStagedLdsBytes - kStagedTouchBytes);
         if (c + 1 < a.chunks) issue(c + 1);
-        const char *base = lds + (c & 1) * a.buffer + lane * (int)(V * sizeof(T));
+        const char *base = lds + (c & 1) * buffer + lane * (int)(V * sizeof(T));
         uint32_t cnt[RW / 4];
 #pragma unroll
         for (int i = 0; i < RW / 4; ++i) cnt[i] = counts[c * (RW / 4) + i];
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(con
     typedef out_t out_v __attribute__((ext_vector_type(V), aligned(sizeof(out_t))));
     const int col = col0 + lane * V;
     if (lane >= a.lanes || col >= a.N) return;
-    out_t *out = static_cast<out_t *>(a.out) + (int64_t)blockIdx.y * a.out_stride;
+    out_t *out = static_cast<out_t *>(a.out) + (int64_t)blockIdx.y * ((int64_t)a.M * a.ldc);
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
         const int row = ((ints_t)a.rows)[owner * RW + r];
@@ -222,16 +224,12 @@ int prepare_staged_rows(const HostPlan &h, DevicePlan &d, std::string &err) {
     a.counts = reinterpret_cast<const uint32_t *>(d.staged_counts);
     a.starts = d.staged_starts; a.rows = d.staged_rows;
     a.in = nullptr; a.out = nullptr;   // of the call
-    a.N = h.N; a.ldb = h.ldb; a.ldc = h.ldc;
-    a.in_bytes = (int32_t)(((int64_t)(h.K - 1) * h.ldb + h.N) * esz);
+    a.M = h.M; a.K = h.K; a.N = h.N; a.ldb = h.ldb; a.ldc = h.ldc;
     a.lanes = s.lanes; a.tiles = s.tiles; a.groups = s.groups;
     const int64_t tasks = (int64_t)s.tiles * s.groups;
-    a.tasks_per_xcd = (int32_t)((tasks + 7) / 8);
     a.stream_bytes = (int32_t)d.staged_stream_bytes;
     a.pitch = s.pitch; a.chunk = s.chunk; a.chunks = s.chunks;
-    a.buffer = ((s.chunk + 1) * s.pitch + 1023) / 1024 * 1024;
-    a.in_stride = (int64_t)h.K * h.ldb; a.out_stride = (int64_t)h.M * h.ldc;
-    if (s.V == 0 || tasks > (1ll << 28) || 2 * a.buffer > kStagedLdsBytes - kStagedTouchBytes || d.staged_stream_bytes >= (1ull << 31) || s.chunk > 510 || s.lanes > kWave || s.pitch < s.lanes * s.V * esz ||
+    if (s.V == 0 || tasks > (1ll << 28) || 2 * staged_buffer_bytes(s.chunk, s.pitch) > kStagedLdsBytes - kStagedTouchBytes || d.staged_stream_bytes >= (1ull << 31) || s.chunk > 510 || s.lanes > kWave || s.pitch < s.lanes * s.V * esz ||
         (int64_t)s.groups * kStagedWaves * s.rows_per_wave < h.M || (int64_t)s.tiles * s.lanes * s.V < h.N) {
         err = "plan geometry is inconsistent";
         return SPARSERT_EINVAL;
@@ -246,7 +244,7 @@ int prepare_staged_rows(const HostPlan &h, DevicePlan &d, std::string &err) {
     if (e != hipSuccess) { err = std::string("staged row-walk kernel: ") + hipGetErrorString(e); return SPARSERT_EHIP; }
     static_assert(sizeof(StagedArgs) <= sizeof(d.launch.args), "room for the arguments");
     d.launch.function = fn;
-    d.launch.grid[0] = (uint32_t)a.tasks_per_xcd * 8u; d.launch.grid[1] = (uint32_t)h.batch; d.launch.grid[2] = 1;
+    d.launch.grid[0] = (uint32_t)((tasks + 7) / 8) * 8u; d.launch.grid[1] = (uint32_t)h.batch; d.launch.grid[2] = 1;
     d.launch.threads = kStagedWaves * kWave;
     d.launch.arg_bytes = sizeof(a); d.launch.in_at = offsetof(StagedArgs, in); d.launch.out_at = offsetof(StagedArgs, out);
     std::memcpy(d.launch.args, &a, sizeof(a));
