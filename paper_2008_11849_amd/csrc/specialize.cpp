@@ -701,6 +701,20 @@ int rows_without_thin_round(int32_t M, int R, int groups_per_wg, int64_t wg_colu
     return R;
 }
 
+// A launch of 257 to 512 workgroups gives some compute units two and the others one, and takes as long as the
+// two.  If the fewest rows per block that make it 256 workgroups are at most 7/4 of R, one larger workgroup each is
+// faster: blocks of 64 rows instead of 52 on 104 column tiles (half convolution of 128 x 1152, 28 x 28, batch 8),
+// 312 -> 208 workgroups, 11.3 -> 7.9 us; 504 x 1664 x 691, batch 4, fp32: 86 -> 101 rows, 264 -> 220, 37.2 -> 21.0 us.
+// Over 52 drawn products and convolutions that it changes: 1.04 to 2.1 times faster, 1.36 on average.  Twice the rows lose
+// what the second workgroup hides (2048 x 376 x 67, batch 4, 16 -> 32 rows: 8.4 -> 10.2 us), and so may blocks of
+// more than 96 rows without a K split (1096 x 308 x 1600, batch 4, 96 -> 122: 18.8 -> 20.4 us).
+static int rows_for_one_round(int32_t M, int R, int64_t wg_columns, int hi) {
+    const int64_t wgs = workgroups_for(M, R, 1, wg_columns);
+    if (R < 8 || wgs <= 256 || wgs > 512) return R;
+    const int r = rows_for_rounds(M, 1, wg_columns, 1, std::min(hi, R * 7 / 4));
+    return r > R ? r : R;
+}
+
 // What the stages below hand to each other besides the SpecPlan itself.
 struct Shape {
     bool lds = false;   // LDS-staged variant
@@ -770,6 +784,7 @@ static int choose_launch_shape(const HostPlan &h, const sparsert_options &opt, S
         // units: 34.8 us; in blocks of 54 they are 247: 21.3 us (4096 columns of A at 95 %)
         const int T = opt.spec_tiles ? opt.spec_tiles : 4;
         const int64_t wg_columns = KS > 1 ? tiles_all : (sp.n_tiles + T - 1) / T * std::max(1, h.batch);
+        R = rows_for_one_round(M, R, wg_columns, (KS > 1 ? 128 : 96) / V);
         R = rows_without_thin_round(M, R, 1, wg_columns, 128 / V);
     }
     sp.ksplit = KS;

@@ -367,6 +367,20 @@ def test_untuned_defaults_of_the_generated_kernel(M, K, N, batch, rows, ksplit):
     assert plan.info()["spec_ksplit"] == 1
 
 
+@pytest.mark.parametrize("M,K,N,batch,rows,ksplit", [
+    (384, 600, 2209, 2, 128, 8),     # 96 rows: 4 blocks x 70 tiles = 280 workgroups; the largest count of the rule makes it 210
+    (504, 1664, 691, 4, 101, 8),     # 86 rows: 264 workgroups; 101 rows: 220
+    (384, 128, 1024, 16, 96, 1),     # 96 rows already make 256
+    (2048, 376, 67, 4, 16, 1),       # 512 workgroups would need twice the rows
+    (1096, 308, 1600, 4, 96, 1),     # without a K split blocks stay at 96 rows
+    (576, 528, 4096, 1, 96, 8),      # 384 workgroups: 128 rows would still make 320
+])
+def test_untuned_defaults_that_fit_one_round_of_workgroups(M, K, N, batch, rows, ksplit):
+    csr = synth.uniform_csr(M, K, 0.98, 11)
+    info = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, kernel=sp.KERNEL_SPEC, batch=batch).info()
+    assert (info["spec_rows"], info["spec_ksplit"]) == (rows, ksplit)
+
+
 @pytest.mark.parametrize("mode", [sp.SPEC_DIRECT, sp.SPEC_LDS])
 @pytest.mark.parametrize("rows", [1, 7, 24])
 def test_generated_kernel_plan_assembles_on_the_host(rows, mode):

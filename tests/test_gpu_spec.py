@@ -732,6 +732,17 @@ def test_default_rows_that_avoid_a_thin_last_round(M, K, N, rows):
     assert np.array_equal(got.astype(np.float64), Cref)
 
 
+@pytest.mark.parametrize("M,K,N,rows", [(760, 530, 2209, 109), (61, 520, 8192, 31), (393, 130, 4000, 25)])
+def test_default_rows_that_fit_one_round(M, K, N, rows):
+    """Shapes of 257 to 512 workgroups whose row count is raised to make them 256 at most."""
+    csr = synth.small_int_csr(M, K, 0.95, N)
+    B = synth.small_int_dense(K, N, N + 1)
+    Cref, _ = _oracle(csr, B)
+    got, info = run_spmm(csr, B, kernel=sp.KERNEL_SPEC)
+    assert info["spec_rows"] == rows, info
+    assert np.array_equal(got.astype(np.float64), Cref)
+
+
 @pytest.mark.parametrize("N", [49, 130])
 def test_blocks_of_the_most_rows_the_registers_hold(N):
     """232 rows per block with the reduction axis split over eight waves: the partial sums are
