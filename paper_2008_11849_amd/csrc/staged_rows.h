@@ -52,6 +52,14 @@ inline double plain_rows_microseconds(const HostPlan &h, int32_t longest) {
          + 1e-2 * f[3] * chain + 1e-6 * f[4] * h.M * h.N * (double)h.batch * h.out_elem_size();
 }
 
+// What the kernel's addressing holds: the pair stream, with at most one filler per row and chunk and the padding
+// at its end, under 2 GiB (its touches go through a descriptor with 32-bit offsets), and a launch of less than
+// 2^32 threads.  Larger plans stay with the plain kernel, which counts pairs and not bytes.
+inline bool staged_rows_fits(const HostPlan &h, const StagedRows &s) {
+    const int64_t pairs = (int64_t)h.nnz + (int64_t)h.M * s.chunks + 16, tasks = (int64_t)s.tiles * s.groups;
+    return pairs * 8 < (1ll << 31) && (tasks + 7) / 8 * 8 * kStagedWaves * kWave < (1ll << 32);
+}
+
 // The staged kernel pays where many nonzeros share a workgroup's copy of B; few columns, few rows, a long K
 // with few nonzeros per chunk, or one row much longer than the rest leave it behind (1/2 to 2 times the plain
 // kernel's time over the products above), so it is taken where it is estimated to need less than 0.8 of the
@@ -79,10 +87,11 @@ inline StagedRows staged_rows_shape(const HostPlan &h) {
         s.chunk = std::min(510, (kStagedLdsBytes - 2048) / 2 / s.pitch - 1);
         s.chunk = std::min(s.chunk, h.K);
         s.chunks = (h.K + s.chunk - 1) / s.chunk;
+        if (!staged_rows_fits(h, s)) continue;
         s.microseconds = staged_rows_microseconds(h, s, longest);
         if (best.V == 0 || s.microseconds < best.microseconds) best = s;
     }
-    if (best.microseconds > 0.8 * plain_rows_microseconds(h, longest)) best.V = 0;
+    if (best.V && best.microseconds > 0.8 * plain_rows_microseconds(h, longest)) best.V = 0;
     return best;
 }
 

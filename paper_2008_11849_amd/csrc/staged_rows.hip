@@ -229,7 +229,8 @@ int prepare_staged_rows(const HostPlan &h, DevicePlan &d, std::string &err) {
     const int64_t tasks = (int64_t)s.tiles * s.groups;
     a.stream_bytes = (int32_t)d.staged_stream_bytes;
     a.pitch = s.pitch; a.chunk = s.chunk; a.chunks = s.chunks;
-    if (s.V == 0 || tasks > (1ll << 28) || 2 * staged_buffer_bytes(s.chunk, s.pitch) > kStagedLdsBytes - kStagedTouchBytes || d.staged_stream_bytes >= (1ull << 31) || s.chunk > 510 || s.lanes > kWave || s.pitch < s.lanes * s.V * esz ||
+    // (the rule of staged_rows.h hands over nothing that does not fit)
+    if (s.V == 0 || !staged_rows_fits(h, s) || 2 * staged_buffer_bytes(s.chunk, s.pitch) > kStagedLdsBytes - kStagedTouchBytes || d.staged_stream_bytes >= (1ull << 31) || s.chunk > 510 || s.lanes > kWave || s.pitch < s.lanes * s.V * esz ||
         (int64_t)s.groups * kStagedWaves * s.rows_per_wave < h.M || (int64_t)s.tiles * s.lanes * s.V < h.N) {
         err = "plan geometry is inconsistent";
         return SPARSERT_EINVAL;

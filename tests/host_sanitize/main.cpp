@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/sparsert.h"
+#include "../../paper_2008_11849_amd/csrc/staged_rows.h"
 
 namespace {
 
@@ -83,9 +84,28 @@ void exercise(const Csr &c, int M, int K, int N, sparsert_options o, bool may_re
     sparsert_plan_destroy(p);
 }
 
+// A row-walk plan of M rows of `row` nonzeros as far as the rule of the staged kernel looks at it.
+sparsert::HostPlan rows_plan(int M, int K, int N, int row, int dtype = SPARSERT_F32) {
+    sparsert::HostPlan h;
+    h.M = M; h.K = K; h.N = h.ldb = h.ldc = N; h.nnz = M * row; h.dtype = dtype; h.kernel = SPARSERT_KERNEL_ROWS;
+    h.vec = 4; h.n_tiles = (N / 4 + 63) / 64; h.lanes_per_tile = 64; h.split_threshold = 512;
+    for (int64_t i = 0; i <= M; ++i) h.p_row_ptr.push_back((int32_t)(i * row));
+    return h;
+}
+
+// What the rule hands to the staged kernel, the kernel's launch accepts: its pair stream is addressed with
+// 31 bits, a launch holds less than 2^32 threads.
+void staged_rule_stays_inside_the_limits() {
+    EXPECT(sparsert::staged_rows_shape(rows_plan(6000, 6000, 784, 3000)).V);          // 144 MB of pairs
+    EXPECT(sparsert::staged_rows_shape(rows_plan(16000, 24000, 784, 16000)).V);       // 2.05 GB
+    EXPECT(!sparsert::staged_rows_shape(rows_plan(24000, 24000, 784, 12000)).V);      // 2.3 GB
+    EXPECT(!sparsert::staged_rows_shape(rows_plan(16700, 30000, 784, 16000)).V);      // 2.138 GB, more with the fill
+}
+
 }  // namespace
 
 int main() {
+    staged_rule_stays_inside_the_limits();
     Rng r{20081184ull};
     const int shapes[][3] = {{1, 1, 1}, {7, 5, 3}, {64, 48, 100}, {70, 150, 196}, {33, 260, 65}};
     int plans = 0;
