@@ -115,10 +115,17 @@ class Layer:
         self.info = plan.info()
         self.args = (ctypes.c_void_p(plan.handle), self.args[1], self.args[2])
 
+    def plan_options(self):
+        """The options that make this plan again."""
+        opts = {k: self.info[k] for k in self.PLAN_KEYS}
+        if self.info["staged_vec"]:   # the LDS-staged row-walk kernel: taken where these are not set
+            opts["vec"] = opts["split_threshold"] = 0
+        return opts
+
     def variant(self, **changes):
         """A new plan with this plan's options and `changes` on top (generated-kernel plans)."""
         csr, case = self.case.csr, self.case
-        opts = {k: self.info[k] for k in self.PLAN_KEYS}
+        opts = self.plan_options()
         opts["spec_prefetch"] = 1 if opts.get("spec_prefetch") else 0   # the plan reports lines, the option is a switch
         opts.update(changes)
         return self.sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, csr.M, csr.K, case.N, conv=case.conv, **opts)
@@ -511,7 +518,7 @@ def main():
         in_context = refine_in_context(torch, sp, layers, stream)
     if args.plan_file and not saved:
         with open(args.plan_file, "w") as f:
-            json.dump({f"{L.case.name}_{args.dtype}": {k: L.info[k] for k in Layer.PLAN_KEYS} for L in layers}, f)
+            json.dump({f"{L.case.name}_{args.dtype}": L.plan_options() for L in layers}, f)
 
     if args.pmc_mode:
         src = torch.empty(64 * 1024 * 1024, dtype=torch.float32, device="cuda:0").normal_()
@@ -609,7 +616,7 @@ def main():
     if not args.no_traffic:
         import tempfile
         with tempfile.NamedTemporaryFile("w", suffix=".json", dir="/tmp", delete=False) as f:
-            json.dump({f"{L.case.name}_{args.dtype}": {k: L.info[k] for k in Layer.PLAN_KEYS} for L in layers}, f)
+            json.dump({f"{L.case.name}_{args.dtype}": L.plan_options() for L in layers}, f)
         try:
             traffic_detail = measure_traffic(args, layers, f.name)
         finally:

@@ -58,7 +58,10 @@ typedef enum sparsert_kernel {
                                   the latency path, Section 2.3) and neither vec nor split_threshold is set;
                                   the row-walk kernel otherwise, and also when the generator declines the
                                   problem (EUNSUPPORTED / ECOMPILE) */
-    SPARSERT_KERNEL_ROWS = 1,  /* one wave per row, B read straight from L2/HBM */
+    SPARSERT_KERNEL_ROWS = 1,  /* a fixed kernel that walks the rows' nonzeros: one wave per row, B read straight from
+                                  L2/HBM.  SpMM plans with none of vec, split_threshold and natural_order set run a
+                                  variant that copies B to LDS where that is estimated to be faster
+                                  (SPARSERT_INFO_STAGED_VEC); setting one of them keeps the plain kernel */
     SPARSERT_KERNEL_SPEC = 2   /* per-matrix generated gfx950 code with the nonzeros of A as
                                   instruction constants (Section 3.5) */
 } sparsert_kernel;
@@ -85,7 +88,7 @@ typedef struct sparsert_options {
                                 or B/C pairs of an SpMM stored back to back (one more grid dimension) */
     int32_t host_only;       /* 1: analyse only; no HIP call is made, the plan can be
                                 exported but not executed */
-    int32_t vec;             /* columns of C per lane; 0 = automatic, else 1,2,4 (,8 for f16; 1 or 4 for int8) */
+    int32_t vec;             /* row-walk kernel: columns of C per lane; 0 = automatic, else 1,2,4 (,8 for f16; 1 or 4 for int8) */
     int32_t split_threshold; /* rows with at least this many nonzeros are split over the
                                 waves of a workgroup; 0 = automatic */
     int32_t spec_rows;       /* SPARSERT_KERNEL_SPEC: rows of A per generated code block
@@ -339,6 +342,9 @@ enum {
     SPARSERT_INFO_LDB,            /* elements between consecutive rows of B (N unless options.ldb) */
     SPARSERT_INFO_LDC,            /* elements between consecutive rows of C (N unless options.ldc) */
     SPARSERT_INFO_SPEC_PREFETCH,  /* SPEC plans: 128-byte lines of its block's code every lane touches ahead (0 = no prefetch) */
+    SPARSERT_INFO_STAGED_VEC,     /* row-walk plans that run the LDS-staged kernel: its columns per lane; 0 = the plan runs
+                                     the plain kernel, which VEC ... N_WG_ROWS describe */
+    SPARSERT_INFO_STAGED_ROWS,    /* ... and its rows per wave */
     SPARSERT_INFO_COUNT = 48      /* remaining entries are zero */
 };
 

@@ -125,6 +125,10 @@ int sparsert_plan_export(const sparsert_plan *plan, int32_t field, void *buf, si
         info[SPARSERT_INFO_SPEC_PREFETCH] = h.kernel == SPARSERT_KERNEL_SPEC ? h.spec.prefetch_lines : 0;
         info[SPARSERT_INFO_SPEC_LANES] = h.kernel == SPARSERT_KERNEL_SPEC ? h.spec.lanes_per_tile : 0;
         info[SPARSERT_INFO_SPEC_SWIZZLE] = h.kernel == SPARSERT_KERNEL_SPEC ? h.spec.swizzle : 0;
+        if (const sparsert::StagedRows s = sparsert::staged_rows_shape(h); s.V) {
+            info[SPARSERT_INFO_STAGED_VEC] = s.V;
+            info[SPARSERT_INFO_STAGED_ROWS] = s.rows_per_wave;
+        }
         src = info; bytes = sizeof(info);
         break;
     case SPARSERT_FIELD_ROW_NNZ: vec32(h.row_nnz); break;

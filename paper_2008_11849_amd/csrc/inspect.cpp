@@ -108,6 +108,15 @@ static int choose_vec(int32_t M, int32_t N, int32_t ldb, int32_t ldc, int vmax, 
     return best > 0 ? best : smallest;
 }
 
+static int default_vec(const HostPlan &h) {
+    const int vmax = h.conv ? 1 : (h.dtype == SPARSERT_F16 ? 8 : 4);
+    return choose_vec(h.M, h.N, h.ldb, h.ldc, vmax, h.dtype == SPARSERT_I8 ? 2 : 0);
+}
+
+static int32_t default_split_threshold(const HostPlan &h) { return ((int64_t)h.M * h.n_tiles < kFullTasks) ? 64 : 512; }
+
+bool row_walk_defaults(const HostPlan &h) { return h.vec == default_vec(h) && h.split_threshold == default_split_threshold(h); }
+
 int build_host_plan(const int32_t *row_ptr, const int32_t *col_idx, const void *vals,
                     int32_t M, int32_t K, int32_t N, const sparsert_options &opt,
                     HostPlan &h, std::string &err) {
@@ -170,8 +179,8 @@ int build_host_plan(const int32_t *row_ptr, const int32_t *col_idx, const void *
     }
 
     // Column tiling.
-    const int vmax = h.conv ? 1 : (h.dtype == SPARSERT_F16 ? 8 : 4);
-    h.vec = opt.vec ? opt.vec : choose_vec(M, N, h.ldb, h.ldc, vmax, h.dtype == SPARSERT_I8 ? 2 : 0);
+    h.vec = opt.vec ? opt.vec : default_vec(h);
+    h.plain_rows = opt.vec || opt.split_threshold || opt.natural_order;
     const int32_t nvc = N / h.vec;  // vector columns
     h.n_tiles = (nvc + kWave - 1) / kWave;
     h.lanes_per_tile = (nvc + h.n_tiles - 1) / h.n_tiles;
@@ -179,7 +188,7 @@ int build_host_plan(const int32_t *row_ptr, const int32_t *col_idx, const void *
 
     // Long rows are split over the waves of one workgroup.
     if (opt.split_threshold) h.split_threshold = opt.split_threshold;
-    else h.split_threshold = ((int64_t)M * h.n_tiles < kFullTasks) ? 64 : 512;
+    else h.split_threshold = default_split_threshold(h);
     h.n_split = 0;
     if (h.natural_order) h.split_threshold = INT32_MAX;   // split rows are a prefix of the sorted order only
     while (h.n_split < M && h.row_nnz[h.perm[h.n_split]] >= h.split_threshold) ++h.n_split;

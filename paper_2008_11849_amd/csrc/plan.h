@@ -62,6 +62,7 @@ struct HostPlan {
     int32_t natural_order = 0;         // rows kept in input order (load-balance ablation)
     int32_t batch = 1;                 // problems per call: images of a convolution, B/C pairs of an SpMM
     int32_t ldb = 0, ldc = 0;          // elements between consecutive rows of B and of C (N unless the caller widens them)
+    int32_t plain_rows = 0;            // vec, split_threshold or natural_order was set: a row-walk plan runs the plain kernel they describe
     bool kernel_auto = false;          // the executor family was the inspector's choice, not the caller's
 
     std::vector<int32_t> row_nnz, hist, perm, inv_perm, p_row_ptr, p_col_idx;
@@ -103,6 +104,9 @@ struct DevicePlan {
 int build_host_plan(const int32_t *row_ptr, const int32_t *col_idx, const void *vals,
                     int32_t M, int32_t K, int32_t N, const sparsert_options &opt,
                     HostPlan &out, std::string &err);
+
+// Are the columns per lane and the split threshold of a plan the ones chosen when nothing is set?
+bool row_walk_defaults(const HostPlan &h);
 
 // Generated-kernel path (specialize.cpp): fills h.spec, including the assembled code object.
 int build_spec_plan(HostPlan &h, const sparsert_options &opt, std::string &err);

@@ -15,7 +15,8 @@
 namespace {
 
 constexpr uint32_t kMagic = 0x54525053u;   // "SPRT"
-constexpr uint32_t kFormat = 3;   // bumped whenever the field list below changes
+constexpr uint32_t kFormat = 4;   // bumped whenever the field list below changes
+constexpr uint32_t kFormatWithoutPlainRows = 3;   // as 4 without plain_rows; still read
 
 struct Writer {
     std::vector<uint8_t> out;
@@ -158,6 +159,7 @@ int save_impl(const sparsert_plan *plan, void *buf, size_t cap, size_t *need) {
     sparsert::HostPlan &h = const_cast<sparsert::HostPlan &>(plan->host);   // the writer only reads
     Writer w;
     scalars(w, h);
+    w.i32(h.plain_rows);
     w.i64(h.spec.asm_bytes);
     w.str(h.spec.symbol);
     w.vec(h.row_nnz); w.vec(h.hist); w.vec(h.perm); w.vec(h.inv_perm); w.vec(h.p_row_ptr); w.vec(h.p_col_idx);
@@ -183,7 +185,7 @@ int load_impl(const void *buf, size_t size, int32_t host_only, sparsert_plan **o
     uint32_t magic, format; uint64_t len, sum;
     std::memcpy(&magic, b, 4); std::memcpy(&format, b + 4, 4); std::memcpy(&len, b + 8, 8); std::memcpy(&sum, b + 16, 8);
     if (magic != kMagic) return sparsert::set_error(SPARSERT_EINVAL, "not a serialised plan: bad magic word");
-    if (format != kFormat) return sparsert::set_error(SPARSERT_EUNSUPPORTED, "serialised plan has another format version");
+    if (format != kFormat && format != kFormatWithoutPlainRows) return sparsert::set_error(SPARSERT_EUNSUPPORTED, "serialised plan has another format version");
     if (len != size - 24) return sparsert::set_error(SPARSERT_EINVAL, "serialised plan is truncated or padded");
     if (fnv1a(b + 24, (size_t)len) != sum) return sparsert::set_error(SPARSERT_EINVAL, "serialised plan fails its checksum");
     sparsert_plan *plan = new (std::nothrow) sparsert_plan();
@@ -191,6 +193,7 @@ int load_impl(const void *buf, size_t size, int32_t host_only, sparsert_plan **o
     sparsert::HostPlan &h = plan->host;
     Reader r{b + 24, b + size};
     scalars(r, h);
+    if (format == kFormat) h.plain_rows = r.i32();
     h.spec.asm_bytes = r.i64();
     r.str(h.spec.symbol);
     r.vec(h.row_nnz); r.vec(h.hist); r.vec(h.perm); r.vec(h.inv_perm); r.vec(h.p_row_ptr); r.vec(h.p_col_idx);
@@ -201,6 +204,8 @@ int load_impl(const void *buf, size_t size, int32_t host_only, sparsert_plan **o
         delete plan;
         return sparsert::set_error(SPARSERT_EINVAL, "serialised plan is inconsistent");
     }
+    // (values that nothing but an option gives; an option that repeated the automatic value left no trace)
+    if (format == kFormatWithoutPlainRows) h.plain_rows = h.natural_order || !sparsert::row_walk_defaults(h);
     if (!host_only) {
         std::string err;
         const int rc = sparsert::upload_plan(h, plan->dev, err);

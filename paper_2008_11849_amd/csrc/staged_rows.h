@@ -66,7 +66,7 @@ inline bool staged_rows_fits(const HostPlan &h, const StagedRows &s) {
 // plain kernel's time: 58 of the 230, which gain 1.53 times, 3 of them losing 5 % to 12 %.
 inline StagedRows staged_rows_shape(const HostPlan &h) {
     StagedRows best;
-    if (h.kernel != SPARSERT_KERNEL_ROWS || h.conv) return best;
+    if (h.kernel != SPARSERT_KERNEL_ROWS || h.conv || h.plain_rows) return best;
     const int esz = h.elem_size();
     // 4-byte accesses past the operand's end are dropped whole: the copies need rows that end on 4 bytes.
     if ((int64_t)h.ldb * esz % 4 || (int64_t)h.N * esz % 4 || (int64_t)h.K * h.ldb * esz >= (1ll << 31)) return best;

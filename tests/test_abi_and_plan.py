@@ -554,6 +554,64 @@ def test_load_rejects_damaged_blobs():
     assert sp.raw.sparsert_plan_save(None, None, 0, None) == sp.EINVAL
 
 
+def _blob_layout(blob):
+    """Where the arrays of a saved plan lie: name -> (offset of the first byte, bytes)."""
+    at, out = 24 + 4 * (34 if blob[4] == 3 else 35) + 8, {}
+    at += 8 + int.from_bytes(blob[at:at + 8], "little")    # the kernel symbol
+    for name in ("row_nnz", "hist", "perm", "inv_perm", "p_row_ptr", "p_col_idx", "p_vals", "bins", "stream", "conv_seg", "segments"):
+        n = int.from_bytes(blob[at:at + 8], "little") * (1 if name == "p_vals" else 4)
+        out[name] = (at + 8, n)
+        at += 8 + n
+    return out
+
+
+def _resealed(blob):
+    """The blob with its length and checksum made right again."""
+    h = 1469598103934665603
+    for b in blob[24:]:
+        h = ((h ^ b) * 1099511628211) & (2 ** 64 - 1)
+    return blob[:8] + (len(blob) - 24).to_bytes(8, "little") + h.to_bytes(8, "little") + blob[24:]
+
+
+# 2048 x 256 at 50 % on 256 columns: a product that row-walk plans run with B staged through LDS
+STAGED = (2048, 256, 256)
+
+
+@pytest.mark.parametrize("opts", [dict(vec=1), dict(vec=2), dict(vec=4), dict(split_threshold=64), dict(split_threshold=1 << 30),
+                                  dict(natural_order=True)])
+def test_row_walk_options_keep_the_plain_kernel(opts):
+    """vec, split_threshold and natural_order describe the plain row-walk kernel: a plan made with one of them
+    runs it, also where a plan with nothing set takes the staged one."""
+    M, K, N = STAGED
+    csr = synth.uniform_csr(M, K, 0.5, 3)
+    plan = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, kernel=sp.KERNEL_ROWS)
+    info = plan.info()
+    assert plan.kernel_name() == f"void sparsert::staged_rows_kernel<float, {info['staged_vec']}, {info['staged_rows']}>(sparsert::StagedArgs)"
+    plan = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, kernel=sp.KERNEL_ROWS, **opts)
+    assert plan.kernel_name() == f"void sparsert::rows_kernel<float, {plan.info()['vec']}, false>(sparsert::RowsArgs)"
+    assert plan.info()["staged_vec"] == plan.info()["staged_rows"] == 0
+    again = sp.load(plan.save(), host_only=True)
+    assert again.kernel_name() == plan.kernel_name() and again.save() == plan.save()
+
+
+@pytest.mark.parametrize("opts,staged", [(dict(), True), (dict(vec=1), False), (dict(split_threshold=65), False), (dict(natural_order=True), False),
+                                         (dict(kernel=sp.KERNEL_SPEC, spec_rows=64, spec_ksplit=1), False)])
+def test_plans_saved_in_the_previous_format_load(opts, staged):
+    """Format 3 lacked the word that says whether a row-walk option was set; values other than the
+    automatic ones tell as much."""
+    M, K, N = STAGED if opts.get("kernel", 1) == 1 else (64, 64, 64)
+    csr = synth.uniform_csr(M, K, 0.5, 3)
+    plan = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, **dict(dict(kernel=sp.KERNEL_ROWS), **opts))
+    blob = plan.save()
+    assert blob[4] == 4
+    words = 24 + 4 * 34
+    old = _resealed(blob[:4] + b"\x03" + blob[5:words] + blob[words + 4:])
+    again = sp.load(old, host_only=True)
+    assert ("staged_rows_kernel" in again.kernel_name()) == staged
+    for name, fid in ALL_FIELDS.items():
+        assert again.export(fid).tobytes() == plan.export(fid).tobytes(), name
+
+
 def test_staged_default_for_large_and_very_sparse_products():
     """With no tiling option set, a large fp32 SpMM with a long reduction axis and at least 94.5 %
     zeros takes the LDS-staged variant with eight waves; anything else keeps DIRECT."""
