@@ -102,9 +102,35 @@ void staged_rule_stays_inside_the_limits() {
     EXPECT(!sparsert::staged_rows_shape(rows_plan(16700, 30000, 784, 16000)).V);      // 2.138 GB, more with the fill
 }
 
+// The tuner's list holds what an untuned plan would run, for any number of nonzeros: the generated kernel and, for
+// half and int8 products, the matrix cores with nothing else set; other families' plans only where they may win.
+void tuner_candidates_hold_the_defaults() {
+    for (int dtype = SPARSERT_F32; dtype <= SPARSERT_I8; ++dtype)
+        for (int64_t nnz : {(int64_t)5000, (int64_t)300000, (int64_t)2000000, (int64_t)5035156, (int64_t)100000000})
+            for (int family : {SPARSERT_KERNEL_AUTO, SPARSERT_KERNEL_ROWS, SPARSERT_KERNEL_SPEC})
+                for (int natural : {0, 1}) {
+                    sparsert_options b;
+                    std::memset(&b, 0, sizeof(b));
+                    b.dtype = dtype; b.kernel = family; b.natural_order = natural;
+                    int rows = 0, generated = 0, mfma = 0, generated_default = 0, mfma_default = 0;
+                    for (const sparsert_options &o : sparsert::tune_candidates(12288, 12288, 1024, nnz, b)) {
+                        const bool tiles = o.spec_rows || o.spec_tiles || o.spec_ksplit;
+                        if (o.kernel == SPARSERT_KERNEL_ROWS) { ++rows; continue; }
+                        ++(o.spec_mode == SPARSERT_SPEC_MFMA ? mfma : generated);
+                        if (!tiles) ++(o.spec_mode == SPARSERT_SPEC_MFMA ? mfma_default : generated_default);
+                        EXPECT(o.natural_order == natural && o.dtype == dtype);
+                    }
+                    const bool wants_mfma = dtype != SPARSERT_F32 && family != SPARSERT_KERNEL_ROWS && !natural;
+                    EXPECT((rows > 0) == (family != SPARSERT_KERNEL_SPEC));
+                    EXPECT(mfma_default == (wants_mfma ? 1 : 0) && mfma == (wants_mfma ? 6 : 0));
+                    EXPECT((generated > 0) == (family != SPARSERT_KERNEL_ROWS) && generated_default == (generated ? 1 : 0));
+                }
+}
+
 }  // namespace
 
 int main() {
+    tuner_candidates_hold_the_defaults();
     staged_rule_stays_inside_the_limits();
     Rng r{20081184ull};
     const int shapes[][3] = {{1, 1, 1}, {7, 5, 3}, {64, 48, 100}, {70, 150, 196}, {33, 260, 65}};
