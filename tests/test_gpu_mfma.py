@@ -64,6 +64,29 @@ def test_half_values_subnormals_and_non_finite_operands(tile):
     assert np.array_equal(got, base, equal_nan=True)
 
 
+@pytest.mark.parametrize("tile", TILES)
+def test_a_non_finite_operand_changes_its_own_columns_only(tile):
+    """Every other column keeps its bits, also where two waves store it (the last 16-byte chunk of a row overlaps the
+    one before if N is no multiple of 8), and a column's value does not depend on how many others are redone."""
+    rng = np.random.default_rng(11)
+    M, K = 150, 701
+    vals = rng.standard_normal((M, K)).astype(np.float16)
+    mask = rng.random((M, K)) < 0.25
+    csr = synth.csr_from_mask(vals, mask)
+    for N in (201, 131, 21):
+        B = rng.standard_normal((K, N)).astype(np.float16)
+        clean, _ = run_spmm(csr, B, **_opts(tile))
+        rows, _ = run_spmm(csr, B, kernel=sp.KERNEL_ROWS, split_threshold=1 << 30)   # sums in the order of the nonzeros
+        for columns in ((N - 9,), (N - 1,), (0, 5, N - 8, N - 3), tuple(range(0, N, 2)), tuple(range(N))):
+            X = B.copy()
+            X[3, list(columns)] = np.inf
+            got, _ = run_spmm(csr, X, **_opts(tile))
+            others = np.setdiff1d(np.arange(N), columns)
+            assert np.array_equal(got[:, others].view(np.uint16), clean[:, others].view(np.uint16)), (N, columns[:4])
+            want = np.where(mask[:, 3:4], np.copysign(np.float16(np.inf), vals[:, 3:4]), rows[:, list(columns)])
+            assert np.array_equal(got[:, list(columns)], want), (N, columns[:4])
+
+
 def test_plan_round_trip_and_refusals():
     csr = synth.int8_csr(70, 200, 0.8, 3)
     B = synth.int8_dense(200, 100, 4)
