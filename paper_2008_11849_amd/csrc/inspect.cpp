@@ -132,7 +132,7 @@ int build_host_plan(const int32_t *row_ptr, const int32_t *col_idx, const void *
     // row-walk kernel, whose inspector generates nothing.  Options that only the row-walk kernel
     // reads (vec, split_threshold) select it as well.
     if (opt.kernel != SPARSERT_KERNEL_AUTO) h.kernel = opt.kernel;
-    else h.kernel = (opt.vec == 0 && opt.split_threshold == 0 && ((h.nnz <= kAutoSpecNnz && spec_available()) || mfma_preferred(h, opt) >= 0))
+    else h.kernel = (opt.vec == 0 && opt.split_threshold == 0 && ((h.nnz <= kAutoSpecNnz && spec_available()) || mfma_preferred(h, opt, vals) >= 0))
                         ? SPARSERT_KERNEL_SPEC : SPARSERT_KERNEL_ROWS;
     h.kernel_auto = opt.kernel == SPARSERT_KERNEL_AUTO;
     const int esz = h.elem_size();

@@ -125,8 +125,8 @@ int rows_for_rounds(int32_t M, int groups_per_wg, int64_t wg_columns, int rounds
 // count; else R.
 int rows_without_thin_round(int32_t M, int R, int groups_per_wg, int64_t wg_columns, int hi);
 // The matrix-core tile (index into kMfmaConfigs) the inspector would take for this problem if nothing is set,
-// or -1 where generated code is expected to be faster or the variant does not apply.
-int mfma_preferred(const HostPlan &h, const sparsert_options &opt);
+// or -1 where generated code is expected to be faster or the variant does not apply.  vals: the nonzeros' values, in any order.
+int mfma_preferred(const HostPlan &h, const sparsert_options &opt, const void *vals);
 // What the autotuner times besides its first candidate (candidates.cpp); b: the caller's options, tuning fields cleared.
 std::vector<sparsert_options> tune_candidates(int32_t M, int32_t K, int32_t N, int64_t nnz, const sparsert_options &b);
 bool spec_available();   // can generated kernels be assembled in this process (is the code object manager loadable)?

@@ -1206,13 +1206,25 @@ static bool mfma_applies(const HostPlan &h) {
     return h.dtype != SPARSERT_F32 && !h.conv && h.N >= 16 && mfma_weight_bytes(h.M, h.K, h.elem_size()) < (1ll << 31);
 }
 
-int mfma_preferred(const HostPlan &h, const sparsert_options &opt) {
+// An infinite or undefined weight makes every sum of its row non-finite, and the kernel would redo that row's columns
+// on every call.
+static bool all_finite(const HostPlan &h, const void *vals) {
+    if (h.dtype != SPARSERT_F16) return true;   // int8
+    for (int32_t p = 0; p < h.nnz; ++p) {
+        uint16_t v;
+        std::memcpy(&v, static_cast<const char *>(vals) + 2 * (size_t)p, 2);
+        if ((v & 0x7c00u) == 0x7c00u) return false;
+    }
+    return true;
+}
+
+int mfma_preferred(const HostPlan &h, const sparsert_options &opt, const void *vals) {
     if (opt.kernel != SPARSERT_KERNEL_AUTO || opt.vec || opt.split_threshold || opt.spec_mode || opt.spec_rows || opt.spec_depth || opt.spec_tiles ||
         opt.spec_ksplit || opt.spec_lanes || opt.spec_swizzle || opt.spec_vec || opt.spec_prefetch || opt.natural_order || !mfma_applies(h))
         return -1;
     double t = 0;
     const int tile = mfma_best_tile(h, &t);
-    return t < generated_microseconds(h) ? tile : -1;
+    return t < generated_microseconds(h) && all_finite(h, vals) ? tile : -1;
 }
 
 // Matrix-core plan: which tile, and the name a kernel trace shows.
@@ -1239,7 +1251,7 @@ static int build_mfma_plan(HostPlan &h, const sparsert_options &opt, std::string
 
 int build_spec_plan(HostPlan &h, const sparsert_options &opt, std::string &err) {
     SpecPlan &sp = h.spec;
-    if (opt.spec_mode == SPARSERT_SPEC_MFMA || mfma_preferred(h, opt) >= 0) return build_mfma_plan(h, opt, err);
+    if (opt.spec_mode == SPARSERT_SPEC_MFMA || mfma_preferred(h, opt, h.p_vals.data()) >= 0) return build_mfma_plan(h, opt, err);
     Shape sh;
     if (int rc = choose_launch_shape(h, opt, sp, sh, err)) return rc;
     std::vector<std::vector<int32_t>> members;

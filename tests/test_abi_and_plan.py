@@ -554,6 +554,20 @@ def test_load_rejects_damaged_blobs():
     assert sp.raw.sparsert_plan_save(None, None, 0, None) == sp.EINVAL
 
 
+@pytest.mark.parametrize("weight", [np.inf, -np.inf, np.nan])
+def test_non_finite_weights_stay_off_the_matrix_cores(weight):
+    """Such a weight makes all sums of its row non-finite there, which costs a second pass on every call."""
+    csr = synth.uniform_csr(1024, 512, 0.8, 6, dtype=np.float16)
+    plan = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, 1024, 512, 1024, host_only=True)
+    assert plan.info()["spec_mode"] == sp.SPEC_MFMA
+    vals = csr.vals.copy()
+    vals[-1] = weight
+    plan = sp.inspect(csr.row_ptr, csr.col_idx, vals, 1024, 512, 1024, host_only=True)
+    assert plan.info()["kernel"] == sp.KERNEL_SPEC and plan.info()["spec_mode"] == sp.SPEC_DIRECT
+    plan = sp.inspect(csr.row_ptr, csr.col_idx, vals, 1024, 512, 1024, host_only=True, kernel=sp.KERNEL_SPEC, spec_mode=sp.SPEC_MFMA)
+    assert plan.info()["spec_mode"] == sp.SPEC_MFMA        # asked for
+
+
 def _blob_layout(blob):
     """Where the arrays of a saved plan lie: name -> (offset of the first byte, bytes)."""
     at, out = 24 + 4 * (34 if blob[4] == 3 else 35) + 8, {}
