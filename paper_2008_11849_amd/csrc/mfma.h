@@ -20,11 +20,6 @@ struct MfmaConfig {
 // One instruction contracts 64 bytes of every column: 32 halves or 64 int8.
 constexpr int mfma_step(int elem_size) { return 64 / elem_size; }
 
-// Upper bound of the zero-filled copy of A (rows rounded up to 128, columns to the longest slab).
-inline int64_t mfma_weight_bytes(int64_t M, int64_t K, int elem_size) {
-    return (M + 127) / 128 * 128 * ((K * elem_size + 511) / 512 * 512);
-}
-
 #define SPARSERT_MFMA_CONFIGS(X)                                  \
     X(0, 128, 128, 2, 4, 4, 2, 2, 4, 3.74, 0.197, 0.376, 0.27) \
     X(1, 64, 128, 2, 4, 2, 2, 2, 3, 3.00, 0.222, 0.324, 0.21)  \
@@ -42,6 +37,13 @@ constexpr MfmaConfig kMfmaConfigs[] = {
 #undef X
 };
 constexpr int kMfmaConfigCount = (int)(sizeof(kMfmaConfigs) / sizeof(kMfmaConfigs[0]));
+
+// The zero-filled copy of A for a tile: rows in whole tiles, columns in whole slabs.  It is addressed with 31 bits.
+inline int64_t mfma_weight_bytes(const MfmaConfig &c, int64_t M, int64_t K, int elem_size) {
+    const int64_t slab = (int64_t)c.steps * 64;
+    return (M + c.tm - 1) / c.tm * c.tm * ((K * elem_size + slab - 1) / slab * slab);
+}
+inline bool mfma_fits(const MfmaConfig &c, int64_t M, int64_t K, int elem_size) { return mfma_weight_bytes(c, M, K, elem_size) < (1ll << 31); }
 
 // Index of the configuration with this tile; 0 for a field means any.  -1: none.
 inline int mfma_find(int tm, int tn) {

@@ -375,7 +375,7 @@ int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err) {
         return SPARSERT_EINVAL;
     }
     const MfmaConfig &c = kMfmaConfigs[sp.mfma_config];
-    const int esz = h.elem_size(), slab = c.steps * mfma_step(esz);
+    const int esz = h.elem_size();
     MfmaArgs a;
     a.weights = d.mfma_weights; a.in = nullptr; a.out = nullptr;   // of the call
     a.p_row_ptr = d.p_row_ptr; a.inv_perm = d.inv_perm; a.stream = reinterpret_cast<const uint2 *>(d.stream);
@@ -385,8 +385,7 @@ int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err) {
     // Each XCD takes an eighth of the tiles: along M if that leaves its L2 less of A and B to hold, else along N.
     const double wb = (double)m_tiles * c.tm * a.K * esz, bb = (double)h.K * h.N * esz;
     a.m_fast = wb + bb / 8 < wb / 8 + bb;
-    const int64_t weight_bytes = m_tiles * (c.tm / 16) * ((a.K + slab - 1) / slab * c.steps) * 1024;
-    if (weight_bytes >= (1ll << 31) || ((int64_t)(h.K - 1) * h.ldb + h.N) * esz >= (1ll << 31)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
+    if (!mfma_fits(c, h.M, h.K, esz) || ((int64_t)(h.K - 1) * h.ldb + h.N) * esz >= (1ll << 31)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
     const void *kernel = nullptr;
     switch (sp.mfma_config * 2 + (h.dtype == SPARSERT_I8 ? 1 : 0)) {
 #define X(id, tm, tn, wm, wn, mf, nf, steps, stages, ...)                                              \

@@ -129,7 +129,7 @@ bool consistent(const sparsert::HostPlan &h) {
         for (size_t i = 0; i < M; ++i)
             if (h.inv_perm[i] < 0 || h.inv_perm[i] >= h.M || h.perm[h.inv_perm[i]] != (int32_t)i) return false;
         return h.dtype != SPARSERT_F32 && sp.mfma_config >= 0 && !sp.symbol.empty() &&
-               h.N >= 16 && !h.conv && sparsert::mfma_weight_bytes(h.M, h.K, h.elem_size()) < (1ll << 31);
+               h.N >= 16 && !h.conv && sparsert::mfma_fits(sparsert::kMfmaConfigs[sp.mfma_config], h.M, h.K, h.elem_size());
     }
     if (h.kernel == SPARSERT_KERNEL_SPEC) {
         const sparsert::SpecPlan &sp = h.spec;

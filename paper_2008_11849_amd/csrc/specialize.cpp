@@ -1182,11 +1182,13 @@ static void emit_kernel_descriptor(Gen &gen, const Shape &sh) {
 
 }
 
+// The tile with the least expected time of those that hold the zero-filled A; -1: none does.
 static int mfma_best_tile(const HostPlan &h, double *microseconds) {
-    int best = 0;
+    int best = -1;
     for (int i = 0; i < kMfmaConfigCount; ++i) {
+        if (!mfma_fits(kMfmaConfigs[i], h.M, h.K, h.elem_size())) continue;
         const double t = mfma_microseconds(kMfmaConfigs[i], h.M, h.K, h.N, h.batch, h.elem_size(), h.out_elem_size());
-        if (i == 0 || t < *microseconds) { *microseconds = t; best = i; }
+        if (best < 0 || t < *microseconds) { *microseconds = t; best = i; }
     }
     return best;
 }
@@ -1203,7 +1205,7 @@ static double generated_microseconds(const HostPlan &h) {
 }
 
 static bool mfma_applies(const HostPlan &h) {
-    return h.dtype != SPARSERT_F32 && !h.conv && h.N >= 16 && mfma_weight_bytes(h.M, h.K, h.elem_size()) < (1ll << 31);
+    return h.dtype != SPARSERT_F32 && !h.conv && h.N >= 16;
 }
 
 // An infinite or undefined weight makes every sum of its row non-finite, and the kernel would redo that row's columns
@@ -1224,15 +1226,19 @@ int mfma_preferred(const HostPlan &h, const sparsert_options &opt, const void *v
         return -1;
     double t = 0;
     const int tile = mfma_best_tile(h, &t);
-    return t < generated_microseconds(h) && all_finite(h, vals) ? tile : -1;
+    return tile >= 0 && t < generated_microseconds(h) && all_finite(h, vals) ? tile : -1;
 }
 
 // Matrix-core plan: which tile, and the name a kernel trace shows.
 static int build_mfma_plan(HostPlan &h, const sparsert_options &opt, std::string &err) {
     SpecPlan &sp = h.spec;
-    if (!mfma_applies(h)) { err = "the matrix-core variant is for half and int8 SpMM plans of at least 16 columns whose zero-filled A stays under 2 GiB"; return SPARSERT_EUNSUPPORTED; }
     double t = 0;
-    const int found = opt.spec_ksplit > 1 ? -1 : opt.spec_rows || opt.spec_tiles ? mfma_find(opt.spec_rows, 16 * opt.spec_tiles) : mfma_best_tile(h, &t);
+    const int best = mfma_best_tile(h, &t);
+    const int found = opt.spec_ksplit > 1 ? -1 : opt.spec_rows || opt.spec_tiles ? mfma_find(opt.spec_rows, 16 * opt.spec_tiles) : best;
+    if (!mfma_applies(h) || best < 0 || (found >= 0 && !mfma_fits(kMfmaConfigs[found], h.M, h.K, h.elem_size()))) {
+        err = "the matrix-core variant is for half and int8 SpMM plans of at least 16 columns whose zero-filled A stays under 2 GiB";
+        return SPARSERT_EUNSUPPORTED;
+    }
     if (found < 0) { err = "no matrix-core kernel with these spec_rows and spec_tiles"; return SPARSERT_EINVAL; }
     const MfmaConfig &c = kMfmaConfigs[found];
     sp.mode = SPARSERT_SPEC_MFMA;

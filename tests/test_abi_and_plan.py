@@ -568,6 +568,26 @@ def test_non_finite_weights_stay_off_the_matrix_cores(weight):
     assert plan.info()["spec_mode"] == sp.SPEC_MFMA        # asked for
 
 
+def test_matrix_core_tiles_that_cannot_hold_the_weights_are_refused_by_the_inspector():
+    """Tiles of 96 and 48 rows round M = 128 up further than 128 does: the zero-filled A of 128 x 6000000 halves takes
+    1.54 GB, 2.30 GB in tiles of 96 rows and 1.73 GB in tiles of 48."""
+    M, K, N = 128, 6_000_000, 16
+    row_ptr = np.minimum(np.arange(M + 1), 1).astype(np.int32)
+    col, vals = np.array([K - 1], dtype=np.int32), np.array([2.0], dtype=np.float16)
+
+    def status(K=K, **kw):
+        try:
+            sp.inspect(row_ptr, col if K > 5_999_999 else col * 0, vals, M, K, N, host_only=True, kernel=sp.KERNEL_SPEC, spec_mode=sp.SPEC_MFMA, **kw).destroy()
+            return sp.OK
+        except sp.SparseRTError as e:
+            return e.status
+
+    assert status() == status(spec_rows=128) == status(spec_rows=48) == sp.OK
+    assert status(spec_rows=96) == sp.EUNSUPPORTED
+    assert status(K=9_000_000) == status(K=9_000_000, spec_rows=16) == sp.EUNSUPPORTED   # no tile holds 2.30 GB
+    assert status(spec_rows=24) == sp.EINVAL                                             # no such tile
+
+
 def _blob_layout(blob):
     """Where the arrays of a saved plan lie: name -> (offset of the first byte, bytes)."""
     at, out = 24 + 4 * (34 if blob[4] == 3 else 35) + 8, {}
