@@ -104,7 +104,12 @@ bool consistent(const sparsert::HostPlan &h) {
         for (size_t p = 0; p < nnz; ++p) {
             const uint64_t off = h.stream[2 * p];
             if (off >= limit || off % row_bytes) return false;
+            // The staged and the matrix-core plans are laid out from the columns: the same rows of B, in ascending order.
+            if (off / row_bytes != (uint64_t)h.p_col_idx[p]) return false;
         }
+        for (size_t i = 0; i < M; ++i)
+            for (int32_t p = h.p_row_ptr[i] + 1; p < h.p_row_ptr[i + 1]; ++p)
+                if (h.p_col_idx[p] <= h.p_col_idx[p - 1]) return false;
     } else {
         if (h.Cin <= 0 || h.H <= 0 || h.W <= 0 || (int64_t)h.K != 9ll * h.Cin || (int64_t)h.N != (int64_t)h.H * h.W) return false;
         if (((int64_t)h.Cin * h.H * h.W + h.W + 1) * esz >= (1ll << 27)) return false;

@@ -646,6 +646,52 @@ def test_plans_saved_in_the_previous_format_load(opts, staged):
         assert again.export(fid).tobytes() == plan.export(fid).tobytes(), name
 
 
+@pytest.mark.parametrize("shape,opts,dtype", [(STAGED, dict(kernel=sp.KERNEL_ROWS), np.float32), ((9, 40, 32), dict(kernel=sp.KERNEL_ROWS), np.int8),
+                                              ((9, 40, 32), dict(kernel=sp.KERNEL_ROWS, vec=1), np.float32),
+                                              ((9, 40, 32), dict(kernel=sp.KERNEL_SPEC, spec_mode=sp.SPEC_MFMA), np.float16)])
+def test_load_rejects_columns_out_of_order_or_at_odds_with_the_stream(shape, opts, dtype):
+    """The staged and the matrix-core plans lay the weights out from the column indices: columns that do not ascend
+    would point outside the chunk of B that LDS holds, and a column's word of the stream names the same row of B."""
+    M, K, N = shape
+    csr = synth.csr_from_mask(np.ones((M, K), dtype=dtype), np.random.default_rng(8).random((M, K)) < 0.5)
+    plan = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, **opts)
+    blob = plan.save()
+    layout = _blob_layout(blob)
+    row_ptr = plan.export(sp.FIELD_P_ROW_PTR)
+    assert row_ptr[8] - row_ptr[7] > 2
+    first, row_bytes = int(row_ptr[7]), N * np.dtype(dtype).itemsize
+
+    def status(change):
+        b = bytearray(blob)
+        at, n = layout["p_col_idx"]
+        col = np.frombuffer(b, dtype=np.int32, count=n // 4, offset=at)
+        at, n = layout["stream"]
+        change(col, np.frombuffer(b, dtype=np.uint32, count=n // 4, offset=at)[0::2])
+        try:
+            sp.load(_resealed(bytes(b)), host_only=True).destroy()
+            return sp.OK
+        except sp.SparseRTError as e:
+            return e.status
+
+    def swap(col, word):          # two nonzeros of a row change places
+        for x in (col, word):
+            x[first], x[first + 1] = x[first + 1], int(x[first])
+
+    def repeat(col, word):        # a column twice
+        for x in (col, word):
+            x[first + 1] = x[first]
+
+    def word_only(col, word):     # another row of B, in bounds
+        word[first] = (int(col[first]) + 1) % K * row_bytes
+
+    def column_only(col, word):
+        col[first + 1] = col[first]
+
+    assert status(lambda col, word: None) == sp.OK
+    for change in (swap, repeat, word_only, column_only):
+        assert status(change) == sp.EINVAL, change.__name__
+
+
 def test_staged_default_for_large_and_very_sparse_products():
     """With no tiling option set, a large fp32 SpMM with a long reduction axis and at least 94.5 %
     zeros takes the LDS-staged variant with eight waves; anything else keeps DIRECT."""
