@@ -28,6 +28,10 @@ static int address(PyObject *o, void **out) {
 
 static PyObject *execute(int which, PyObject *self, PyObject *const *args, Py_ssize_t nargs, PyObject *kwnames) {
     (void)self;
+    if (g_check == NULL) {
+        PyErr_SetString(PyExc_RuntimeError, "bind() has not been called: import the sparsert module");
+        return NULL;
+    }
     if (kwnames == NULL && (nargs == 3 || nargs == 4)) {
         PyObject *handle = PyObject_GetAttr(args[0], g_handle);
         if (handle == NULL) return NULL;
