@@ -37,7 +37,6 @@
 #include <string>
 #include <type_traits>
 #include <utility>
-#include <vector>
 
 #include "lds_copy.h"
 #include "mfma.h"
@@ -346,24 +345,6 @@ __global__ __launch_bounds__(WM *WN *kWave, 2) void mfma_kernel(const MfmaArgs a
                 const int n = column(n0 + __builtin_amdgcn_ds_bpermute((e - i * count) * 4, nth));
                 if (i < MF * 16 && row < a.M) out[(size_t)row * a.ldc + n] = (_Float16)exact_element(a, in, row, n);
             }
-        }
-    }
-}
-
-// A as fragments, zero-filled to whole workgroup tiles and slabs.
-void mfma_pack(const HostPlan &h, std::vector<uint8_t> &out) {
-    const MfmaConfig &c = kMfmaConfigs[h.spec.mfma_config];
-    const int esz = h.elem_size(), step = mfma_step(esz);
-    const int64_t m_tiles = (h.M + c.tm - 1) / c.tm * (c.tm / 16), k_steps = (h.K + c.steps * step - 1) / (c.steps * step) * c.steps;
-    out.assign((size_t)(m_tiles * k_steps) * 1024, 0);
-    for (int32_t slot = 0; slot < h.M; ++slot) {
-        const int32_t m = h.perm[slot];
-        for (int32_t p = h.p_row_ptr[slot]; p < h.p_row_ptr[slot + 1]; ++p) {
-            const int32_t k = h.p_col_idx[p];
-            const int kk = k % step, half_step = step / 2, rows = step / 8;
-            const int lane = kk % half_step / rows * 16 + m % 16, elem = kk / half_step * rows + kk % rows;
-            std::memcpy(&out[(size_t)(((m / 16) * k_steps + k / step) * 64 + lane) * 16 + (size_t)elem * esz],
-                        &h.p_vals[(size_t)p * esz], (size_t)esz);
         }
     }
 }

@@ -148,10 +148,10 @@ struct StagedPack {
     std::vector<uint8_t> counts;
     std::vector<int32_t> starts, rows;
 };
-void staged_rows_pack(const HostPlan &h, StagedPack &out);
+void staged_rows_pack(const HostPlan &h, StagedPack &out);   // (pack.cpp)
 int prepare_staged_rows(const HostPlan &h, DevicePlan &d, std::string &err);   // fills d.launch
 // Matrix-core executor (mfma.hip).
-void mfma_pack(const HostPlan &h, std::vector<uint8_t> &out);
+void mfma_pack(const HostPlan &h, std::vector<uint8_t> &out);   // (pack.cpp)
 int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err);   // fills d.launch
 // Comparison of two results of a plan (kernels.hip).  launch_compare: two kernels on `stream`,
 // partials_dev must hold 4 words per block of compare_blocks(h), result_dev receives 4 words.

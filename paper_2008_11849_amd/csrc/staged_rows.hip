@@ -19,11 +19,9 @@
 // order over the rows by descending length.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cstddef>
 #include <cstring>
 #include <string>
-#include <vector>
 
 #include "lds_copy.h"
 #include "staged_rows.h"
@@ -176,44 +174,6 @@ __global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(con
                 if (col + j < a.N) dst[j] = (out_t)acc[r][j];
         }
     }
-}
-
-// The nonzeros in the order the waves meet them, and what goes with it.
-void staged_rows_pack(const HostPlan &h, StagedPack &out) {
-    const StagedRows s = staged_rows_shape(h);
-    const int rw = s.rows_per_wave, owners = s.groups * kStagedWaves;
-    out.stream.reserve((size_t)h.nnz * 2 + (size_t)owners * s.chunks * rw * 3 + 32);
-    out.counts.assign((size_t)owners * s.chunks * rw, 0);
-    out.starts.assign(owners, 0);
-    out.rows.assign((size_t)owners * rw, -1);
-    std::vector<int32_t> slot_of((size_t)owners * rw, -1);
-    for (int32_t i = 0; i < h.M; ++i) {   // serpentine over the groups, then over the waves of a group
-        const int round = i / s.groups, pos = i % s.groups, g = round & 1 ? s.groups - 1 - pos : pos;
-        const int r = round / kStagedWaves, w = round % kStagedWaves, wave = r & 1 ? kStagedWaves - 1 - w : w;
-        const size_t at = ((size_t)g * kStagedWaves + wave) * rw + r;
-        slot_of[at] = i;
-        out.rows[at] = h.perm[i];
-    }
-    std::vector<int32_t> next((size_t)rw);
-    for (int o = 0; o < owners; ++o) {
-        out.starts[o] = (int32_t)(out.stream.size() / 2);
-        for (int r = 0; r < rw; ++r) next[r] = slot_of[(size_t)o * rw + r] < 0 ? 0 : h.p_row_ptr[slot_of[(size_t)o * rw + r]];
-        for (int c = 0; c < s.chunks; ++c)
-            for (int r = 0; r < rw; ++r) {
-                const int32_t slot = slot_of[(size_t)o * rw + r];
-                if (slot < 0) continue;
-                const int32_t limit = std::min<int64_t>(h.K, (int64_t)(c + 1) * s.chunk), end = h.p_row_ptr[slot + 1];
-                int n = 0;
-                const uint32_t zero_row = (uint32_t)(s.chunk * s.pitch);
-                for (; next[r] < end && h.p_col_idx[next[r]] < limit; ++next[r], ++n) {
-                    out.stream.push_back((uint32_t)(h.p_col_idx[next[r]] - c * s.chunk) * (uint32_t)s.pitch);
-                    out.stream.push_back(h.stream[2 * (size_t)next[r] + 1]);
-                }
-                if (n % 2) { ++n; out.stream.push_back(zero_row); out.stream.push_back(0); }
-                out.counts[((size_t)o * s.chunks + c) * rw + r] = (uint8_t)(n / 2);
-            }
-    }
-    out.stream.resize(out.stream.size() + 32, 0);
 }
 
 int prepare_staged_rows(const HostPlan &h, DevicePlan &d, std::string &err) {

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/sparsert.h"
+#include "../../paper_2008_11849_amd/csrc/mfma.h"
 #include "../../paper_2008_11849_amd/csrc/staged_rows.h"
 
 namespace {
@@ -127,6 +128,96 @@ void tuner_candidates_hold_the_defaults() {
                 }
 }
 
+sparsert::HostPlan host_plan(const Csr &c, int M, int K, int N, sparsert_options o) {
+    sparsert::HostPlan h;
+    std::string err;
+    o.host_only = 1;
+    EXPECT(sparsert::build_host_plan(c.row_ptr.data(), c.col.data(), c.vals.data(), M, K, N, o, h, err) == SPARSERT_OK);
+    if (h.kernel == SPARSERT_KERNEL_SPEC) EXPECT(sparsert::build_spec_plan(h, o, err) == SPARSERT_OK);
+    return h;
+}
+
+// Fragments of every matrix-core tile: each weight once, at the place its row, step and lane give, zeros elsewhere.
+int mfma_layout_holds_every_weight_once(Rng &r) {
+    int plans = 0;
+    const int shapes[][2] = {{1, 1}, {15, 31}, {17, 65}, {97, 129}, {130, 700}};
+    for (const auto &s : shapes)
+        for (int dtype : {(int)SPARSERT_F16, (int)SPARSERT_I8})
+            for (const sparsert::MfmaConfig &cfg : sparsert::kMfmaConfigs) {
+                const int M = s[0], K = s[1], esz = dtype == SPARSERT_F16 ? 2 : 1;
+                Csr c = make(M, K, 0.4, esz, r, (M & 1) != 0);
+                for (uint8_t &v : c.vals) v |= 1;   // no zeros among them
+                sparsert_options o;
+                std::memset(&o, 0, sizeof(o));
+                o.dtype = dtype; o.kernel = SPARSERT_KERNEL_SPEC; o.spec_mode = SPARSERT_SPEC_MFMA;
+                o.spec_rows = cfg.tm; o.spec_tiles = cfg.tn / 16;
+                const sparsert::HostPlan h = host_plan(c, M, K, 33, o);
+                std::vector<uint8_t> f;
+                sparsert::mfma_pack(h, f);
+                EXPECT((int64_t)f.size() == sparsert::mfma_weight_bytes(cfg, M, K, esz));
+                // lane 16 g + i of a fragment holds row i; its 16 bytes are the g-th eighth of K's first half of a
+                // step (4 halves, 8 int8), then of the second half
+                const int step = 64 / esz, piece = 8 / esz, steps = (int)(f.size() / 1024 / ((M + cfg.tm - 1) / cfg.tm * (cfg.tm / 16)));
+                size_t nonzero = 0;
+                for (uint8_t v : f) nonzero += v != 0;
+                EXPECT(nonzero == c.vals.size());
+                for (int m = 0; m < M; ++m)
+                    for (int p = c.row_ptr[m]; p < c.row_ptr[m + 1]; ++p) {
+                        const int k = c.col[p], second = k % step / (step / 2), g = k % (step / 2) / piece;
+                        const size_t at = ((size_t)(m / 16) * steps + k / step) * 1024 + (size_t)(16 * g + m % 16) * 16 + (size_t)second * 8 + (size_t)(k % piece) * esz;
+                        EXPECT(at + esz <= f.size() && std::memcmp(&f[at], &c.vals[(size_t)p * esz], esz) == 0);
+                    }
+                ++plans;
+            }
+    return plans;
+}
+
+// The staged stream walked as a wave does: every row of C belongs to one place, its pairs name its columns in order,
+// operands lie inside the chunk and fillers on the row of zeros behind it.
+int staged_layout_walks_every_row(Rng &r) {
+    int plans = 0;
+    const struct { int M, K, N, batch; double density; } shapes[] = {{2049, 200, 196, 4, 0.3}, {2100, 333, 516, 1, 0.2}, {4000, 90, 2000, 1, 0.1}, {4096, 1500, 788, 1, 0.1}};
+    for (const auto &s : shapes)
+        for (int dtype = SPARSERT_F32; dtype <= SPARSERT_I8; ++dtype) {
+            const Csr c = make(s.M, s.K, s.density, dtype == SPARSERT_F16 ? 2 : dtype == SPARSERT_I8 ? 1 : 4, r, false);
+            sparsert_options o;
+            std::memset(&o, 0, sizeof(o));
+            o.dtype = dtype; o.kernel = SPARSERT_KERNEL_ROWS; o.batch = s.batch;
+            const sparsert::HostPlan h = host_plan(c, s.M, s.K, s.N, o);
+            const sparsert::StagedRows g = sparsert::staged_rows_shape(h);
+            if (!g.V) { EXPECT(dtype != SPARSERT_F32); continue; }
+            sparsert::StagedPack pack;
+            sparsert::staged_rows_pack(h, pack);
+            const int rw = g.rows_per_wave, owners = g.groups * sparsert::kStagedWaves;
+            EXPECT((int)pack.starts.size() == owners && (int)pack.rows.size() == owners * rw && (int64_t)pack.counts.size() == (int64_t)owners * g.chunks * rw);
+            EXPECT((int64_t)pack.stream.size() <= 2 * ((int64_t)h.nnz + (int64_t)h.M * g.chunks + 16));   // what the rule allows for
+            std::vector<int> seen(s.M, 0);
+            for (int owner = 0; owner < owners; ++owner) {
+                size_t p = (size_t)pack.starts[owner] * 2;
+                std::vector<int> at(rw);
+                for (int i = 0; i < rw; ++i)
+                    if (pack.rows[owner * rw + i] >= 0) { ++seen[pack.rows[owner * rw + i]]; at[i] = c.row_ptr[pack.rows[owner * rw + i]]; }
+                for (int chunk = 0; chunk < g.chunks; ++chunk)
+                    for (int i = 0; i < rw; ++i) {
+                        const int n = 2 * pack.counts[((size_t)owner * g.chunks + chunk) * rw + i], row = pack.rows[owner * rw + i];
+                        if (row < 0) { EXPECT(n == 0); continue; }
+                        for (int q = 0; q < n; ++q, p += 2) {
+                            const uint32_t off = pack.stream[p], k = (uint32_t)chunk * g.chunk + off / g.pitch;
+                            EXPECT(off % g.pitch == 0 && off <= (uint32_t)(g.chunk * g.pitch));
+                            if (off == (uint32_t)(g.chunk * g.pitch)) { EXPECT(q == n - 1 && pack.stream[p + 1] == 0); continue; }
+                            EXPECT(at[i] < c.row_ptr[row + 1] && (uint32_t)c.col[at[i]] == k);
+                            ++at[i];
+                        }
+                    }
+                for (int i = 0; i < rw; ++i)
+                    if (pack.rows[owner * rw + i] >= 0) EXPECT(at[i] == c.row_ptr[pack.rows[owner * rw + i] + 1]);
+            }
+            for (int v : seen) EXPECT(v == 1);
+            ++plans;
+        }
+    return plans;
+}
+
 }  // namespace
 
 int main() {
@@ -135,6 +226,8 @@ int main() {
     Rng r{20081184ull};
     const int shapes[][3] = {{1, 1, 1}, {7, 5, 3}, {64, 48, 100}, {70, 150, 196}, {33, 260, 65}};
     int plans = 0;
+    plans += mfma_layout_holds_every_weight_once(r);
+    plans += staged_layout_walks_every_row(r);
     for (const auto &s : shapes) {
         const int M = s[0], K = s[1], N = s[2];
         for (int dtype = SPARSERT_F32; dtype <= SPARSERT_I8; ++dtype) {

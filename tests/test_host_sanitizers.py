@@ -20,7 +20,7 @@ def test_host_code_is_clean_under_address_and_undefined_behaviour_sanitizers(tmp
     cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
            "-static-libasan", "-static-libubsan", "-I", os.path.join(ROOT, "include"), "-o", exe,
            os.path.join(HERE, "main.cpp"), os.path.join(HERE, "stubs.cpp")]
-    cmd += [os.path.join(CSRC, f) for f in ("api.cpp", "inspect.cpp", "specialize.cpp", "candidates.cpp", "serialize.cpp")]
+    cmd += [os.path.join(CSRC, f) for f in ("api.cpp", "inspect.cpp", "specialize.cpp", "candidates.cpp", "serialize.cpp", "pack.cpp")]
     cmd += ["-ldl", "-lpthread"]
     build = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
     assert build.returncode == 0, build.stderr[-3000:]
