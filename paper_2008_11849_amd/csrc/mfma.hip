@@ -120,8 +120,14 @@ template <typename F, int... I> __device__ __forceinline__ void each_constant(F 
     (f(std::integral_constant<int, I>()), ...);
 }
 
+// Waves per SIMD the registers are to leave room for: two, or one where the slabs in LDS keep a second workgroup of
+// four waves from the compute unit (160 KiB).
+constexpr int mfma_waves_per_simd(int tm, int tn, int waves, int steps, int stages) {
+    return waves >= 8 || 2 * (tm + tn) * 64 * steps * stages <= 160 * 1024 ? 2 : 1;
+}
+
 template <int DT, int WM, int WN, int MF, int NF, int STEPS, int STAGES>
-__global__ __launch_bounds__(WM *WN *kWave, 2) void mfma_kernel(const MfmaArgs a) {
+__global__ __launch_bounds__(WM *WN *kWave, mfma_waves_per_simd(WM *MF * 16, WN *NF * 16, WM *WN, STEPS, STAGES)) void mfma_kernel(const MfmaArgs a) {
     typedef Kind<DT> Q;
     typedef typename Q::acc_t acc_t;
     typedef typename Q::frag_t frag_t;
