@@ -52,21 +52,27 @@ typedef enum sparsert_dtype { SPARSERT_F32 = 0, SPARSERT_F16 = 1, SPARSERT_I8 = 
 
 /* Executor families (options.kernel / INFO[SPARSERT_INFO_KERNEL]). */
 typedef enum sparsert_kernel {
-    SPARSERT_KERNEL_AUTO = 0,  /* the inspector chooses: the generated kernel with its shape-dependent
+    SPARSERT_KERNEL_AUTO = 0,  /* the inspector chooses.  Half and int8 SpMM plans of at least 16 columns, with no tuning field
+                                  set and no infinite or undefined weight, take the matrix-core variant
+                                  (SPARSERT_SPEC_MFMA) where it is estimated to be faster than generated code, for any
+                                  number of nonzeros; their plan holds a zero-filled copy of A on the device: M x K
+                                  elements and what rounding up to whole tiles adds, under 2 GiB.
+                                  Otherwise the generated kernel with its shape-dependent
                                   defaults when the code object manager (libamd_comgr) can be loaded, A has
                                   at most 4194304 nonzeros (about 4 s of assembling per million; the inspector is off
                                   the latency path, Section 2.3) and neither vec nor split_threshold is set;
-                                  the row-walk kernel otherwise, and also when the generator declines the
+                                  the row-walk kernel in all other cases, and also when the generator declines the
                                   problem (EUNSUPPORTED / ECOMPILE) */
     SPARSERT_KERNEL_ROWS = 1,  /* a fixed kernel that walks the rows' nonzeros: one wave per row, B read straight from
                                   L2/HBM.  SpMM plans with none of vec, split_threshold and natural_order set run a
                                   variant that copies B to LDS where that is estimated to be faster
                                   (SPARSERT_INFO_STAGED_VEC); setting one of them keeps the plain kernel */
     SPARSERT_KERNEL_SPEC = 2   /* per-matrix generated gfx950 code with the nonzeros of A as
-                                  instruction constants (Section 3.5) */
+                                  instruction constants (Section 3.5); with spec_mode = SPARSERT_SPEC_MFMA the
+                                  matrix-core kernel, for which nothing is generated */
 } sparsert_kernel;
 
-/* Variants of the generated kernel (options.spec_mode). */
+/* Variants of SPARSERT_KERNEL_SPEC (options.spec_mode). */
 typedef enum sparsert_spec_mode {
     SPARSERT_SPEC_AUTO = 0,
     SPARSERT_SPEC_DIRECT = 1, /* a workgroup's waves run one code block on adjacent column tiles;
@@ -74,8 +80,13 @@ typedef enum sparsert_spec_mode {
     SPARSERT_SPEC_LDS = 2,    /* a workgroup's waves run adjacent code blocks on one column tile;
                                  the tile's B rows are staged once through LDS (SpMM plans of every
                                  storage type; half and int8 operands are widened to 32 bits on the way in) */
-    SPARSERT_SPEC_MFMA = 3    /* half and int8 SpMM plans: zero-filled tiles of A on the matrix cores, from a fixed kernel (nothing
-                                 is generated).  spec_rows rows x 16 * spec_tiles columns of C per workgroup; fields left at 0 are chosen, combinations without a kernel give EINVAL */
+    SPARSERT_SPEC_MFMA = 3    /* half and int8 SpMM plans of at least 16 columns: zero-filled tiles of A on the matrix cores, from a
+                                 fixed kernel (nothing is generated).  spec_rows rows x 16 * spec_tiles columns of C per workgroup;
+                                 fields left at 0 are chosen, a tile without a kernel and a spec_ksplit above 1 give EINVAL.
+                                 spec_depth, spec_lanes, spec_swizzle, spec_vec and spec_prefetch describe generated
+                                 code and are not read.  The plan holds a zero-filled copy of A on the device; one of 2 GiB or
+                                 more gives EUNSUPPORTED.  Columns that an infinite or undefined operand reaches are computed a
+                                 second time, from the nonzeros alone, within the same call */
 } sparsert_spec_mode;
 
 /* Zero-initialise, then set what you need.  All-zero = fp32 SpMM, automatic tiling. */
@@ -95,8 +106,9 @@ typedef struct sparsert_options {
                                 (accumulator registers per wave), 1 ... 232 as far as the registers
                                 of the workgroup's waves fit a compute unit; 0 = automatic: as many
                                 as leave the launch about two waves per SIMD of the chip, at most 96,
-                                then up to 15 % more (at most 128) where that spares the launch a
-                                last round of workgroups that only a few compute units take part in */
+                                then up to 3/4 more (at most 128, 96 without a K split) where 257 to 512
+                                workgroups become 256 at most, or up to 15 % more (at most 128) where that spares
+                                the launch a last round of workgroups that only a few compute units take part in */
     int32_t spec_depth;      /* SPARSERT_KERNEL_SPEC: B rows a wave keeps in flight; 0 = automatic */
     int32_t spec_tiles;      /* SPARSERT_KERNEL_SPEC: waves per workgroup (adjacent column tiles in
                                 DIRECT mode, adjacent code blocks in LDS mode): 1,2,4,8,16;

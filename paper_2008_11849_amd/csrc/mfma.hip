@@ -48,14 +48,9 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-typedef _Float16 half4_any __attribute__((ext_vector_type(4), aligned(2)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef int32_t int2v __attribute__((ext_vector_type(2)));
-typedef int32_t int4_any __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
-typedef uint32_t uint4_any __attribute__((ext_vector_type(4), aligned(1)));
 typedef float float4v __attribute__((ext_vector_type(4)));
-typedef const char __attribute__((address_space(1))) *gbytes;
 typedef __attribute__((address_space(3))) short4v *lds_short4;
 typedef __attribute__((address_space(3))) int2v *lds_int2;
 

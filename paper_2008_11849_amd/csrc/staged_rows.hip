@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(con
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();   // the chunk is there, and nobody reads the other buffer any more
         asm volatile("" ::: "memory");
-        // The stream's cache lines of the next two KiB, into the L2 cache: a scalar load that has to go beyond it
+        // The stream's cache lines of the next four KiB, into the L2 cache: a scalar load that has to go beyond it
         // takes 1 us, and waiting for LDS waits for scalar loads as well.  (The words themselves go to a corner of LDS.)
         touch_to_lds(rstream, (int)((const char __attribute__((address_space(4))) *)p - (const char __attribute__((address_space(4))) *)a.stream) + lane * 64, lds0 + kStagedLdsBytes - kStagedTouchBytes);
         if (c + 1 < a.chunks) issue(c + 1);
