@@ -554,6 +554,49 @@ def test_load_rejects_damaged_blobs():
     assert sp.raw.sparsert_plan_save(None, None, 0, None) == sp.EINVAL
 
 
+# M, K, N, batch, type, sparsity; rows and 16-column tiles of the matrix-core plan, or None for generated code.  The
+# measured times, microseconds: matrix cores | generated, both in their default shapes.
+AUTO_CHOICES = [
+    (3072, 768, 1024, 1, np.float16, 0.95, (96, 8)),      # 9.2 | 11.3
+    (1024, 1024, 4096, 1, np.float16, 0.80, (128, 8)),    # 12.4 | 45.0
+    (768, 3072, 1024, 1, np.int8, 0.95, (64, 4)),         # 9.9 | 13.8
+    (440, 448, 715, 1, np.float16, 0.884, (32, 4)),       # 3.5 | 7.4
+    (96, 2304, 1358, 1, np.float16, 0.81, (32, 2)),       # 7.5 | 12.0
+    (744, 784, 144, 1, np.int8, 0.811, (32, 2)),          # 2.9 | 4.4
+    (246, 240, 555, 4, np.int8, 0.847, (64, 4)),          # 3.6 | 5.3
+    (4096, 4096, 1024, 1, np.float16, 0.70, (128, 8)),    # five million nonzeros: beyond what code is generated for
+    (384, 3151, 381, 1, np.float16, 0.937, None),         # 10.2 | 8.6
+    (1624, 112, 2432, 1, np.float16, 0.964, None),        # 6.7 | 4.8
+    (4000, 704, 60, 1, np.float16, 0.969, None),          # 3.3 | 2.9
+    (704, 164, 384, 4, np.float16, 0.952, None),          # 5.0 | 3.8
+    (256, 1216, 80, 1, np.int8, 0.95, None),              # 3.3 | 2.4
+    (1024, 512, 15, 1, np.float16, 0.80, None),           # fewer columns than a chunk of 16 bytes needs
+    (1024, 512, 1024, 1, np.float32, 0.80, None),         # no fp32 variant
+]
+
+
+@pytest.mark.parametrize("M,K,N,batch,dtype,sparsity,tile", AUTO_CHOICES)
+def test_which_products_go_to_the_matrix_cores(M, K, N, batch, dtype, sparsity, tile):
+    csr = synth.int8_csr(M, K, sparsity, 6) if dtype == np.int8 else synth.uniform_csr(M, K, sparsity, 6, dtype=dtype)
+    plan = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, batch=batch)
+    info = plan.info()
+    assert info["kernel"] == sp.KERNEL_SPEC
+    assert (info["spec_mode"] == sp.SPEC_MFMA) == (tile is not None)
+    if tile:
+        assert (info["spec_rows"], info["spec_tiles"]) == tile
+        # a field of another executor, or of generated code, keeps the choice from being made
+        if csr.vals.size < 200_000:
+            for opts in (dict(vec=1), dict(split_threshold=99), dict(natural_order=True), dict(spec_rows=16), dict(spec_mode=sp.SPEC_DIRECT)):
+                info = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, batch=batch, **opts).info()
+                assert info["spec_mode"] != sp.SPEC_MFMA, opts
+
+
+def test_convolutions_stay_off_the_matrix_cores():
+    csr, _ = synth.conv_weights_csr(64, 64, 0.8, 5)
+    info = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals.astype(np.float16), 64, 576, 784, host_only=True, conv=(64, 28, 28), batch=8).info()
+    assert info["kernel"] == sp.KERNEL_SPEC and info["spec_mode"] == sp.SPEC_DIRECT
+
+
 @pytest.mark.parametrize("weight", [np.inf, -np.inf, np.nan])
 def test_non_finite_weights_stay_off_the_matrix_cores(weight):
     """Such a weight makes all sums of its row non-finite there, which costs a second pass on every call."""
