@@ -25,6 +25,8 @@ CASES = [
     (4000, 90, 2000, 0.1, 1, 0, "44", True, True),
     (4096, 1500, 788, 0.1, 1, 0, "44", True, True),
     (2000, 1000, 500, 0.3, 4, 0, "44", True, False),
+    (1500, 200, 516, 0.3, 3, 4, "44", True, True),     # batches with a row pitch, of every type
+    (1030, 300, 772, 0.3, 3, 8, "44", True, True),
 ]
 
 
