@@ -242,6 +242,7 @@ int sparsert_conv3x3(const sparsert_plan *plan, const void *X_dev, void *Y_dev, 
  */
 #define SPARSERT_TUNE_MAX 64
 typedef struct sparsert_tune_entry {
+    /* the options that make the plan again; vec and split_threshold are 0 for the LDS-staged row-walk kernel */
     int32_t kernel, vec, split_threshold, spec_mode, spec_rows, spec_tiles, spec_ksplit, spec_lanes, spec_swizzle, spec_vec;
     float microseconds;      /* per launch, back-to-back launches of this plan; negative if the candidate failed */
     float cold_microseconds; /* per launch when a cache-displacing fill runs before every launch (the fill's own

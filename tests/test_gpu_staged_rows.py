@@ -77,3 +77,18 @@ def test_rows_that_do_not_end_on_four_bytes_stay_on_the_plain_kernel(dtype):
     B = rng.integers(-2, 3, size=(K, N)).astype(dtype)
     want = ref.spmm(M, K, N, csr.row_ptr, csr.col_idx, csr.vals, B)[0]
     assert np.array_equal(run_spmm(csr, B, kernel=sp.KERNEL_ROWS)[0].astype(np.float64), want)
+
+
+def test_the_tuner_times_the_staged_kernel_beside_the_plain_one():
+    M, K, N = 2048, 256, 256
+    rng = np.random.default_rng(6)
+    csr = synth.csr_from_mask(np.ones((M, K), dtype=np.float32), rng.random((M, K)) < 0.5)
+    B = torch.from_numpy(rng.integers(-2, 3, size=(K, N)).astype(np.float32)).cuda()
+    C = torch.empty(M, N, device="cuda")
+    plan, entries = sp.tune(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, B.data_ptr(), C.data_ptr(),
+                            torch.cuda.current_stream().cuda_stream, kernel=sp.KERNEL_ROWS)
+    assert all(e["agrees"] == 1 for e in entries)
+    assert sorted({e["vec"] for e in entries}) == [0, 1, 2, 4] and sum(e["vec"] == 0 for e in entries) == 1
+    for e in entries:   # the fields of an entry make its plan again
+        again = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, kernel=sp.KERNEL_ROWS, vec=e["vec"], split_threshold=e["split_threshold"], host_only=True)
+        assert ("staged_rows_kernel" in again.kernel_name()) == (e["vec"] == 0)
