@@ -217,3 +217,47 @@ def test_largest_sweep_shape_on_sampled_rows(dtype):
         sub_ptr[i + 1] = sub_ptr[i] + (rp[r + 1] - rp[r])
     Cref, S = ref.spmm(len(rows), 4096, 4096, sub_ptr, np.concatenate(cols), np.concatenate(vals), case.B)
     check(got[rows], Cref, S, dtype)
+
+
+ROWS = dict(kernel=sp.KERNEL_ROWS)
+# The executors for which nothing is generated, on a product that the staged and the matrix-core kernel take by
+# themselves: storage type, options, kernel.
+FIXED = [(np.float32, dict(ROWS, vec=4), "rows_kernel"), (np.float32, dict(ROWS, vec=2, split_threshold=64), "rows_kernel"),
+         (np.float32, dict(ROWS, natural_order=True), "rows_kernel"), (np.float16, dict(ROWS, vec=4), "rows_kernel"),
+         (np.int8, dict(ROWS, vec=4), "rows_kernel"), (np.float32, ROWS, "staged_rows_kernel"),
+         (np.float16, ROWS, "staged_rows_kernel"), (np.int8, ROWS, "staged_rows_kernel"),
+         (np.float16, dict(), "mfma_kernel"), (np.int8, dict(), "mfma_kernel")]
+
+
+@pytest.mark.parametrize("dtype,opts,kernel", FIXED)
+def test_fixed_kernels_eagerly_from_saved_plans_and_from_a_graph(dtype, opts, kernel):
+    M, K, N = 2100, 333, 516
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(5)
+    csr = synth.csr_from_mask((rng.integers(1, 4, size=(M, K)) * rng.choice([-1, 1], size=(M, K))).astype(dtype), rng.random((M, K)) < 0.2)
+    operands = [rng.integers(-4, 5, size=(K, N)).astype(dtype) for _ in range(3)]
+    wants = [torch.from_numpy(_oracle(csr, B)[0]).to(dev) for B in operands]     # small integers: exact in any order
+    made = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, **opts)
+    plan = sp.load(made.save())
+    assert kernel in plan.kernel_name() and plan.kernel_name() == made.kernel_name()
+    assert ("staged" in kernel) == (plan.info()["staged_vec"] > 0)
+    Bd = torch.from_numpy(operands[0]).to(dev)
+    C = torch.empty(M, N, device=dev, dtype={np.float32: torch.float32, np.float16: torch.float16, np.int8: torch.int32}[dtype])
+    for p in (made, plan):
+        C.fill_(-7)
+        sp.spmm(p, Bd.data_ptr(), C.data_ptr(), torch.cuda.current_stream(dev).cuda_stream)
+        assert torch.equal(C.double(), wants[0])
+    made.destroy()
+    side = torch.cuda.Stream(dev)
+    side.wait_stream(torch.cuda.current_stream(dev))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        sp.spmm(plan, Bd.data_ptr(), C.data_ptr(), side.cuda_stream)
+    for rep in range(6):   # eager work on the graph's buffers between the replays
+        Bd.copy_(torch.from_numpy(operands[rep % 3]))
+        C.fill_(rep)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C.double(), wants[rep % 3]), rep
+    plan.destroy()
