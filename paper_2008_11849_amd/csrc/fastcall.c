@@ -1,8 +1,8 @@
 /*
  * The two executor calls of the Python binding as C functions.  A small product takes little longer
- * on the GPU than its launch does on the host, and marshalling four arguments through ctypes was a
- * quarter of that: sp.spmm on a 1024 x 512 x 49 layer took 2.9 us per call from Python against
- * 2.3 us from C.
+ * on the GPU than its launch does on the host, and marshalling four arguments through ctypes is a
+ * seventh of that: sp.spmm on a 1024 x 512 x 49 layer keeps the host for 2.95 us through ctypes and
+ * for 2.55 us through here, and takes 3.15 and 2.65 to 2.85 us per call back to back.
  *
  * Arguments that are not plain integers (or None) go to the ctypes functions handed over by
  * bind(), which accept everything ctypes does; so does the raising of errors.
