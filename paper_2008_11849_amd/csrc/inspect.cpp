@@ -127,14 +127,6 @@ int build_host_plan(const int32_t *row_ptr, const int32_t *col_idx, const void *
     h.batch = std::max(1, opt.batch);
     h.ldb = opt.ldb ? opt.ldb : N;
     h.ldc = opt.ldc ? opt.ldc : N;
-    // AUTO: the per-matrix generated kernel with the inspector's shape defaults where it can be
-    // built in a few seconds (the inspector is off the latency path, Section 2.3), else the
-    // row-walk kernel, whose inspector generates nothing.  Options that only the row-walk kernel
-    // reads (vec, split_threshold) select it as well.
-    if (opt.kernel != SPARSERT_KERNEL_AUTO) h.kernel = opt.kernel;
-    else h.kernel = (opt.vec == 0 && opt.split_threshold == 0 && ((h.nnz <= kAutoSpecNnz && spec_available()) || mfma_preferred(h, opt, vals) >= 0))
-                        ? SPARSERT_KERNEL_SPEC : SPARSERT_KERNEL_ROWS;
-    h.kernel_auto = opt.kernel == SPARSERT_KERNEL_AUTO;
     const int esz = h.elem_size();
 
     // Row histogram and the nnz-descending stable row order.
@@ -144,6 +136,14 @@ int build_host_plan(const int32_t *row_ptr, const int32_t *col_idx, const void *
         h.row_nnz[m] = row_ptr[m + 1] - row_ptr[m];
         ++h.hist[bin_of(h.row_nnz[m])];
     }
+    // AUTO: the per-matrix generated kernel with the inspector's shape defaults where it can be
+    // built in a few seconds (the inspector is off the latency path, Section 2.3), else the
+    // row-walk kernel, whose inspector generates nothing.  Options that only the row-walk kernel
+    // reads (vec, split_threshold) select it as well.
+    if (opt.kernel != SPARSERT_KERNEL_AUTO) h.kernel = opt.kernel;
+    else h.kernel = (opt.vec == 0 && opt.split_threshold == 0 && ((h.nnz <= kAutoSpecNnz && spec_available()) || mfma_preferred(h, opt, vals) >= 0))
+                        ? SPARSERT_KERNEL_SPEC : SPARSERT_KERNEL_ROWS;
+    h.kernel_auto = opt.kernel == SPARSERT_KERNEL_AUTO;
     h.perm.resize(M);
     std::iota(h.perm.begin(), h.perm.end(), 0);
     h.natural_order = opt.natural_order;

@@ -52,6 +52,12 @@ inline int mfma_find(int tm, int tn) {
     return -1;
 }
 
+// Each XCD takes an eighth of the tiles: along M if that leaves its L2 less of A and B to hold, else along N.
+inline bool mfma_m_fast(const MfmaConfig &c, int64_t M, int64_t K, int64_t N, int elem_size) {
+    const double wb = (double)((M + c.tm - 1) / c.tm) * c.tm * K * elem_size, bb = (double)K * N * elem_size;
+    return wb + bb / 8 < wb / 8 + bb;
+}
+
 // Time of an M x K x N product with this tile, from the constants above: they reproduce 122 measured shapes
 // (M 64 ... 4000, K 64 ... 3867, N 49 ... 4096, both storage types) to about 9 %, and the tile they choose is
 // within 1 % of the best one on average, 10 % at most.

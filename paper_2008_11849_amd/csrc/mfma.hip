@@ -364,9 +364,7 @@ int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err) {
     a.M = h.M; a.K = h.K; a.N = h.N; a.ldb = h.ldb; a.ldc = h.ldc;
     const int64_t m_tiles = (h.M + c.tm - 1) / c.tm, tasks = m_tiles * ((h.N + c.tn - 1) / c.tn);
     if (tasks > (1ll << 30)) { err = "too many workgroups"; return SPARSERT_EUNSUPPORTED; }
-    // Each XCD takes an eighth of the tiles: along M if that leaves its L2 less of A and B to hold, else along N.
-    const double wb = (double)m_tiles * c.tm * a.K * esz, bb = (double)h.K * h.N * esz;
-    a.m_fast = wb + bb / 8 < wb / 8 + bb;
+    a.m_fast = mfma_m_fast(c, h.M, h.K, h.N, esz);
     if (!mfma_fits(c, h.M, h.K, esz) || ((int64_t)(h.K - 1) * h.ldb + h.N) * esz >= (1ll << 31)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
     const void *kernel = nullptr;
     switch (sp.mfma_config * 2 + (h.dtype == SPARSERT_I8 ? 1 : 0)) {

@@ -1209,6 +1209,50 @@ static double generated_microseconds(const HostPlan &h) {
     return 2.33 + 3.45e-3 * std::ceil(h.M / rows) * h.K * touched * tiles / 256 + 2.69e-3 * (double)h.nnz * tiles / 1024;
 }
 
+// Second estimates of both, which look at more than the two above: a product that they put clearly on the generated
+// kernel's side stays there.  Fitted, 9 % and 15 % root mean square, to 840 half and int8 products (M, K and N up to 4096,
+// 80 % to 98 % zeros, uniform and skewed rows, odd sizes, batches), each timed with both kernels.
+// The matrix-core plan's time: the L2s fill up slower than the slabs are multiplied where the tiles that an XCD has in
+// hand share little; rows of C that do not begin on 8 bytes are stored in pieces, rows of B that do not begin on 4 bytes
+// are copied in pieces; and a large C leaves the caches.
+static double matrix_core_microseconds(const HostPlan &h, int tile, double first_estimate) {
+    static const double fit[2][5] = {{0.946, 0.326, 0.179, 0.0267, 0.223}, {0.952, 0.356, 0.0306, 0.0557, 0.0228}};   // half, int8
+    const double *f = fit[h.dtype == SPARSERT_I8];
+    const MfmaConfig &c = kMfmaConfigs[tile];
+    const int esz = h.elem_size(), osz = h.out_elem_size();
+    const int64_t m_tiles = ((int64_t)h.M + c.tm - 1) / c.tm, n_tiles = ((int64_t)h.N + c.tn - 1) / c.tn, wgs = m_tiles * n_tiles * h.batch;
+    const int64_t slab = (int64_t)c.steps * mfma_step(esz), slabs = (h.K + slab - 1) / slab;
+    const double rounds = wgs > 1024 ? wgs / 256.0 : (double)((wgs + 255) / 256), out_mb = 1e-6 * h.M * h.N * (double)h.batch * osz;
+    const bool m_fast = mfma_m_fast(c, h.M, h.K, h.N, esz);
+    const double at_once = (double)std::min<int64_t>(32, (m_tiles * n_tiles + 7) / 8);   // tiles of an XCD
+    const double fast = std::min((double)(m_fast ? m_tiles : n_tiles), at_once), slow = std::max(1.0, at_once / fast);
+    const double bytes = 64.0 * c.steps * (m_fast ? fast * c.tm + slow * c.tn : fast * c.tn + slow * c.tm);   // of a slab
+    const double fill = 8 * bytes / 4e6 - std::max(c.slab_shared * rounds, c.slab_alone) / rounds;            // all XCDs, 4 TB/s
+    double t = f[0] * first_estimate + f[1] * std::max(0.0, fill) * rounds * slabs + f[4] * std::max(0.0, out_mb - 16);
+    if ((int64_t)h.ldc * osz % 8) t += f[2] * out_mb;
+    if ((int64_t)h.ldb * esz % 4) t += f[3] * rounds * slabs;
+    return t;
+}
+
+// The generated kernel's time in its default shape: the fetches of B and the multiply-adds of the busiest compute unit, C,
+// one wave's chain of fetches, the longest row (one compute unit works it off), and the code a compute unit runs, which
+// the waves of a K split do not share.
+static double generated_shape_microseconds(const HostPlan &h, const sparsert_options &opt) {
+    static const double fit[2][7] = {{2.04, 0.696, 0.411, 0.293, 9.37, 1.74, 0.449}, {2.14, 0.459, 1.50, 0.157, 9.07, 1.99, 0.345}};   // half, int8
+    const double *f = fit[h.dtype == SPARSERT_I8];
+    SpecPlan sp;
+    Shape sh;
+    std::string err;
+    if (choose_launch_shape(h, opt, sp, sh, err)) return HUGE_VAL;   // no generated kernel
+    const double nonzeros = (double)h.nnz / sp.n_groups;   // of a block
+    const double touched = h.K * (1.0 - std::pow(1.0 - (double)h.nnz / ((double)h.M * h.K), (double)h.M / sp.n_groups));
+    const int tiles = sp.ksplit > 1 ? 1 : sp.tiles_per_wg;   // of a workgroup
+    const double wgs = (double)sp.n_groups * ((sp.n_tiles + tiles - 1) / tiles) * h.batch, rounds = wgs > 1024 ? wgs / 256 : std::ceil(wgs / 256);
+    const double longest = *std::max_element(h.row_nnz.begin(), h.row_nnz.end());
+    return f[0] + f[3] * 1e-6 * h.M * h.N * (double)h.batch * h.out_elem_size() +
+           1e-3 * (rounds * (f[1] * touched * tiles + f[2] * nonzeros * tiles / 4 + f[6] * (nonzeros + 1.5 * touched)) + f[4] * touched / sp.ksplit + f[5] * longest);
+}
+
 static bool mfma_applies(const HostPlan &h) {
     return h.dtype != SPARSERT_F32 && !h.conv && h.N >= 16;
 }
@@ -1231,7 +1275,12 @@ int mfma_preferred(const HostPlan &h, const sparsert_options &opt, const void *v
         return -1;
     double t = 0;
     const int tile = mfma_best_tile(h, &t);
-    return tile >= 0 && t < generated_microseconds(h) && all_finite(h, vals) ? tile : -1;
+    if (tile < 0 || t >= generated_microseconds(h)) return -1;
+    // 1.1: of the 562 of those products that the first estimates give to the matrix cores, those more than 5 % slower there than generated
+    // fall from 19 (1.57 times at most: half 1384 x 128 x 3489, batch 4, at 85 %, 30.0 against 19.1 us) to 8 (1.25), and
+    // two that were faster there by 7 % and 8 % are given up; a factor of 1 gives up ten, 1.32 times faster at most.
+    if (matrix_core_microseconds(h, tile, t) > 1.1 * generated_shape_microseconds(h, opt)) return -1;
+    return all_finite(h, vals) ? tile : -1;
 }
 
 // Matrix-core plan: which tile, and the name a kernel trace shows.

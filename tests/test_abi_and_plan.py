@@ -591,6 +591,19 @@ def test_which_products_go_to_the_matrix_cores(M, K, N, batch, dtype, sparsity, 
                 assert info["spec_mode"] != sp.SPEC_MFMA, opts
 
 
+@pytest.mark.parametrize("M,K,N,batch,dtype,sparsity", [
+    (4096, 1024, 3136, 1, np.float16, 0.98),     # 43.0 us on the matrix cores | 32.1 generated: the L2s cannot fill up as fast
+    (4096, 1024, 4096, 1, np.float16, 0.98),     # 55.9 | 43.6
+    (1384, 128, 3489, 4, np.float16, 0.852),     # 30.0 | 19.1: rows of C at odd addresses
+    (3769, 278, 1315, 4, np.float16, 0.898),     # 37.5 | 27.4
+    (512, 2960, 502, 1, np.int8, 0.973),         # 7.8 | 6.5
+])
+def test_products_that_the_matrix_cores_would_slow_down_stay_generated(M, K, N, batch, dtype, sparsity):
+    csr = synth.int8_csr(M, K, sparsity, 6) if dtype == np.int8 else synth.uniform_csr(M, K, sparsity, 6, dtype=dtype)
+    info = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, batch=batch).info()
+    assert info["kernel"] == sp.KERNEL_SPEC and info["spec_mode"] == sp.SPEC_DIRECT
+
+
 def test_convolutions_stay_off_the_matrix_cores():
     csr, _ = synth.conv_weights_csr(64, 64, 0.8, 5)
     info = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals.astype(np.float16), 64, 576, 784, host_only=True, conv=(64, 28, 28), batch=8).info()
