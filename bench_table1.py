@@ -316,6 +316,11 @@ def main():
         write_markdown(args.markdown, result, " ".join(["python3", "bench_table1.py"] + sys.argv[1:]))
 
 
+def executor(plan):
+    """1 = row-walk, 2 = generated, 3 = matrix cores (a kernel of the second family for which nothing is generated)."""
+    return 3 if plan["kernel"] == 2 and plan["spec_mode"] == 3 else plan["kernel"]
+
+
 def write_sweep_markdown(path, res, command):
     mask = res["workload"].split(",")[1].strip()
     oc = res["oracle_check"]
@@ -324,13 +329,14 @@ def write_sweep_markdown(path, res, command):
              f"{oc['timed_plans_checked']} timed plans, every element (64 sampled rows for the largest cases), "
              f"worst componentwise error {oc['worst_componentwise_error']:.2e} against {oc['tolerance']:g}.", "",
              f"command: `{command}` (one MI355X; `plan`: tune = sparsert_tune, auto = sparsert_inspect without options, gen = sparsert_inspect with kernel = generated and nothing else;",
-             f"sparse and dense both timed as {INNER} launches per HIP graph, 20 replays, HIP events; effective GFLOP/s = 2 nnz N / t).", "",
+             f"sparse and dense both timed as {INNER} launches per HIP graph, 20 replays, HIP events; effective GFLOP/s = 2 nnz N / t;",
+             "kernel: 1 = row-walk, 2 = generated, 3 = matrix cores; R = rows per code block, of 3 per workgroup).", "",
              "| M | K | N | sparsity | sparse us | dense us | speedup | effective GFLOP/s | kernel | R | KS | swizzle | plan | oracle err |",
              "|---|---|---|---|---|---|---|---|---|---|---|---|---|---|"]
     for r in res["problems"]:
         p = r["plan"]
         lines.append(f"| {r['M']} | {r['K']} | {r['N']} | {r['sparsity']:.2f} | {r['sparse_us']:.2f} | {r['dense_us']:.2f} | "
-                     f"{r['speedup']:.2f} | {r['gflops']:.0f} | {p['kernel']} | {p['spec_rows']} | {p['spec_ksplit']} | "
+                     f"{r['speedup']:.2f} | {r['gflops']:.0f} | {executor(p)} | {p['spec_rows']} | {p['spec_ksplit']} | "
                      f"{p['spec_swizzle']} | {'tune' if r['plan_from'] == 'sparsert_tune' else 'auto' if r['plan_from'] == 'inspect defaults' else 'gen'} | {r['oracle_componentwise_error']:.1e} |")
     with open(path, "w") as f:
         f.write("\n".join(lines) + "\n")
@@ -365,15 +371,16 @@ def write_markdown(path, res, command):
                   "The paper reports: unrolled over 10x faster than not unrolled, load balancing comparable in most cases,",
                   "a single fixed parameter choice about 2x slower.", ""]
     lines += ["Most SpMM problems finish in 2.5-3.3 us on the sparse path, about the floor of one kernel node in a",
-              "graph on this machine; the dense kernels take 4.2-9.5 us.  kernel: 1 = row-walk, 2 = generated;",
-              "R = rows per code block, KS = K split, W = waves per workgroup.", "",
+              "graph on this machine; the dense kernels take 4.2-9.5 us.  kernel: 1 = row-walk, 2 = generated,",
+              "3 = matrix cores; R = rows per code block, KS = K split, W = waves per workgroup (3: rows and 16-column tiles",
+              "of C per workgroup).", "",
               "| problem | shape | sparse us | dense us | speedup | paper (T4) | kernel | R | KS | W | row-walk us | input-order us | untuned us | fixed us |",
               "|---|---|---|---|---|---|---|---|---|---|---|---|---|---|"]
     for r in res["problems"]:
         shape = (f"{r['M']}x{r['K']}x{r['N']}" if "M" in r else f"conv {r['Cin']}->{r['Cout']} @ {r['image']}x{r['image']}")
         p = r["plan"]
         lines.append(f"| {r['tag']} | {shape} | {r['sparse_us']:.2f} | {r['dense_us']:.2f} | {r['speedup']:.2f} | "
-                     f"{r['paper_speedup_t4']} | {p['kernel']} | {p['spec_rows']} | {p['spec_ksplit']} | {p['spec_tiles']} | "
+                     f"{r['paper_speedup_t4']} | {executor(p)} | {p['spec_rows']} | {p['spec_ksplit']} | {p['spec_tiles']} | "
                      f"{r.get('rows_only_us', '-')} | {r.get('natural_order_us', '-')} | {r.get('untuned_us', '-')} | {r.get('fixed_us', '-')} |")
     with open(path, "w") as f:
         f.write("\n".join(lines) + "\n")
