@@ -684,6 +684,18 @@ def test_row_walk_options_keep_the_plain_kernel(opts):
     assert again.kernel_name() == plan.kernel_name() and again.save() == plan.save()
 
 
+@pytest.mark.parametrize("M,K,N,batch,dtype,sparsity", [
+    (2512, 680, 1664, 1, np.float16, 0.844),     # 59.7 us staged | 37.6 plain, eight halves per lane
+    (1960, 1680, 640, 4, np.float16, 0.894),     # 99.3 | 66.6
+    (1295, 2521, 1472, 4, np.int8, 0.936),       # 109.6 | 82.8
+    (1664, 169, 2768, 4, np.float32, 0.962),     # 35.6 | 27.0
+])
+def test_row_walk_plans_that_staging_would_slow_down_stay_plain(M, K, N, batch, dtype, sparsity):
+    csr = synth.int8_csr(M, K, sparsity, 6) if dtype == np.int8 else synth.uniform_csr(M, K, sparsity, 6, dtype=dtype)
+    info = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, kernel=sp.KERNEL_ROWS, batch=batch).info()
+    assert info["kernel"] == sp.KERNEL_ROWS and info["staged_vec"] == 0
+
+
 @pytest.mark.parametrize("opts,staged", [(dict(), True), (dict(vec=1), False), (dict(split_threshold=65), False), (dict(natural_order=True), False),
                                          (dict(kernel=sp.KERNEL_SPEC, spec_rows=64, spec_ksplit=1), False)])
 def test_plans_saved_in_the_previous_format_load(opts, staged):
