@@ -1279,7 +1279,8 @@ int mfma_preferred(const HostPlan &h, const sparsert_options &opt, const void *v
     // 1.1: of the 562 of those products that the first estimates give to the matrix cores, those more than 5 % slower there than generated
     // fall from 19 (1.57 times at most: half 1384 x 128 x 3489, batch 4, at 85 %, 30.0 against 19.1 us) to 8 (1.25), and
     // two that were faster there by 7 % and 8 % are given up; a factor of 1 gives up ten, 1.32 times faster at most.
-    if (matrix_core_microseconds(h, tile, t) > 1.1 * generated_shape_microseconds(h, opt)) return -1;
+    // (Where no code is generated the row-walk kernel would take over, which is further behind.)
+    if (h.nnz <= kAutoSpecNnz && spec_available() && matrix_core_microseconds(h, tile, t) > 1.1 * generated_shape_microseconds(h, opt)) return -1;
     return all_finite(h, vals) ? tile : -1;
 }
 

@@ -604,6 +604,16 @@ def test_products_that_the_matrix_cores_would_slow_down_stay_generated(M, K, N, 
     assert info["kernel"] == sp.KERNEL_SPEC and info["spec_mode"] == sp.SPEC_DIRECT
 
 
+def test_products_beyond_what_code_is_generated_for_stay_on_the_matrix_cores():
+    """Beyond 4194304 nonzeros the row-walk kernel would take over, which is further behind than generated code is ahead."""
+    M, K, per_row = 60000, 1024, 72
+    step = K // per_row
+    col = (np.arange(per_row)[None, :] * step + np.arange(M)[:, None] % step).astype(np.int32).ravel()
+    row_ptr = (np.arange(M + 1) * per_row).astype(np.int32)
+    info = sp.inspect(row_ptr, col, np.ones(col.size, dtype=np.float16), M, K, 4096, host_only=True).info()
+    assert info["kernel"] == sp.KERNEL_SPEC and info["spec_mode"] == sp.SPEC_MFMA
+
+
 def test_convolutions_stay_off_the_matrix_cores():
     csr, _ = synth.conv_weights_csr(64, 64, 0.8, 5)
     info = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals.astype(np.float16), 64, 576, 784, host_only=True, conv=(64, 28, 28), batch=8).info()
