@@ -185,7 +185,7 @@ int assemble(const std::string &text, std::vector<char> &code, std::string &err)
 // ---------------------------------------------------------------- assembly text
 struct Emitter {
     std::string s;
-    int64_t lines = 0;
+    int64_t lines = 0, bytes = 0;   // text lines; code bytes, as if every constant that may be one were a literal
     char buf[256];
     void line(const char *fmt, ...) __attribute__((format(printf, 2, 3))) {
         va_list ap;
@@ -195,6 +195,14 @@ struct Emitter {
         s.append(buf, (size_t)n);
         s.push_back('\n');
         ++lines;
+        bytes += code_bytes(fmt);
+    }
+    static int code_bytes(const char *fmt) {
+        static const char *const kShort[] = {"s_waitcnt", "s_mov_b64", "s_movk", "s_barrier", "s_endpgm", "s_nop", "v_mov", "v_cvt_f32_f16_e32", "v_cvt_f16_f32_e32", "%s v%d, v%d, v%d"};
+        if (fmt[0] != '\t' || fmt[1] == '.') return 0;   // labels and directives
+        for (const char *k : kShort)
+            if (!std::strncmp(fmt + 1, k, std::strlen(k))) return 4;
+        return 8;
     }
 };
 
@@ -931,9 +939,158 @@ static int plan_registers(const HostPlan &h, SpecPlan &sp, const Shape &sh, cons
     return SPARSERT_OK;
 }
 
+// Which workgroups share an L2.  Workgroup i of a launch runs on XCD i mod 8, and every XCD has an L2 of its own, which
+// pulls the code blocks and the column tiles of B that its workgroups touch.  In launch order (column tile, then code
+// block, then problem of the batch) that is an eighth of the tiles and all of the code if the tile count is a multiple of
+// 8, and everything otherwise: 1024 x 1024 at 90 % fetched 23 MB on 13 column tiles and 11 MB on 16, and took 11.4 and
+// 6.7 us.  So the prologue deals the workgroups anew: they stand in a row - part of the code blocks, column tile, block -
+// and every XCD takes an eighth of that row.
+struct Deal {
+    int64_t tiles = 0, blocks = 0, batch = 1;   // of the launch, in workgroups
+    int parts = 0, per_part = 0;                // 0: launch order
+    int64_t workgroups() const { return tiles * blocks * batch; }
+    // The workgroup in place `at` of the row: column tile (counted over the batch) and code block.
+    void work(int64_t at, int64_t &tile, int64_t &block) const {
+        const int64_t part = at / (tiles * batch * per_part), in = at - part * tiles * batch * per_part;
+        const int64_t here = std::min<int64_t>(per_part, blocks - part * per_part);
+        tile = in / here;
+        block = part * per_part + in % here;
+    }
+};
+
+// What a deal costs: the bytes that all L2s together pull, a tile (of one problem) and a code block counted once for every
+// XCD that touches them, and the most code that one XCD runs.  A byte of code weighs three times: its misses come one
+// after the other, B's overlap.  (Over 75 products and convolutions, each timed in launch order and in 1, 2, 4 and 8
+// parts: with a factor of 3 to 5 the choice is 1.058 times faster than launch order, with 1 or 8 1.053, the best of the five 1.079.)
+struct DealCost { double bytes = 0, weighed = 0, busiest = 0; };
+constexpr double kCodeByte = 3;
+
+static DealCost deal_cost(const Deal &d, double tile_bytes, const std::vector<int64_t> &block_bytes) {
+    const int64_t all = d.workgroups(), share = all / 8, more = all % 8, tiles = d.tiles * d.batch;
+    std::vector<uint8_t> has_tile(8 * (size_t)tiles, 0), has_block(8 * (size_t)d.blocks, 0);
+    double run[8] = {0};
+    for (int64_t i = 0; i < all; ++i) {
+        const int64_t x = i & 7;
+        int64_t tile, block;
+        if (d.parts) {
+            d.work(x * share + std::min(x, more) + (i >> 3), tile, block);
+        } else {
+            tile = i / (d.tiles * d.blocks) * d.tiles + i % d.tiles;
+            block = i / d.tiles % d.blocks;
+        }
+        has_tile[(size_t)(x * tiles + tile)] = has_block[(size_t)(x * d.blocks + block)] = 1;
+        run[x] += (double)block_bytes[(size_t)block];
+    }
+    DealCost c;
+    for (uint8_t v : has_tile) c.bytes += v * tile_bytes;
+    c.weighed = c.bytes;
+    for (size_t i = 0; i < has_block.size(); ++i) {
+        const double code = has_block[i] * (double)block_bytes[i % (size_t)d.blocks];
+        c.bytes += code;
+        c.weighed += kCodeByte * code;
+    }
+    c.busiest = *std::max_element(run, run + 8);
+    return c;
+}
+
+// The row that costs least and does not push an XCD's share towards the size of its L2 (4 MiB; 768 x 3072, 1024 columns, 95 %: 3.2 MB
+// in launch order, 4.0 MB in two parts, 13.5 and 13.6 us).  Launch order stays where the best row saves less than a tenth; where the code,
+// which every column tile of a part runs again, would not stay in an L2; and where blocks are so unequal (rows of very different
+// lengths, few to a block) that the long ones, which come first in launch order, should start first and on different XCDs:
+// half convolution of 64 x 1152, 18 x 18, skewed rows, one to a block: 4.9 us in launch order, 7.7 us in parts.
+static Deal choose_deal(const HostPlan &h, const SpecPlan &sp, const std::vector<int64_t> &code_block_bytes) {
+    Deal d;
+    const bool lds = sp.mode == SPARSERT_SPEC_LDS;
+    d.tiles = lds || sp.ksplit > 1 ? sp.n_tiles : (sp.n_tiles + sp.tiles_per_wg - 1) / sp.tiles_per_wg;
+    d.blocks = lds ? sp.n_blocks / sp.tiles_per_wg : sp.n_groups;
+    d.batch = h.batch;
+    std::vector<int64_t> block_bytes((size_t)d.blocks, 0);   // the code of a workgroup
+    int64_t code_bytes = 0;
+    for (size_t i = 0; i < code_block_bytes.size(); ++i) {
+        block_bytes[i * (size_t)d.blocks / code_block_bytes.size()] += code_block_bytes[i];
+        code_bytes += code_block_bytes[i];
+    }
+    if (d.workgroups() > (1 << 20) || code_bytes > (3 << 20)) return d;
+    if (*std::max_element(block_bytes.begin(), block_bytes.end()) * d.blocks > 2 * code_bytes) return d;
+    const int64_t columns = (h.N + d.tiles - 1) / d.tiles;   // of a workgroup
+    const double tile_bytes = (h.conv ? (double)h.Cin * (columns + 2 * (h.W + 1)) : (double)h.K * columns) * h.elem_size();
+    Deal best = d;
+    const DealCost now = deal_cost(d, tile_bytes, block_bytes);
+    double least = 0.9 * now.weighed;
+    for (d.parts = 1; d.parts <= 8; d.parts *= 2) {
+        d.per_part = (int)((d.blocks + d.parts - 1) / d.parts);
+        if (d.per_part * (d.parts - 1) >= d.blocks) continue;                                                   // a part without blocks
+        if (d.workgroups() * std::max<int64_t>(d.tiles * d.batch * d.per_part, d.tiles) >= (1ll << 32)) continue;   // (the prologue's divisions)
+        const DealCost c = deal_cost(d, tile_bytes, block_bytes);
+        if (c.bytes > now.bytes && c.bytes > 8 * 3.5e6) continue;
+        if (c.weighed < least && c.busiest < 1.1 * now.busiest) { least = c.weighed; best = d; }
+    }
+    return best;
+}
+
+// s[q] = s[x] / divisor by multiplication with ceil(2^32 / divisor): exact while x * divisor < 2^32.
+static void emit_quotient(Emitter &e, int q, int x, int64_t divisor) {
+    if (divisor > 1) e.line("\ts_mul_hi_u32 s%d, s%d, 0x%x", q, x, (unsigned)(((1ull << 32) + divisor - 1) / divisor));
+    else e.line("\ts_mov_b32 s%d, s%d", q, x);
+}
+
+// Workgroup id (s2, s3, s[kSgprImage]) -> the column tile, code block and problem that Deal::work gives this workgroup.
+static void emit_deal(Emitter &e, const Deal &d) {
+    const int at = kSgprOffRing, tmp = kSgprOffRing + 1, part = kSgprOffRing + 2, here = kSgprOffRing + 3;
+    const int64_t share = d.workgroups() / 8, more = d.workgroups() % 8, part_size = d.tiles * d.batch * d.per_part;
+    const int last = (int)(d.blocks - (int64_t)d.per_part * (d.parts - 1));   // blocks of the last part
+    if (d.batch > 1) {
+        e.line("\ts_mul_i32 s%d, s%d, 0x%x", tmp, kSgprImage, (unsigned)d.blocks);
+        e.line("\ts_add_u32 s3, s3, s%d", tmp);
+    }
+    e.line("\ts_mul_i32 s%d, s3, 0x%x", at, (unsigned)d.tiles);
+    e.line("\ts_add_u32 s%d, s%d, s2", at, at);                       // i
+    e.line("\ts_and_b32 s%d, s%d, 7", tmp, at);                       // XCD
+    e.line("\ts_lshr_b32 s%d, s%d, 3", at, at);
+    e.line("\ts_mul_i32 s%d, s%d, 0x%x", part, tmp, (unsigned)share);
+    e.line("\ts_min_u32 s%d, s%d, %d", tmp, tmp, (int)more);
+    e.line("\ts_add_u32 s%d, s%d, s%d", at, at, part);
+    e.line("\ts_add_u32 s%d, s%d, s%d", at, at, tmp);                 // place in the row
+    if (d.parts > 1) {
+        emit_quotient(e, part, at, part_size);
+        e.line("\ts_mul_i32 s%d, s%d, 0x%x", tmp, part, (unsigned)part_size);
+        e.line("\ts_sub_u32 s%d, s%d, s%d", at, at, tmp);
+    }
+    emit_quotient(e, 2, at, d.per_part);
+    e.line("\ts_mul_i32 s%d, s2, 0x%x", tmp, (unsigned)d.per_part);
+    if (d.parts > 1 && last != d.per_part) {
+        e.line("\ts_cmp_eq_u32 s%d, %d", part, d.parts - 1);
+        emit_quotient(e, here, at, last);
+        e.line("\ts_cselect_b32 s2, s%d, s2", here);
+        e.line("\ts_mul_i32 s%d, s2, 0x%x", here, (unsigned)last);
+        e.line("\ts_cselect_b32 s%d, s%d, s%d", tmp, here, tmp);
+    }
+    e.line("\ts_sub_u32 s3, s%d, s%d", at, tmp);
+    if (d.parts > 1) {
+        e.line("\ts_mul_i32 s%d, s%d, 0x%x", part, part, (unsigned)d.per_part);
+        e.line("\ts_add_u32 s3, s3, s%d", part);
+    }
+    if (d.batch > 1) {
+        emit_quotient(e, kSgprImage, 2, d.tiles);
+        e.line("\ts_mul_i32 s%d, s%d, 0x%x", tmp, kSgprImage, (unsigned)d.tiles);
+        e.line("\ts_sub_u32 s2, s2, s%d", tmp);
+    }
+}
+
+// Bytes between code blocks.  The waves of a launch run through their blocks side by side, and blocks that lie a
+// multiple of 8 KiB apart are then all at once on the same few channels of the memory behind the L2s: 1024 x 1024 at 90 %
+// on 832 columns has 8131 bytes from one block to the next and took 12.7 us; 8.8 us with any distance from 8.7 to 15.5 KB,
+// 12.1 us again at 16.4 KB (around multiples of 16 KiB the range is wider: 3072 x 768, 14.4 us, reaches 15.1 us at 17.9 KB).
+static int gap_between_blocks(int64_t code_bytes, int64_t blocks) {
+    constexpr int64_t kPeriod = 8192, kNearest = 2048;
+    const int64_t distance = code_bytes / std::max<int64_t>(1, blocks);
+    const int64_t off = (distance + kNearest) % kPeriod;   // 2 * kNearest and more: far enough from the next multiple on either side
+    return distance + kNearest < kPeriod || off >= 2 * kNearest ? 0 : (int)(2 * kNearest - off + 3) / 4 * 4;
+}
+
 // Stage 4a, emission of everything before the blocks: directives, the prologue that turns the
 // workgroup and lane ids into a block, a column and two buffer descriptors, and the jump table.
-static void emit_prologue(Gen &gen, Emitter &e, const Shape &sh, const Extents &ex, int prefetch_lines) {
+static void emit_prologue(Gen &gen, Emitter &e, const Shape &sh, const Extents &ex, const Deal &deal, int prefetch_lines) {
     const HostPlan &h = gen.h;
     SpecPlan &sp = gen.sp;
     const bool lds = sh.lds;
@@ -954,6 +1111,7 @@ static void emit_prologue(Gen &gen, Emitter &e, const Shape &sh, const Extents &
     const bool images = h.batch > 1;
     if (images) e.line("\ts_mov_b32 s%d, s4", kSgprImage);   // s4 is about to receive a kernel argument
     e.line("\ts_load_dwordx4 s[%d:%d], s[0:1], 0x0", kSgprB, kSgprC + 1);
+    if (deal.parts) emit_deal(e, deal);
     e.line("\tv_lshrrev_b32_e32 v%d, 6, v0", kVgprT1);
     e.line("\tv_and_b32_e32 v%d, 63, v0", kVgprOff);
     e.line("\ts_nop 1");
@@ -1324,21 +1482,32 @@ int build_spec_plan(HostPlan &h, const sparsert_options &opt, std::string &err) 
     Emitter &e = gen.e;
     sp.group_columns.assign(sp.n_blocks, 0);
     int64_t longest = 0;   // instructions of the longest block
+    std::vector<size_t> gaps;            // where the text says how far apart the blocks are
+    std::vector<int64_t> block_bytes;
     for (int g = 0; g < sp.n_blocks; ++g) {
-        const int64_t before = e.lines;
+        const int64_t before = e.lines, bytes_before = e.bytes;
+        gaps.push_back(e.s.size());
+        e.line("\t.space %8d", 0);   // (filled in below)
         e.line("\t.p2align 2");
         e.line(".Lg%d:", g);
         sp.group_columns[g] = sh.lds ? gen.block_lds(members[g], g % sh.W, sh.W)
                                      : gen.block_direct(members[g / sh.KS], g % sh.KS, sh.KS);
         longest = std::max(longest, e.lines - before);
+        block_bytes.push_back(e.bytes - bytes_before);
     }
+    if (const int gap = gap_between_blocks(e.bytes, sp.n_blocks)) {
+        char text[24];
+        const int n = snprintf(text, sizeof(text), "\t.space %8d", gap);
+        for (size_t at : gaps) e.s.replace(at, (size_t)n, text);
+    }
+    const Deal deal = choose_deal(h, sp, block_bytes);
     emit_kernel_descriptor(gen, sh);
     // an instruction is at most 8 bytes; 64 lanes touch one 128-byte line each per prefetch
     // instruction, at most 32 of them (their offsets must fit the load's immediate field)
     const int prefetch_lines = !opt.spec_prefetch ? 0 : (int)std::min<int64_t>(32, (longest * 8 + 64 * 128 - 1) / (64 * 128));
     sp.prefetch_lines = prefetch_lines;
     Emitter head;
-    emit_prologue(gen, head, sh, ex, prefetch_lines);
+    emit_prologue(gen, head, sh, ex, deal, prefetch_lines);
     e.s.insert(0, head.s);
 
     if (const char *dump = getenv("SPARSERT_DUMP_ASM")) {

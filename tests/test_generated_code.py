@@ -161,3 +161,67 @@ def test_random_generated_kernels_are_clean(M, K, N, sparsity, rows, ks, mode, d
         return
     problems, _ = asm_check.check(text, info, *ESZ[np.dtype(dtype)])
     assert not problems, (opts, problems[:5])
+
+
+def _deal(text):
+    """The prologue from the load of the kernel's arguments on."""
+    body = [l.strip() for l in text[:text.index("\n.Ltable:")].splitlines()]
+    return body[next(i for i, l in enumerate(body) if l.startswith("s_load_dwordx4 s[4:7]")) + 1:]
+
+
+def _dealt(prologue, x, y, z):
+    """(column tile, code block, problem) that the prologue computes for a workgroup of the launch."""
+    s, scc = {"s2": x, "s3": y, "s52": z}, False
+    value = lambda tok: s[tok] if tok in s else int(tok, 0)
+    ops = {"s_and_b32": lambda a, b: a & b, "s_lshr_b32": lambda a, b: a >> b, "s_mul_i32": lambda a, b: a * b & 0xFFFFFFFF, "s_min_u32": min,
+           "s_mul_hi_u32": lambda a, b: a * b >> 32, "s_add_u32": lambda a, b: a + b & 0xFFFFFFFF, "s_sub_u32": lambda a, b: a - b & 0xFFFFFFFF}
+    for l in prologue:
+        op, _, rest = l.partition(" ")
+        args = [a.strip() for a in rest.split(",")]
+        if op in ops:
+            s[args[0]] = ops[op](value(args[1]), value(args[2]))
+        elif op == "s_mov_b32":
+            s[args[0]] = value(args[1])
+        elif op == "s_cmp_eq_u32":
+            scc = value(args[0]) == value(args[1])
+        elif op == "s_cselect_b32":
+            s[args[0]] = value(args[1] if scc else args[2])
+        else:
+            assert op.startswith("v_"), l
+            return s["s2"], s["s3"], s["s52"]
+
+
+@pytest.mark.parametrize("M,K,N,batch,mask,opts,moved", [
+    (1024, 1024, 771, 1, "uniform", dict(), True),                                         # 13 column tiles; blocks in parts
+    (1024, 2000, 320, 1, "uniform", dict(spec_rows=48, spec_ksplit=2), True),              # the last part has fewer blocks
+    (1000, 2000, 30, 5, "uniform", dict(spec_rows=24, spec_ksplit=4), True),               # one tile, five problems
+    (640, 2000, 577, 1, "uniform", dict(spec_rows=32, spec_tiles=2), True),                # workgroups of two adjacent tiles
+    (400, 2000, 700, 3, "uniform", dict(spec_mode=sp.SPEC_LDS, spec_rows=12, spec_tiles=4), True),
+    (64, 4096, 330, 1, "uniform", dict(spec_rows=64, spec_ksplit=8), False),               # one block: launch order costs the least
+    (512, 512, 771, 1, "skewed", dict(spec_rows=1, spec_ksplit=4), False),                 # long rows first
+])
+def test_every_tile_and_block_is_dealt_to_one_workgroup(M, K, N, batch, mask, opts, moved, tmp_path):
+    csr = synth.uniform_csr(M, K, 0.9, 4) if mask == "uniform" else synth.skewed_csr(M, K, 0.9, 4)
+    text, info = _generated(csr, N, tmp_path, batch=batch, **opts)
+    lds, n_tiles = info["spec_mode"] == sp.SPEC_LDS, -(-N // info["spec_lanes"])
+    tiles = n_tiles if lds or info["spec_ksplit"] > 1 else -(-n_tiles // info["spec_tiles"])
+    blocks = -(-info["spec_groups"] // info["spec_tiles"]) if lds else info["spec_groups"]
+    ids = [(x, y, z) for z in range(batch) for y in range(blocks) for x in range(tiles)]
+    prologue = _deal(text)
+    got = [_dealt(prologue, *i) for i in ids]
+    assert sorted(got) == sorted(ids)
+    assert (got != ids) == moved
+    if moved:   # what an XCD touches, a byte of code counted three times
+        touched = lambda work: sum(len({(t, z) for t, _, z in work[x::8]}) * K * info["spec_lanes"] * 4 + 3 * len({b for _, b, _ in work[x::8]}) * info["spec_code_bytes"] / blocks
+                                   for x in range(8))
+        assert touched(got) < 0.95 * touched(ids)
+
+
+@pytest.mark.parametrize("rows,gap", [(54, True), (36, False), (100, False)])
+def test_code_blocks_do_not_lie_a_multiple_of_8_kib_apart(rows, gap, tmp_path):
+    csr = synth.uniform_csr(1024, 1024, 0.9, 4)
+    text, info = _generated(csr, 832, tmp_path, spec_rows=rows, spec_ksplit=8)
+    spaces = {l.strip() for l in text.splitlines() if ".space" in l}
+    assert len(spaces) == 1 and (int(spaces.pop().split()[1]) > 0) == gap
+    between = info["spec_code_bytes"] / (8 * info["spec_groups"])
+    assert 1900 < between % 8192 < 6300
