@@ -1,6 +1,7 @@
 // Tile shapes of the matrix-core executor (mfma.hip): what the inspector chooses from and the
 // launch looks up.  Host code only.
 #pragma once
+#include <algorithm>
 #include <cstdint>
 
 namespace sparsert {
@@ -56,6 +57,31 @@ inline int mfma_find(int tm, int tn) {
 inline bool mfma_m_fast(const MfmaConfig &c, int64_t M, int64_t K, int64_t N, int elem_size) {
     const double wb = (double)((M + c.tm - 1) / c.tm) * c.tm * K * elem_size, bb = (double)K * N * elem_size;
     return wb + bb / 8 < wb / 8 + bb;
+}
+
+// Tiles along M that stand together in the order of the tasks, of which every XCD takes an eighth: the number for which
+// the eight L2s together pull the least of A and B (768 x 3072 x 1024 int8 in tiles of 64 x 64, a column of all twelve:
+// 22 MB; six: 15.8 MB).
+inline int mfma_rows_per_part(const MfmaConfig &c, int64_t M, int64_t K, int64_t N, int elem_size) {
+    const int64_t m_tiles = (M + c.tm - 1) / c.tm, n_tiles = (N + c.tn - 1) / c.tn, tasks = m_tiles * n_tiles, share = (tasks + 7) / 8;
+    int64_t best = mfma_m_fast(c, M, K, N, elem_size) ? m_tiles : 1;
+    double least = 0;
+    for (int64_t parts = 0; parts <= 16 && parts <= m_tiles && tasks <= 65536; ++parts) {
+        const int64_t per = parts ? (m_tiles + parts - 1) / parts : best;   // first the better one of the two that end at 1
+        double rows = 0, columns = 0;   // tiles pulled
+        for (int64_t x = 0; x * share < tasks; ++x) {
+            int64_t m_lo = m_tiles, m_hi = -1, n_lo = n_tiles, n_hi = -1;
+            for (int64_t t = x * share; t < std::min(tasks, (x + 1) * share); ++t) {
+                const int64_t part = t / (per * n_tiles), in = t - part * per * n_tiles, here = std::min(per, m_tiles - part * per);
+                const int64_t n = in / here, m = part * per + in % here;
+                m_lo = std::min(m_lo, m); m_hi = std::max(m_hi, m); n_lo = std::min(n_lo, n); n_hi = std::max(n_hi, n);
+            }
+            rows += (double)(m_hi - m_lo + 1); columns += (double)(n_hi - n_lo + 1);
+        }
+        const double bytes = (rows * c.tm + columns * c.tn) * (double)K * elem_size;
+        if (parts == 0 || bytes < 0.95 * least) { least = bytes; best = per; }
+    }
+    return (int)best;
 }
 
 // Time of an M x K x N product with this tile, from the constants above: they reproduce 122 measured shapes

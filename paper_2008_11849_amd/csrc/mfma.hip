@@ -28,8 +28,11 @@
 // LDS reads alone need 0.27 us per slab, matrix instructions alone 0.21 us, both 0.36 us, and 0.5 us with
 // the copies, which also write LDS.  Eight waves instead of four were worth 1.1x (a wave issues an instruction
 // every four clocks at best, and a slab is a hundred of them), addresses kept in the descriptor's scalar
-// offset instead of vector adds 1.15x.  1024 x 1024 x 4096 half at 80 %: 45.2 us generated, 12.5 us here;
-// 3072 x 768 x 1024 half at 95 %: 11.3 and 9.3 us; 768 x 3072 x 1024 int8 at 95 %: 13.9 and 9.6 us.
+// offset instead of vector adds 1.15x.  1024 x 1024 x 4096 half at 80 %: 45.2 us generated, 11.5 us here;
+// 3072 x 768 x 1024 half at 95 %: 11.3 and 8.6 us; 768 x 3072 x 1024 int8 at 95 %: 13.9 and 9.5 us.  Measured slower: a ring of
+// eight slabs, or K split over two or four groups of waves with a ring each (before a wave multiplies it issues its part of
+// the ring: 128 KiB take a compute unit 1 us; 768 x 1574 x 172 int8: 3.9 -> 4.9 us), and two slabs before the first turn with the
+// rest of the ring issued in the first two (0.2 us faster on repeated operands, 0.1 to 0.3 us slower on new ones).
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
@@ -63,8 +66,12 @@ struct MfmaArgs {
     const int32_t *p_row_ptr, *inv_perm; // the nonzero stream, for tiles with non-finite sums
     const uint2 *stream;
     int32_t M, K, N, ldb, ldc;
-    int32_t m_fast;                      // consecutive tasks: along M
+    int32_t per_part;                    // tiles along M of a part (mfma_rows_per_part)
+    uint32_t part_magic, here_magic, last_magic;   // for the divisions by a part's tiles, by per_part and by what is left for the last part
 };
+
+// x / d for d whose magic is ceil(2^32 / d), exact while x * d < 2^32; 0: d is 1 or the product too large.
+__device__ __forceinline__ uint32_t quotient(uint32_t x, uint32_t d, uint32_t magic) { return magic ? __umulhi(x, magic) : x / d; }
 
 template <int DT> struct Kind;           // 0: half, 1: int8
 template <> struct Kind<0> {
@@ -140,14 +147,18 @@ __global__ __launch_bounds__(WM *WN *kWave, mfma_waves_per_simd(WM *MF * 16, WN 
     __shared__ __align__(1024) char lds[STAGES * STAGE];
 
     // All arguments in one go: left alone they arrive in four batches, each waited for.
-    asm volatile("" ::"s"(a.weights), "s"(a.in), "s"(a.out), "s"(a.M), "s"(a.K), "s"(a.N), "s"(a.ldb), "s"(a.ldc), "s"(a.m_fast));
+    asm volatile("" ::"s"(a.weights), "s"(a.in), "s"(a.out), "s"(a.M), "s"(a.K), "s"(a.N), "s"(a.ldb), "s"(a.ldc), "s"(a.per_part), "s"(a.part_magic), "s"(a.here_magic), "s"(a.last_magic));
     const int m_tiles = (a.M + TM - 1) / TM, n_tiles = (a.N + TN - 1) / TN, tasks = m_tiles * n_tiles;
     const int n_slabs = (a.K + SLAB - 1) / SLAB, k_steps = n_slabs * STEPS;
     const int task = (int)(blockIdx.x & 7) * ((tasks + 7) >> 3) + (int)(blockIdx.x >> 3);
     if (task >= tasks) return;
-    const uint32_t fast_tiles = a.m_fast ? m_tiles : n_tiles;
-    const int slow = (int)((uint32_t)task / fast_tiles), fast = task - slow * (int)fast_tiles;
-    const int tile_m = a.m_fast ? fast : slow, tile_n = a.m_fast ? slow : fast;
+    // Parts of per_part tiles along M one after the other, in a part column tile by column tile: an XCD's eighth of the
+    // tasks is then a block of tiles in both directions.
+    const uint32_t part = quotient(task, (uint32_t)(a.per_part * n_tiles), a.part_magic), in_part = (uint32_t)task - part * (uint32_t)(a.per_part * n_tiles);
+    const uint32_t left = (uint32_t)m_tiles - part * (uint32_t)a.per_part;
+    const uint32_t here = left < (uint32_t)a.per_part ? left : (uint32_t)a.per_part;
+    const int tile_n = (int)quotient(in_part, here, here == (uint32_t)a.per_part ? a.here_magic : a.last_magic);
+    const int tile_m = (int)(part * (uint32_t)a.per_part + in_part - (uint32_t)tile_n * here);
     // of one problem: reads and writes stay inside
     const int in_bytes = ((a.K - 1) * a.ldb + a.N) * ESZ, weight_bytes = m_tiles * (TM / 16) * k_steps * 1024;
     const int out_bytes = (int)(((uint32_t)(a.M - 1) * (uint32_t)a.ldc + (uint32_t)a.N) * (uint32_t)sizeof(out_t));
@@ -293,23 +304,77 @@ __global__ __launch_bounds__(WM *WN *kWave, mfma_waves_per_simd(WM *MF * 16, WN 
 
     // ---- results.  Stores outside C (rows past M, chunks past N) are refused by the descriptor.
     const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, out_bytes, 0x00020000);
-    float probe = 0.0f;   // becomes NaN with the first sum that is not finite
-    int row_off[MF], col_off[NF];
+    const uint32_t row_bytes = (uint32_t)a.ldc * (uint32_t)sizeof(out_t);
+    const bool lines = row_bytes % 128 == 0 && TN * sizeof(out_t) % 128 == 0;   // whole ones are written
+    // Through LDS, so that a wave stores whole rows of the tile: straight from the accumulators it would be 16 rows of 32
+    // (int8: 64) bytes each.  Int8 without whole lines stays with that: 3784 x 182 x 200, batch 4: 6.4 against 6.6 us.
+    // 3072 x 768 x 1024 half: 9.2 -> 8.5 us; 1472 x 168 x 2592 int8 7.8 -> 6.3 us (the hint included).
+    bool finite = true;   // all sums of the workgroup
+    if (DT == 0 || lines) {
+        constexpr int PITCH = TN * (int)sizeof(out_t) + 16;   // rows 16 bytes further apart: fewer bank conflicts
+        constexpr int FLAGS = TM * PITCH;
+        static_assert(FLAGS + WAVES * 4 <= STAGES * STAGE, "the tile's results fit the slabs");
+        float probe = 0.0f;   // becomes NaN with the first sum that is not finite
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();   // every wave has read the last slab, and no copy is on its way
+        asm volatile("" ::: "memory");
+        char *mine = lds + (wm * MF * 16 + lg) * PITCH + (wn * NF * 16 + 4 * g) * (int)sizeof(out_t);
 #pragma unroll
-    for (int i = 0; i < MF; ++i) row_off[i] = (int)((uint32_t)(m0 + i * 16 + lg) * (uint32_t)a.ldc * (uint32_t)sizeof(out_t));
+        for (int i = 0; i < MF; ++i)
 #pragma unroll
-    for (int j = 0; j < NF; ++j) col_off[j] = column(n0 + j * 16 + 4 * g) * (int)sizeof(out_t);
+            for (int j = 0; j < NF; ++j) {
+                const acc_t v = acc[i][j];
+                char *to = mine + i * 16 * PITCH + j * 16 * (int)sizeof(out_t);
+                if constexpr (DT == 0) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) probe = __builtin_fmaf(v[r], 0.0f, probe);
+                    *reinterpret_cast<half4 *>(to) = half4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};   // one rounding to nearest even
+                } else {
+                    *reinterpret_cast<acc_t *>(to) = v;
+                }
+            }
+        if constexpr (DT == 0) *reinterpret_cast<int *>(lds + FLAGS + wave * 4) = __any(probe != probe);
+        __syncthreads();
+        if constexpr (DT == 0) {
+            int flags = 0;
+#pragma unroll
+            for (int w = 0; w < WM * WN; ++w) flags |= *reinterpret_cast<const int *>(lds + FLAGS + w * 4);
+            finite = __builtin_amdgcn_readfirstlane(flags) == 0;
+        }
+        if (__builtin_expect(finite, 1)) {
+            constexpr int CHUNKS = TN * (int)sizeof(out_t) / 16, ROWS = WAVES * kWave / CHUNKS;   // 16-byte pieces of a row; rows per pass
+            static_assert((TM + ROWS - 1) / ROWS * ROWS * PITCH <= STAGES * STAGE, "the last pass reads inside the slabs");
+            const int n = n_tile0 + tid % CHUNKS * (16 / (int)sizeof(out_t)), r0 = tid / CHUNKS;
+            uint32_t off = (uint32_t)(tile_m * TM + r0) * row_bytes + (uint32_t)column(n) * (uint32_t)sizeof(out_t);
+            const bool columns = (n & -EPC) < a.N;
+            const char *from = lds + r0 * PITCH + tid % CHUNKS * 16;
+            auto store = [&](auto policy) {
+#pragma unroll
+                for (int r = 0; r < TM; r += ROWS, off += ROWS * row_bytes) {
+                    const int4v v = *reinterpret_cast<const int4v *>(from + r * PITCH);
+                    const bool stored = columns & (tile_m * TM + r + r0 < a.M) & (TM % ROWS == 0 || r + r0 < TM);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, rout, stored ? (int)off : kRefused, 0, policy);
+                }
+            };
+            // C is not read again: whole 128-byte lines need not stay in the L2 (the same half product: 8.96 -> 8.71 us).
+            if (lines) store(std::integral_constant<int, 2>());
+            else store(std::integral_constant<int, 0>());
+            return;
+        }
+    }
+    float probe = 0.0f;
 #pragma unroll
     for (int i = 0; i < MF; ++i)
 #pragma unroll
         for (int j = 0; j < NF; ++j) {
             const acc_t v = acc[i][j];
-            const bool mine = (m0 + i * 16 + lg < a.M) & (((n0 + j * 16 + 4 * g) & -EPC) < a.N);
-            const int off = mine ? row_off[i] + col_off[j] : kRefused;
+            const int row = m0 + i * 16 + lg, n = n0 + j * 16 + 4 * g;
+            const bool mine = (row < a.M) & ((n & -EPC) < a.N);
+            const int off = mine ? (int)((uint32_t)row * row_bytes + (uint32_t)column(n) * (uint32_t)sizeof(out_t)) : kRefused;
             if constexpr (DT == 0) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) probe = __builtin_fmaf(v[r], 0.0f, probe);
-                const half4 h = {(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};   // one rounding to nearest even
+                const half4 h = {(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
                 int2v b;
                 __builtin_memcpy(&b, &h, 8);
                 __builtin_amdgcn_raw_buffer_store_b64(b, rout, off, 0, 0);
@@ -317,8 +382,9 @@ __global__ __launch_bounds__(WM *WN *kWave, mfma_waves_per_simd(WM *MF * 16, WN 
                 __builtin_amdgcn_raw_buffer_store_b128(v, rout, off, 0, 0);
             }
         }
+    // A sum that is not finite: columns to redo.
     if constexpr (DT == 0) {
-        if (__builtin_expect(__any(probe != probe), 0)) {
+        if (__any(probe != probe)) {
             wait_loads<0>();   // the sums are out before what replaces them
             // The columns to redo, as bits: those of this wave in which any row's sum is not finite.  A column that two
             // waves store is in both or in neither, and with it every result is a function of its own operands alone.
@@ -364,7 +430,10 @@ int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err) {
     a.M = h.M; a.K = h.K; a.N = h.N; a.ldb = h.ldb; a.ldc = h.ldc;
     const int64_t m_tiles = (h.M + c.tm - 1) / c.tm, tasks = m_tiles * ((h.N + c.tn - 1) / c.tn);
     if (tasks > (1ll << 30)) { err = "too many workgroups"; return SPARSERT_EUNSUPPORTED; }
-    a.m_fast = mfma_m_fast(c, h.M, h.K, h.N, esz);
+    const int64_t n_tiles = (h.N + c.tn - 1) / c.tn;
+    a.per_part = mfma_rows_per_part(c, h.M, h.K, h.N, esz);
+    auto magic = [&](int64_t d) { return d > 1 && tasks * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; };
+    a.part_magic = magic(a.per_part * n_tiles); a.here_magic = magic(a.per_part); a.last_magic = magic(m_tiles % a.per_part);
     if (!mfma_fits(c, h.M, h.K, esz) || ((int64_t)(h.K - 1) * h.ldb + h.N) * esz >= (1ll << 31)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }
     const void *kernel = nullptr;
     switch (sp.mfma_config * 2 + (h.dtype == SPARSERT_I8 ? 1 : 0)) {

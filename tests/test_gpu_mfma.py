@@ -44,6 +44,20 @@ def test_spmm_at_the_edges_of_its_tiles(tile, dtype):
         assert pad_ok and np.array_equal(got.astype(np.float64), np.stack([want, -want])), (M, K, N)
 
 
+@pytest.mark.parametrize("dtype", [np.float16, np.int8])
+@pytest.mark.parametrize("tile", [(32, 2), (64, 4), (96, 8)])
+def test_many_tiles_are_dealt_once_each(tile, dtype):
+    """Tile counts that split unevenly over parts and XCDs; rows of C in whole 128-byte lines and not; every element is
+    written (the result starts as NaN or a pattern) and by the right tile."""
+    rng = np.random.default_rng(5)
+    for M, K, N in ((tile[0] * 13 + 5, 40, 16 * tile[1] * 11 + 7), (tile[0] * 17, 300, 48), (70, 300, 16 * tile[1] * 17), (tile[0] * 9, 64, 16 * tile[1] * 8)):
+        csr = _ints(rng, M, K, 0.2, dtype)
+        B = rng.integers(-4, 5, size=(K, N)).astype(dtype)
+        want = ref.spmm(M, K, N, csr.row_ptr, csr.col_idx, csr.vals, B)[0]
+        got, pad_ok, _ = run_spmm_strided(csr, np.stack([B, -B]), N, N + 32, **_opts(tile))
+        assert pad_ok and np.array_equal(got.astype(np.float64), np.stack([want, -want])), (M, K, N)
+
+
 @pytest.mark.parametrize("tile", [TILES[0], TILES[5]])
 def test_half_values_subnormals_and_non_finite_operands(tile):
     case = synth.config("c2", np.float16)
