@@ -570,24 +570,25 @@ struct Gen {
         const int buf_bytes = kChunkRows * 256;
         int ring_pos = 0;
         zero_accs(rows.size());
-        // Staging runs two chunks ahead of the compute: chunk c travels through register set
-        // c % 2, so a fetch has two compute phases to arrive before it is copied into LDS.
+        // Staging runs ahead of the compute: chunk c travels through register set c % 2, so a fetch
+        // has the time of two chunks to arrive before it is copied into LDS.
         const int quads_per_wave = (quads_per_chunk + W - 1) / W;
-        std::vector<int> n_loads(n_chunks + 3, 0);
-        auto stage_loads = [&](int c) {
-            if (c >= n_chunks) return;
-            int t = 0, n = 0;
+        auto stage_rows = [&](int c) {   // (row of B, register) of every fetch of this wave for chunk c
+            std::vector<std::pair<int, int>> rows;
+            if (c >= n_chunks) return rows;
+            int t = 0;
             for (int q = w; q < quads_per_chunk; q += W, ++t)
-                for (int j = 0; j < 4; ++j) {
-                    const int k = c * kChunkRows + 4 * q + j;
-                    if (k < K) { load_b_row(k, vgpr_stage0 + (c & 1) * 4 * quads_per_wave + 4 * t + j, ring_pos++); ++n; }
-                }
-            n_loads[c] = n;
+                for (int j = 0; j < 4; ++j)
+                    if (c * kChunkRows + 4 * q + j < K) rows.push_back({c * kChunkRows + 4 * q + j, vgpr_stage0 + (c & 1) * 4 * quads_per_wave + 4 * t + j});
+            return rows;
+        };
+        auto stage_loads = [&](int c) {
+            for (auto &r : stage_rows(c)) load_b_row(r.first, r.second, ring_pos++);
         };
         auto stage_write = [&](int c) {
             // fetches return in order: chunk c has arrived once only chunk c+1's are outstanding
-            e.line("\ts_waitcnt vmcnt(%d)", c + 1 < n_chunks ? n_loads[c + 1] : 0);
-            int t = 0;
+            e.line("\ts_waitcnt vmcnt(%d)", (int)stage_rows(c + 1).size());
+            int t = 0, n = 0;
             for (int q = w; q < quads_per_chunk; q += W, ++t) {
                 if (c * kChunkRows + 4 * q >= K) break;
                 const int v = vgpr_stage0 + (c & 1) * 4 * quads_per_wave + 4 * t;
@@ -596,7 +597,84 @@ struct Gen {
                 if (half)
                     for (int j = 0; j < 4 && c * kChunkRows + 4 * q + j < K; ++j) e.line("\tv_cvt_f32_f16_e32 v%d, v%d", v + j, v + j);
                 e.line("\tds_write_b128 v%d, v[%d:%d] offset:%d", kVgprLds, v, v + 3, (c & 1) * buf_bytes + q * 1024);
+                ++n;
             }
+            return n;
+        };
+        // The quads that hold a nonzero column of the group, over all chunks.
+        struct Quad { int chunk, q; std::vector<Term> terms[4]; bool need[4] = {false, false, false, false}; int last_read = -1; };
+        std::vector<Quad> quads;
+        for (auto &col : cols) {
+            const int c = col.first / kChunkRows, q = col.first % kChunkRows / 4, j = col.first % 4;
+            if (quads.empty() || quads.back().chunk != c || quads.back().q != q) { quads.push_back(Quad()); quads.back().chunk = c; quads.back().q = q; }
+            quads.back().need[j] = true;
+            quads.back().terms[j] = std::move(col.second);
+        }
+        const int nq = (int)quads.size();
+        int issued = 0;   // LDS instructions
+        auto issue_reads = [&](int i) {
+            Quad &Q = quads[i];
+            const int v0 = vgpr_ring0 + 4 * (i % D), off = (Q.chunk & 1) * buf_bytes + Q.q * 1024;
+            const int cnt = Q.need[0] + Q.need[1] + Q.need[2] + Q.need[3];
+            if (cnt >= 3) {
+                e.line("\tds_read_b128 v[%d:%d], v%d offset:%d", v0, v0 + 3, kVgprLds, off);
+                ++issued;
+            } else {
+                for (int j = 0; j < 4; j += 2) {
+                    if (Q.need[j] && Q.need[j + 1]) {
+                        e.line("\tds_read_b64 v[%d:%d], v%d offset:%d", v0 + j, v0 + j + 1, kVgprLds, off + 4 * j);
+                        ++issued;
+                    } else if (Q.need[j] || Q.need[j + 1]) {
+                        const int jj = Q.need[j] ? j : j + 1;
+                        e.line("\tds_read_b32 v%d, v%d offset:%d", v0 + jj, kVgprLds, off + 4 * jj);
+                        ++issued;
+                    }
+                }
+            }
+            Q.last_read = issued - 1;
+        };
+        // The reads run D quads ahead of the multiply-adds, over the ends of chunks as well: what a wave still has in
+        // registers of a chunk is multiplied while the first reads of the next one are on their way.  A wave enters a
+        // chunk (with its reads, that is) once its reads of the one before have returned and its share of this one is
+        // written; behind the barrier every wave has, so the other buffer is free for the share of the chunk after it.
+        // That is written a quarter of the way through the chunk, and the fetches that take its place in the registers
+        // go out one between two quads: sixteen in a row hold every wave of the workgroup up at the same time.
+        // Reads that ended with their chunk, shares written at its end and fetched in a row, against this, in us
+        // (fp32, uniform masks): 4096^3 at 98 % 76.0, 72.6; 2048 x 4096 x 12544 at 98 % 149.5, 145.1; 3072 x 3000 x 2900
+        // at 96 % 73.6, 72.1; 2048 x 1024 x 4096 at 97 % 19.1, 18.6; 4096 x 1024 x 784, batch 4, at 95 % 43.6, 43.1.
+        // Shares written at the start of the chunk or half way: 74.3 and 74.4 for the first of them.
+        // What is left there: launch and stores alone 10.5, with the staging 30.6 without any multiply-adds, which are 35
+        // at full rate; two waves per SIMD issue some 54 % of that rate.  Code is not it: half as long (values that need
+        // no literal) 71.7 -> 68.5.
+        int chunk = 0;            // the one that is read
+        bool staged_next = false; // this wave's share of the one after it is written
+        int fetch_behind = -1;    // LDS instruction behind which that share has left its registers, for the chunk after the next
+        std::vector<std::pair<int, int>> to_fetch;   // (row of B, register), of that chunk
+        size_t fetched = 0;
+        auto fetch = [&](size_t upto) {
+            for (; fetched < std::min(upto, to_fetch.size()); ++fetched) load_b_row(to_fetch[fetched].first, to_fetch[fetched].second, ring_pos++);
+        };
+        auto fetch_open = [&]() {
+            if (fetch_behind < 0) return;
+            e.line("\ts_waitcnt lgkmcnt(%d)", std::min(kMaxLgkm, issued - 1 - fetch_behind));
+            to_fetch = stage_rows(chunk + 3);
+            fetched = 0;
+            fetch_behind = -1;
+        };
+        auto stage_next = [&]() {
+            if (staged_next || chunk + 1 >= n_chunks) return;
+            issued += stage_write(chunk + 1);
+            fetch_behind = issued - 1;
+            staged_next = true;
+        };
+        auto enter_next_chunk = [&]() {
+            stage_next();
+            fetch_open();
+            fetch(to_fetch.size());
+            e.line("\ts_waitcnt lgkmcnt(0)");
+            e.line("\ts_barrier");
+            ++chunk;
+            staged_next = false;
         };
         stage_loads(0);
         stage_loads(1);
@@ -604,58 +682,26 @@ struct Gen {
         e.line("\ts_waitcnt lgkmcnt(0)");
         stage_loads(2);
         e.line("\ts_barrier");
-        int total_cols = 0;
-        for (int c = 0; c < n_chunks; ++c) {
-            // quads of this chunk that hold a nonzero column of the group
-            struct Quad { int q; std::vector<Term> terms[4]; bool need[4]; };
-            std::vector<Quad> quads;
-            for (auto it = cols.lower_bound(c * kChunkRows); it != cols.end() && it->first < (c + 1) * kChunkRows; ++it) {
-                const int kl = it->first - c * kChunkRows, q = kl / 4, j = kl % 4;
-                if (quads.empty() || quads.back().q != q) { quads.push_back(Quad()); quads.back().q = q; for (bool &b : quads.back().need) b = false; }
-                quads.back().need[j] = true;
-                quads.back().terms[j] = it->second;
-                ++total_cols;
-            }
-            const int nq = (int)quads.size();
-            std::vector<int> last_seq(nq, -1);
-            int issued = 0;
-            auto issue_reads = [&](int i) {
-                const Quad &Q = quads[i];
-                const int v0 = vgpr_ring0 + 4 * (i % D), off = (c & 1) * buf_bytes + Q.q * 1024;
-                const int cnt = Q.need[0] + Q.need[1] + Q.need[2] + Q.need[3];
-                if (cnt >= 3) {
-                    e.line("\tds_read_b128 v[%d:%d], v%d offset:%d", v0, v0 + 3, kVgprLds, off);
-                    ++issued;
-                } else {
-                    for (int j = 0; j < 4; j += 2) {
-                        if (Q.need[j] && Q.need[j + 1]) {
-                            e.line("\tds_read_b64 v[%d:%d], v%d offset:%d", v0 + j, v0 + j + 1, kVgprLds, off + 4 * j);
-                            ++issued;
-                        } else if (Q.need[j] || Q.need[j + 1]) {
-                            const int jj = Q.need[j] ? j : j + 1;
-                            e.line("\tds_read_b32 v%d, v%d offset:%d", v0 + jj, kVgprLds, off + 4 * jj);
-                            ++issued;
-                        }
-                    }
-                }
-                last_seq[i] = issued - 1;
-            };
-            for (int i = 0; i < std::min(D, nq); ++i) issue_reads(i);
-            for (int i = 0; i < nq; ++i) {
-                // LDS reads return in order: quad i is complete once at most
-                // (issued - 1 - last_seq[i]) later reads are outstanding
-                e.line("\ts_waitcnt lgkmcnt(%d)", std::min(kMaxLgkm, issued - 1 - last_seq[i]));
-                for (int j = 0; j < 4; ++j)
-                    if (quads[i].need[j]) fmas(quads[i].terms[j], vgpr_ring0 + 4 * (i % D) + j);
-                if (i + D < nq) issue_reads(i + D);
-            }
-            if (c + 1 < n_chunks) {
-                stage_write(c + 1);
-                e.line("\ts_waitcnt lgkmcnt(0)");
-                stage_loads(c + 3);
-                e.line("\ts_barrier");
-            }
+        int next = 0;             // quad to be read
+        auto read_next = [&]() {
+            if (next >= nq) return;
+            while (chunk < quads[next].chunk) enter_next_chunk();
+            issue_reads(next);
+            if (quads[next++].q >= quads_per_chunk / 4) stage_next();
+        };
+        while (next < std::min(D, nq)) read_next();
+        for (int i = 0; i < nq; ++i) {
+            // LDS instructions complete in order: quad i has arrived once at most
+            // (issued - 1 - last_read) later ones are outstanding
+            e.line("\ts_waitcnt lgkmcnt(%d)", std::min(kMaxLgkm, issued - 1 - quads[i].last_read));
+            if (fetch_behind >= 0 && fetch_behind < quads[i].last_read) fetch_open();
+            fetch(fetched + 1);
+            for (int j = 0; j < 4; ++j)
+                if (quads[i].need[j]) fmas(quads[i].terms[j], vgpr_ring0 + 4 * (i % D) + j);
+            read_next();
         }
+        while (chunk + 1 < n_chunks) enter_next_chunk();   // no quads left: the other waves still need this one's share
+        const int total_cols = (int)cols.size();
         std::vector<std::pair<int32_t, int>> all;
         for (size_t i = 0; i < rows.size(); ++i) all.push_back({rows[i], kVgprAcc0 + (int)i});
         stores(all);

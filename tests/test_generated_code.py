@@ -3,6 +3,7 @@ generated block stays inside its buffer, no register is used before its load has
 for (see asm_check.py).  Runs over the executor variants, storage types, convolution, batch,
 leading dimensions and a randomised grid - with no GPU."""
 import os
+import re
 
 import numpy as np
 import pytest
@@ -79,6 +80,41 @@ def test_lds_staged_blocks_stay_in_bounds(waves, K, dtype, tmp_path):
     csr = _csr(dtype, 90, K, 0.8, K)
     info, stats = _clean(csr, 130, tmp_path, spec_rows=6, spec_mode=sp.SPEC_LDS, spec_tiles=waves)
     assert stats["lds"] > 0 and stats["max_lds_end"] <= info["spec_lds_bytes"]
+
+
+@pytest.mark.parametrize("M,K,N,sparsity,rows,waves", [
+    (90, 515, 130, 0.8, 6, 4), (33, 129, 64, 0.9, 40, 2), (40, 300, 64, 0.99, 3, 16),   # a last chunk of 3, 1 and 44 rows
+    (90, 1000, 130, 0.999, 6, 8),                                                        # chunks without a nonzero of the block
+    (64, 128, 64, 0.9, 8, 4),                                                            # one chunk
+    (2048, 1024, 4035, 0.97, 0, 0)])                                                     # the default shape
+def test_lds_staged_waves_agree_on_which_buffer_is_read(M, K, N, sparsity, rows, waves, tmp_path):
+    opts = dict(spec_rows=rows, spec_tiles=waves, spec_mode=sp.SPEC_LDS) if rows else {}
+    text, info = _generated(synth.uniform_csr(M, K, sparsity, 3), N, tmp_path, **opts)
+    assert info["spec_mode"] == sp.SPEC_LDS
+    chunk = min(128, 32 * info["spec_tiles"])
+    for block in re.split(r"\n\.Lg\d+:", text)[1:]:
+        lines, barriers, in_flight, staging = [l.strip() for l in block.splitlines()], 0, 0, {}
+        for l in lines:
+            if l == "s_barrier":        # chunk `barriers` is read from here on, and the one after it written to the other buffer
+                assert in_flight == 0
+                barriers += 1
+            m = re.match(r"s_waitcnt lgkmcnt\((\d+)\)", l)
+            if m:
+                in_flight = min(in_flight, int(m.group(1)))
+                staging = {r: n for r, n in staging.items() if n < in_flight}
+            m = re.match(r"ds_(read|write)_b\d+ .*offset:(\d+)", l)
+            if m:
+                which = int(m.group(2)) // (chunk * 256)
+                assert which == ((barriers - 1) & 1 if m.group(1) == "read" else barriers & 1), l
+                staging = {r: n + 1 for r, n in staging.items()}
+                in_flight += 1
+                if m.group(1) == "write":
+                    first, last = re.search(r", v\[(\d+):(\d+)\]", l).groups()
+                    staging.update({r: 0 for r in range(int(first), int(last) + 1)})
+            m = re.match(r"buffer_load_dword v(\d+),", l)
+            if m:                       # not over words that may still be on their way into LDS
+                assert int(m.group(1)) not in staging, l
+        assert barriers == -(-K // chunk)
 
 
 @pytest.mark.parametrize("ldb,ldc,batch", [(0, 0, 3), (136, 0, 1), (0, 4096, 1), (200, 264, 2)])
