@@ -66,16 +66,22 @@ inline int mfma_rows_per_part(const MfmaConfig &c, int64_t M, int64_t K, int64_t
     const int64_t m_tiles = (M + c.tm - 1) / c.tm, n_tiles = (N + c.tn - 1) / c.tn, tasks = m_tiles * n_tiles, share = (tasks + 7) / 8;
     int64_t best = mfma_m_fast(c, M, K, N, elem_size) ? m_tiles : 1;
     double least = 0;
+    struct Place { int64_t part, n, m; };
+    auto place = [&](int64_t per, int64_t t) {
+        const int64_t part = t / (per * n_tiles), in = t - part * per * n_tiles, here = std::min(per, m_tiles - part * per);
+        return Place{part, in / here, in % here};
+    };
     for (int64_t parts = 0; parts <= 16 && parts <= m_tiles && tasks <= 65536; ++parts) {
         const int64_t per = parts ? (m_tiles + parts - 1) / parts : best;   // first the better one of the two that end at 1
         double rows = 0, columns = 0;   // tiles pulled
         for (int64_t x = 0; x * share < tasks; ++x) {
-            int64_t m_lo = m_tiles, m_hi = -1, n_lo = n_tiles, n_hi = -1;
-            for (int64_t t = x * share; t < std::min(tasks, (x + 1) * share); ++t) {
-                const int64_t part = t / (per * n_tiles), in = t - part * per * n_tiles, here = std::min(per, m_tiles - part * per);
-                const int64_t n = in / here, m = part * per + in % here;
-                m_lo = std::min(m_lo, m); m_hi = std::max(m_hi, m); n_lo = std::min(n_lo, n); n_hi = std::max(n_hi, n);
-            }
+            const int64_t last = std::min(tasks, (x + 1) * share) - 1;
+            const Place from = place(per, x * share), to = place(per, last);
+            // A range over the end of a part has the last columns of the one and the first of the other.
+            const bool over = from.part != to.part;
+            const int64_t n_lo = over ? 0 : from.n, n_hi = over ? n_tiles - 1 : to.n;
+            const int64_t m_lo = from.part * per + (from.n == (over ? n_tiles - 1 : to.n) ? from.m : 0);
+            const int64_t m_hi = to.part * per + (to.n == (over ? 0 : from.n) ? to.m : std::min(per, m_tiles - to.part * per) - 1);
             rows += (double)(m_hi - m_lo + 1); columns += (double)(n_hi - n_lo + 1);
         }
         const double bytes = (rows * c.tm + columns * c.tn) * (double)K * elem_size;
