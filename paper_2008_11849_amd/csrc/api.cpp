@@ -152,7 +152,7 @@ int sparsert_plan_export(const sparsert_plan *plan, int32_t field, void *buf, si
             const std::string shape = "Li" + std::to_string(s.V) + "ELi" + std::to_string(s.rows_per_wave) + "EEEvNS_10StagedArgsE";
             name = h.dtype == SPARSERT_F16 ? "_ZN8sparsert18staged_rows_kernelIDF16_" + shape
                                            : std::string("void sparsert::staged_rows_kernel<") + (h.dtype == SPARSERT_I8 ? "signed char" : "float") + ", " +
-                                                 std::to_string(s.V) + ", " + std::to_string(s.rows_per_wave) + ">(sparsert::StagedArgs)";
+                                                 std::to_string(s.V) + ", " + std::to_string(s.rows_per_wave) + (s.short_shares ? ">(sparsert::StagedShortArgs)" : ">(sparsert::StagedArgs)");
         } else if (h.dtype == SPARSERT_F16) {
             // the profiler's demangler does not know the half type and shows the symbol as it is
             name = "_ZN8sparsert11rows_kernelIDF16_Li" + std::to_string(h.vec) + "ELb" + (h.conv ? "1" : "0") + "EEEvNS_8RowsArgsE";

@@ -18,6 +18,7 @@ struct StagedRows {
     int pitch = 0;         // bytes of a row of the tile in LDS
     int chunk = 0, chunks = 0;   // rows of B per LDS buffer
     double microseconds = 0;     // what it is expected to take
+    bool short_shares = false;   // pairs in steps of four at most
 };
 
 // The estimates below are fits to 230 products drawn from M, K <= 4096, N from 49 to 4096 and 80 % to 98 %
@@ -114,6 +115,11 @@ inline StagedRows staged_rows_shape(const HostPlan &h) {
         if (best.V == 0 || s.microseconds < best.microseconds) best = s;
     }
     if (best.V && (best.microseconds > 0.8 * plain_rows_microseconds(h, longest) || !staged_rows_confirmed(h, best, longest))) best.V = 0;
+    // A step of eight loads 64 bytes of pairs ahead whatever is left of a row's share.  In fp32 that pays from about eight
+    // pairs to a share on, in us, steps of four and of eight: eight rows to a wave 2049 x 256 x 784 at 95.4 % (7.2 pairs) 7.86 and 8.24,
+    // 2049 x 4096 x 196, batch 4, at 92.8 % (14.5) 77.5 and 75.3; four rows 4096 x 3072 x 2048 at 93.6 % (5.0) 184.2 and 189.5,
+    // 4096 x 3072 x 516 at 92.4 % (8.8) 73.7 and 72.1.  Half and int8 lose nothing with as few as 5.4 (0.5 % within the noise).
+    best.short_shares = best.V && esz == 4 && (int64_t)h.nnz < 8 * (int64_t)h.M * best.chunks;
     return best;
 }
 

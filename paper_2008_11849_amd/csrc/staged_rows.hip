@@ -6,22 +6,26 @@
 // rows of B into LDS once, chunk by chunk (two buffers, the next chunk travels while one is worked on), for
 // all of its 64 or 128 rows of A, and every nonzero reads its operand there.  LDS, 128 bytes per clock, is
 // the bound: for the same product 87 us of operand reads (49 of 64 lanes own columns), 15 % of pairs that
-// only fill up, 25 us of copies into it; measured 142.7 us.  Half and int8 move fewer bytes per nonzero and
-// are bound by the instructions per nonzero (2048 x 2048 at 95 %, 784 columns: half 39.2 -> 25.9 us, int8
-// 41.0 -> 24.7 us).
+// only fill up, 25 us of copies into it; measured 137 us.  Half and int8 move fewer bytes per nonzero and
+// are bound by the instructions per nonzero and by the waits between them (2048 x 2048 at 95 %, 784 columns: half
+// 39.2 us in the plain kernel, 25.9 us here in fours; int8 41.0 and 24.7 us).
 //
 // A wave owns up to RW rows, whose accumulators stay in registers over all chunks.  The nonzeros are laid
 // out in the order the waves meet them - row group, wave, chunk, row - so a wave walks one contiguous
-// stream of {LDS offset of the operand row, value} pairs with scalar loads, four pairs at a time and two at
-// the end of a row's share; how many twos belong to each of its rows comes packed in bytes, one word or two
+// stream of {LDS offset of the operand row, value} pairs with scalar loads, eight pairs at a time and four and
+// two at the end of a row's share; how many twos belong to each of its rows comes packed in bytes, one word or two
 // per chunk.  A share of odd length is filled up with a zero value times a row of zeros behind the chunk,
-// never with elements of B.  (Shares in fours only: 147.6 us.)  Row groups and waves are dealt in serpentine
+// never with elements of B.  A wave waits once per step, for its operands and the next step's words, some 400
+// clocks with sixteen waves at the LDS; in steps of four at most it waited nearly twice as often (the product
+// above 140.5 us; half 4096 x 1000 x 784 with skewed rows at 93.5 % 38.4 -> 31.2 us, int8 2048 x 3072 x 516, batch 4,
+// at 82 % 304.8 -> 262.8 us).  A fourth size, six, cost 2 to 7 % of it all in fp32.  Row groups and waves are dealt in serpentine
 // order over the rows by descending length.
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
 #include <cstring>
 #include <string>
+#include <type_traits>
 
 #include "lds_copy.h"
 #include "staged_rows.h"
@@ -39,6 +43,8 @@ struct StagedArgs {
     int32_t lanes, tiles, groups;
     int32_t stream_bytes, pitch, chunk, chunks;
 };
+
+struct StagedShortArgs : StagedArgs {};   // of plans whose rows have few pairs in a chunk
 
 // Bytes of one of the two LDS buffers: a chunk's rows and one row of zeros, in whole copies.
 __host__ __device__ constexpr int staged_buffer_bytes(int chunk, int pitch) { return ((chunk + 1) * pitch + 1023) & ~1023; }
@@ -64,8 +70,8 @@ template <> struct StagedOps<int8_t, 4> {   // the four packed columns stay in t
     }
 };
 
-template <typename T, int V, int RW>
-__global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(const StagedArgs a) {
+template <typename T, int V, int RW, int MOST>   // MOST: pairs at a time, four or eight
+__device__ __forceinline__ void staged_rows(const StagedArgs &a) {
     typedef StagedOps<T, V> Q;
     typedef typename Q::opd_t opd_t;
     typedef typename Q::out_t out_t;
@@ -105,13 +111,25 @@ __global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(con
         for (int j = 0; j < V; ++j) acc[r][j] = 0;
     const int owner = group * kStagedWaves + wave;
     // (constant address space: scalar loads, whatever the copies' assembly may touch)
-    typedef uint32_t group_t __attribute__((ext_vector_type(8), aligned(4)));   // four pairs
+    typedef uint32_t group_t __attribute__((ext_vector_type(2 * MOST), aligned(4)));
     typedef const uint2 __attribute__((address_space(4))) *pairs_t;
     typedef const uint32_t __attribute__((address_space(4))) *words_t;
     typedef const int32_t __attribute__((address_space(4))) *ints_t;
     pairs_t p = (pairs_t)a.stream + ((ints_t)a.starts)[owner];
     const words_t counts = (words_t)a.counts + (size_t)owner * a.chunks * (RW / 4);
     group_t next = *reinterpret_cast<const group_t __attribute__((address_space(4))) *>(p);
+    // The next PAIRS pairs of the stream, of one row.
+    auto step = [&](acc_t (&sum)[V], const char *base, auto pairs) {
+        constexpr int PAIRS = decltype(pairs)::value;
+        const group_t g = next;
+        p += PAIRS;
+        next = *reinterpret_cast<const group_t __attribute__((address_space(4))) *>(p);   // (the stream is padded by two groups of eight)
+        opd_t b[PAIRS];
+#pragma unroll
+        for (int i = 0; i < PAIRS; ++i) b[i] = *reinterpret_cast<const opd_t *>(base + g[2 * i]);
+#pragma unroll
+        for (int i = 0; i < PAIRS; ++i) Q::mad(sum, g[2 * i + 1], b[i]);
+    };
 
     issue(0);
     for (int c = 0; c < a.chunks; ++c) {
@@ -131,26 +149,9 @@ __global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(con
         for (int r = 0; r < RW; ++r) {
             int n = (int)(cnt[r / 4] >> (8 * (r % 4)) & 0xffu);   // twos
 #pragma unroll 1
-            for (; n > 1; n -= 2) {
-                const group_t g = next;
-                p += 4;
-                next = *reinterpret_cast<const group_t __attribute__((address_space(4))) *>(p);   // (the stream is padded by a group)
-                opd_t b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) b[i] = *reinterpret_cast<const opd_t *>(base + g[2 * i]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) Q::mad(acc[r], g[2 * i + 1], b[i]);
-            }
-            if (n) {
-                const group_t g = next;
-                p += 2;
-                next = *reinterpret_cast<const group_t __attribute__((address_space(4))) *>(p);
-                opd_t b[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) b[i] = *reinterpret_cast<const opd_t *>(base + g[2 * i]);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) Q::mad(acc[r], g[2 * i + 1], b[i]);
-            }
+            for (; n >= MOST / 2; n -= MOST / 2) step(acc[r], base, std::integral_constant<int, MOST>());
+            if (MOST == 8 && n > 1) { step(acc[r], base, std::integral_constant<int, 4>()); n -= 2; }
+            if (n) step(acc[r], base, std::integral_constant<int, 2>());
         }
     }
 
@@ -176,6 +177,11 @@ __global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(con
     }
 }
 
+template <typename T, int V, int RW>
+__global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(const StagedArgs a) { staged_rows<T, V, RW, 8>(a); }
+template <typename T, int V, int RW>
+__global__ __launch_bounds__(kStagedWaves *kWave, 4) void staged_rows_kernel(const StagedShortArgs a) { staged_rows<T, V, RW, 4>(a); }
+
 int prepare_staged_rows(const HostPlan &h, DevicePlan &d, std::string &err) {
     const StagedRows s = staged_rows_shape(h);
     StagedArgs a;
@@ -195,11 +201,16 @@ int prepare_staged_rows(const HostPlan &h, DevicePlan &d, std::string &err) {
         err = "plan geometry is inconsistent";
         return SPARSERT_EINVAL;
     }
+    typedef void (*plain_t)(StagedArgs);
     const void *kernel = nullptr;
-    if (h.dtype == SPARSERT_I8) kernel = (const void *)staged_rows_kernel<int8_t, 4, 4>;
-    else if (h.dtype == SPARSERT_F16) kernel = (const void *)staged_rows_kernel<_Float16, 4, 4>;
-    else if (s.V == 4) kernel = (const void *)staged_rows_kernel<float, 4, 4>;
-    else kernel = s.rows_per_wave == 8 ? (const void *)staged_rows_kernel<float, 2, 8> : (const void *)staged_rows_kernel<float, 2, 4>;
+    if (h.dtype == SPARSERT_I8) kernel = (const void *)static_cast<plain_t>(staged_rows_kernel<int8_t, 4, 4>);
+    else if (h.dtype == SPARSERT_F16) kernel = (const void *)static_cast<plain_t>(staged_rows_kernel<_Float16, 4, 4>);
+    else if (s.short_shares) {
+        typedef void (*short_t)(StagedShortArgs);
+        kernel = (const void *)(s.V == 4 ? static_cast<short_t>(staged_rows_kernel<float, 4, 4>) : s.rows_per_wave == 8 ? static_cast<short_t>(staged_rows_kernel<float, 2, 8>) : static_cast<short_t>(staged_rows_kernel<float, 2, 4>));
+    } else {
+        kernel = (const void *)(s.V == 4 ? static_cast<plain_t>(staged_rows_kernel<float, 4, 4>) : s.rows_per_wave == 8 ? static_cast<plain_t>(staged_rows_kernel<float, 2, 8>) : static_cast<plain_t>(staged_rows_kernel<float, 2, 4>));
+    }
     hipFunction_t fn = nullptr;
     const hipError_t e = hipGetFuncBySymbol(&fn, kernel);
     if (e != hipSuccess) { err = std::string("staged row-walk kernel: ") + hipGetErrorString(e); return SPARSERT_EHIP; }

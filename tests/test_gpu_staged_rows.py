@@ -52,6 +52,24 @@ def test_spmm_against_the_oracle(case, dtype):
     assert pad_ok and np.array_equal(got.astype(np.float64), want)
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float16, np.int8])
+@pytest.mark.parametrize("M,K,N,lengths", [(4096, 600, 788, 22), (4096, 600, 2048, 8), (2049, 256, 784, 6)])
+def test_shares_of_every_length(M, K, N, lengths, dtype):
+    """Eights (fours, where shares are short) in a loop and four or two at the end: rows with 0 to lengths - 1 nonzeros in every
+    50 columns; longer than a loop's step where they are not short."""
+    rng = np.random.default_rng(K)
+    mask = (np.arange(K)[None, :] % 50 * 7 + np.arange(M)[:, None]) % 50 < (np.arange(M) % lengths)[:, None]
+    mask[-3:, :K - 1] |= lengths == 22
+    vals = (rng.integers(1, 3, size=(M, K)) * rng.choice([-1, 1], size=(M, K))).astype(dtype)
+    csr = synth.csr_from_mask(vals, mask)
+    plan = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, kernel=sp.KERNEL_ROWS, host_only=True)
+    assert "staged_rows_kernel" in plan.kernel_name() or (dtype != np.float32 and lengths < 22)
+    assert ("StagedShortArgs" in plan.kernel_name()) == (dtype == np.float32 and lengths < 22)
+    B = rng.integers(-1, 2, size=(K, N)).astype(dtype)
+    want = ref.spmm(M, K, N, csr.row_ptr, csr.col_idx, csr.vals, B)[0]
+    assert np.array_equal(run_spmm(csr, B, kernel=sp.KERNEL_ROWS)[0].astype(np.float64), want)
+
+
 def test_non_finite_operands_stay_where_they_are():
     M, K, N = 2100, 333, 516
     rng = np.random.default_rng(3)
