@@ -58,7 +58,8 @@ void staged_rows_pack(const HostPlan &h, StagedPack &out) {
                 const uint32_t zero_row = (uint32_t)(s.chunk * s.pitch);
                 for (; next[r] < end && h.p_col_idx[next[r]] < limit; ++next[r], ++n) {
                     out.stream.push_back((uint32_t)(h.p_col_idx[next[r]] - c * s.chunk) * (uint32_t)s.pitch);
-                    out.stream.push_back(h.stream[2 * (size_t)next[r] + 1]);
+                    const uint32_t value = h.stream[2 * (size_t)next[r] + 1];
+                    out.stream.push_back(h.dtype == SPARSERT_I8 ? (value & 0xffu) << (n % 2 * 8) : value);   // (int8: where the kernel wants it)
                 }
                 if (n % 2) { ++n; out.stream.push_back(zero_row); out.stream.push_back(0); }
                 out.counts[((size_t)o * s.chunks + c) * rw + r] = (uint8_t)(n / 2);
