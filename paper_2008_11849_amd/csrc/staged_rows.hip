@@ -8,7 +8,7 @@
 // the bound: for the same product 87 us of operand reads (49 of 64 lanes own columns), 5 % of pairs that
 // only fill up, 25 us of copies into it; measured 137 us.  Half and int8 move fewer bytes per nonzero and
 // are bound by the instructions per nonzero and by the waits between them (2048 x 2048 at 95 %, 784 columns: half
-// 39.2 us in the plain kernel, 25.9 us here in fours; int8 41.0 and 24.7 us).
+// 39.2 us in the plain kernel, 25.9 us here in fours; int8 41.0 us, 24.7 us in fours with a v_dot4 per row and column).
 //
 // A wave owns up to RW rows, whose accumulators stay in registers over all chunks.  The nonzeros are laid
 // out in the order the waves meet them - row group, wave, chunk, row - so a wave walks one contiguous
