@@ -315,9 +315,7 @@ __global__ __launch_bounds__(WM *WN *kWave, mfma_waves_per_simd(WM *MF * 16, WN 
         constexpr int FLAGS = TM * PITCH;
         static_assert(FLAGS + WAVES * 4 <= STAGES * STAGE, "the tile's results fit the slabs");
         float probe = 0.0f;   // becomes NaN with the first sum that is not finite
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();   // every wave has read the last slab, and no copy is on its way
-        asm volatile("" ::: "memory");
+        meet();   // every wave has read the last slab, and no copy is on its way
         char *mine = lds + (wm * MF * 16 + lg) * PITCH + (wn * NF * 16 + 4 * g) * (int)sizeof(out_t);
 #pragma unroll
         for (int i = 0; i < MF; ++i)
