@@ -1005,16 +1005,16 @@ struct Deal {
 };
 
 // What a deal costs: the bytes that all L2s together pull, a tile (of one problem) and a code block counted once for every
-// XCD that touches them, and the most code that one XCD runs.  A byte of code weighs three times: its misses come one
-// after the other, B's overlap.  (Over 75 products and convolutions, each timed in launch order and in 1, 2, 4 and 8
-// parts: with a factor of 3 to 5 the choice is 1.058 times faster than launch order, with 1 or 8 1.053, the best of the five 1.079.)
-struct DealCost { double bytes = 0, weighed = 0, busiest = 0; };
+// XCD that touches them, and the most code that one XCD and one compute unit run: an XCD has 32, its workgroups come to them in turn.
+// A byte of code weighs three times: its misses come one after the other, B's overlap.  (Over 75 products and convolutions,
+// each timed in launch order and in 1, 2, 4 and 8 parts, a factor of 3 to 5 chose best, 1 or 8 half a percent worse.)
+struct DealCost { double bytes = 0, weighed = 0, busiest_xcd = 0, busiest_unit = 0; };
 constexpr double kCodeByte = 3;
 
 static DealCost deal_cost(const Deal &d, double tile_bytes, const std::vector<int64_t> &block_bytes) {
     const int64_t all = d.workgroups(), share = all / 8, more = all % 8, tiles = d.tiles * d.batch;
     std::vector<uint8_t> has_tile(8 * (size_t)tiles, 0), has_block(8 * (size_t)d.blocks, 0);
-    double run[8] = {0};
+    double run[8] = {0}, unit[8 * 32] = {0};
     for (int64_t i = 0; i < all; ++i) {
         const int64_t x = i & 7;
         int64_t tile, block;
@@ -1026,6 +1026,7 @@ static DealCost deal_cost(const Deal &d, double tile_bytes, const std::vector<in
         }
         has_tile[(size_t)(x * tiles + tile)] = has_block[(size_t)(x * d.blocks + block)] = 1;
         run[x] += (double)block_bytes[(size_t)block];
+        unit[x * 32 + (i >> 3) % 32] += (double)block_bytes[(size_t)block];
     }
     DealCost c;
     for (uint8_t v : has_tile) c.bytes += v * tile_bytes;
@@ -1035,15 +1036,25 @@ static DealCost deal_cost(const Deal &d, double tile_bytes, const std::vector<in
         c.bytes += code;
         c.weighed += kCodeByte * code;
     }
-    c.busiest = *std::max_element(run, run + 8);
+    c.busiest_xcd = *std::max_element(run, run + 8);
+    c.busiest_unit = *std::max_element(unit, unit + 8 * 32);
     return c;
 }
 
 // The row that costs least and does not push an XCD's share towards the size of its L2 (4 MiB; 768 x 3072, 1024 columns, 95 %: 3.2 MB
 // in launch order, 4.0 MB in two parts, 13.5 and 13.6 us).  Launch order stays where the best row saves less than a tenth; where the code,
-// which every column tile of a part runs again, would not stay in an L2; and where blocks are so unequal (rows of very different
-// lengths, few to a block) that the long ones, which come first in launch order, should start first and on different XCDs:
-// half convolution of 64 x 1152, 18 x 18, skewed rows, one to a block: 4.9 us in launch order, 7.7 us in parts.
+// which every column tile of a part runs again, would not stay in an L2; where an XCD would get a tenth more code, or a compute unit any
+// more and the L2s do not pull 5000 bytes less for each byte of that; and where blocks are so unequal (rows of very different lengths,
+// few to a block) that the long ones, which come first in launch order, should start first and on different XCDs: half convolution of 64 x 1152, 18 x 18, skewed
+// rows, one to a block: 4.9 us in launch order, 7.7 us in parts.
+// The compute unit: with 33 to 64 workgroups to an XCD some run two, in launch order a long block and a short one, in parts whatever comes
+// together: int8 convolution 47 x 891, 46 x 46, skewed rows, 34 to an XCD: 1.54 times the code, 3.6 and 4.7 us; half 64 x 576, 41 x 41:
+// 1.2 to 1.3 times, 3.4 and 3.9 us; half 64 x 1152, 43 x 43, blocks of six and seven rows: 1.04 times, 7.7 MB less for 2 KB more, 7.5 and
+// 7.7 us; but 80 x 4320, 23 x 23, batch 2: 1.04 times, 24 MB less for 3.5 KB more, 14.8 and 13.6 us.  (A compute unit runs some 7 KB in a
+// microsecond; 4000 and 7000 choose as well.)
+// Over 292 drawn products and convolutions (56 with skewed rows, several plans taking turns) the choice is 1.062 times faster than launch order,
+// the best of the five 1.075; 6 % slower at worst where C is large (1216 x 512 x 2880 and 1856 x 120 x 3416, batch 4: 33.6 and 35.6, 29.7 and
+// 31.6 us, the second 24.6 and 21.8 us while C stays in the cache behind the L2s), 3 % and less otherwise.
 static Deal choose_deal(const HostPlan &h, const SpecPlan &sp, const std::vector<int64_t> &code_block_bytes) {
     Deal d;
     const bool lds = sp.mode == SPARSERT_SPEC_LDS;
@@ -1069,7 +1080,9 @@ static Deal choose_deal(const HostPlan &h, const SpecPlan &sp, const std::vector
         if (d.workgroups() * std::max<int64_t>(d.tiles * d.batch * d.per_part, d.tiles) >= (1ll << 32)) continue;   // (the prologue's divisions)
         const DealCost c = deal_cost(d, tile_bytes, block_bytes);
         if (c.bytes > now.bytes && c.bytes > 8 * 3.5e6) continue;
-        if (c.weighed < least && c.busiest < 1.1 * now.busiest) { least = c.weighed; best = d; }
+        const double more = c.busiest_unit - 1.01 * now.busiest_unit;   // (1 %: equal blocks differ by as much)
+        if (more > 0 && now.bytes - c.bytes < 5000 * more) continue;
+        if (c.weighed < least && c.busiest_xcd < 1.1 * now.busiest_xcd) { least = c.weighed; best = d; }
     }
     return best;
 }

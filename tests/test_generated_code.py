@@ -251,6 +251,19 @@ def test_every_tile_and_block_is_dealt_to_one_workgroup(M, K, N, batch, mask, op
         touched = lambda work: sum(len({(t, z) for t, _, z in work[x::8]}) * K * info["spec_lanes"] * 4 + 3 * len({b for _, b, _ in work[x::8]}) * info["spec_code_bytes"] / blocks
                                    for x in range(8))
         assert touched(got) < 0.95 * touched(ids)
+        lines = [len(b.splitlines()) for b in re.split(r"\n\.Lg\d+:", text)[1:]]
+        waves = len(lines) // blocks
+        of_block = [sum(lines[b * waves:(b + 1) * waves]) for b in range(blocks)]   # and what a compute unit runs, 32 to an XCD
+        busiest = lambda work: max(sum(of_block[b] for _, b, _ in work[x::8][cu::32]) for x in range(8) for cu in range(32))
+        assert busiest(got) < 1.05 * busiest(ids)
+
+
+@pytest.mark.parametrize("M,K,N,opts", [
+    (47, 891, 2116, dict(spec_rows=6, spec_ksplit=8)),     # 34 workgroups to an XCD, rows of very different lengths
+    (184, 306, 2500, dict(spec_rows=7, spec_tiles=4))])    # 33 or 34, no K split
+def test_workgroups_stay_in_launch_order_where_a_compute_unit_would_get_more_code(M, K, N, opts, tmp_path):
+    text, _ = _generated(synth.skewed_csr(M, K, 0.9, 4), N, tmp_path, **opts)
+    assert _deal(text)[0].startswith("v_")   # no scalar arithmetic on the workgroup ids
 
 
 @pytest.mark.parametrize("rows,gap", [(54, True), (36, False), (100, False)])
