@@ -274,3 +274,11 @@ def test_code_blocks_do_not_lie_a_multiple_of_8_kib_apart(rows, gap, tmp_path):
     assert len(spaces) == 1 and (int(spaces.pop().split()[1]) > 0) == gap
     between = info["spec_code_bytes"] / (8 * info["spec_groups"])
     assert 1900 < between % 8192 < 6300
+
+
+@pytest.mark.parametrize("M,K,N,rows", [(1024, 1024, 832, 44), (80, 512, 3136, 80)])   # 1.5 KB from the multiple; 59 KB of code
+def test_code_blocks_stay_where_they_are_fetched_as_fast(M, K, N, rows, tmp_path):
+    text, info = _generated(synth.uniform_csr(M, K, 0.879 if M == 80 else 0.9, 4), N, tmp_path, spec_rows=rows, spec_ksplit=8)
+    assert {l.strip().split()[1] for l in text.splitlines() if ".space" in l} == {"0"}
+    off = info["spec_code_bytes"] / (8 * info["spec_groups"]) % 8192
+    assert 6100 < off < 7900 or off < 2048
