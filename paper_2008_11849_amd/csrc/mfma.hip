@@ -430,7 +430,7 @@ int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err) {
     const int64_t m_tiles = (h.M + c.tm - 1) / c.tm, tasks = m_tiles * ((h.N + c.tn - 1) / c.tn);
     if (tasks > (1ll << 30)) { err = "too many workgroups"; return SPARSERT_EUNSUPPORTED; }
     const int64_t n_tiles = (h.N + c.tn - 1) / c.tn;
-    a.per_part = mfma_rows_per_part(c, h.M, h.K, h.N, esz);
+    a.per_part = mfma_rows_per_part(c, h.M, h.K, h.N, h.ldb, esz);
     auto magic = [&](int64_t d) { return d > 1 && tasks * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; };
     a.part_magic = magic(a.per_part * n_tiles); a.here_magic = magic(a.per_part); a.last_magic = magic(m_tiles % a.per_part);
     if (!mfma_fits(c, h.M, h.K, esz) || ((int64_t)(h.K - 1) * h.ldb + h.N) * esz >= (1ll << 31)) { err = "plan geometry is inconsistent"; return SPARSERT_EINVAL; }

@@ -1,4 +1,4 @@
-"""Checks of the assembly that the compiler makes of the hand-written kernels (no GPU)."""
+"""Checks of the assembly that the compiler makes of the hand-written kernels, and of their launch geometry (no GPU)."""
 import os
 import re
 import subprocess
@@ -38,3 +38,29 @@ def test_half_results_of_low_tiles_go_straight_to_memory(tmp_path):
     """Tiles of 32 rows and less with rows of C that are no whole 128-byte lines; 32 columns of halves never are."""
     bodies = dict(re.findall(r"^_ZN8sparsert11mfma_kernelI(\w+?)EEEvNS_8MfmaArgsE:.*?$(.*?)^\.Lfunc_end", _assembly("mfma.hip", tmp_path), re.S | re.M))
     assert "ds_write" not in bodies["Li0ELi2ELi2ELi1ELi1ELi2ELi4"] and "ds_write" in bodies["Li0ELi2ELi2ELi2ELi2ELi2ELi4"]
+
+
+def _pulled(M, K, N, ldb, esz, tm, tn, per):
+    """Bytes of A and B, B in lines of 128 bytes, that the eight XCDs pull with the tiles in parts of `per` along M."""
+    m_tiles, n_tiles = -(-M // tm), -(-N // tn)
+    order = [(m, n) for m0 in range(0, m_tiles, per) for n in range(n_tiles) for m in range(m0, min(m_tiles, m0 + per))]
+    share, total = -(-len(order) // 8), 0
+    for x in range(0, len(order), share):
+        mine = order[x:x + share]
+        total += len({m for m, _ in mine}) * tm * K * esz
+        total += 128 * len({line for n in {n for _, n in mine} for k in range(K)
+                            for line in range((k * ldb + n * tn) * esz // 128, ((k * ldb + min(N, (n + 1) * tn)) * esz - 1) // 128 + 1)})
+    return total
+
+
+@pytest.mark.parametrize("M,K,N,ldb,esz,tm,tn", [
+    (272, 3592, 196, 196, 1, 32, 32), (768, 3072, 1024, 1024, 1, 64, 64), (3072, 768, 1024, 1024, 2, 96, 128), (226, 1768, 128, 128, 2, 32, 32),
+    (594, 640, 1142, 1142, 1, 64, 128), (608, 1024, 496, 550, 2, 32, 64), (248, 2696, 640, 640, 1, 32, 32), (147, 1904, 1248, 1248, 1, 32, 32)])
+def test_order_of_tiles_pulls_few_bytes(M, K, N, ldb, esz, tm, tn, tmp_path):
+    source = tmp_path / "order.cpp"
+    source.write_text('#include <cstdio>\n#include "mfma.h"\nint main() { using namespace sparsert;\n'
+                      f'    printf("%d", mfma_rows_per_part(kMfmaConfigs[mfma_find({tm}, {tn})], {M}, {K}, {N}, {ldb}, {esz})); }}\n')
+    subprocess.run(["g++", "-std=c++17", "-I", entry.CSRC, "-o", str(tmp_path / "order"), str(source)], check=True)
+    chosen = int(subprocess.run([str(tmp_path / "order")], capture_output=True, text=True, check=True).stdout)
+    least = min(_pulled(M, K, N, ldb, esz, tm, tn, per) for per in {1, -(-M // tm)})
+    assert _pulled(M, K, N, ldb, esz, tm, tn, chosen) < 1.05 * least
