@@ -307,11 +307,12 @@ __global__ __launch_bounds__(WM *WN *kWave, mfma_waves_per_simd(WM *MF * 16, WN 
     const uint32_t row_bytes = (uint32_t)a.ldc * (uint32_t)sizeof(out_t);
     const bool lines = row_bytes % 128 == 0 && TN * sizeof(out_t) % 128 == 0;   // whole ones are written
     // Through LDS, so that a wave stores whole rows of the tile: straight from the accumulators it would be 16 rows of 32
-    // (int8: 64) bytes each.  Without whole lines int8 stays with that (3784 x 182 x 200, batch 4: 6.4 against 6.6 us), and so do
-    // half tiles of 32 rows and less (47 products of 3 to 6 us: 1.1 % faster; 352 x 960 x 720: 4.17 against 4.35 us).
+    // (int8: 64) bytes each.  Without whole lines int8 stays with that (3784 x 182 x 200, batch 4: 6.4 against 6.6 us), and so do half
+    // tiles of 32 x 32, whose rows never are whole lines (83 products of 3 to 5 us: 1.2 % faster).  Half tiles of 32 x 64: 0.98 times as fast
+    // through LDS where rows of C begin on 8 bytes, 1.03 times with whole lines or many rows that do not; asking at run time costs 2 %.
     // 3072 x 768 x 1024 half: 9.2 -> 8.5 us; 1472 x 168 x 2592 int8 7.8 -> 6.3 us (the hint included).
     bool finite = true;   // all sums of the workgroup
-    if (lines || (DT == 0 && TM > 32)) {
+    if (DT == 0 ? TM > 32 || TN > 32 : lines) {
         constexpr int PITCH = TN * (int)sizeof(out_t) + 16;   // rows 16 bytes further apart: fewer bank conflicts
         constexpr int FLAGS = TM * PITCH;
         static_assert(FLAGS + WAVES * 4 <= STAGES * STAGE, "the tile's results fit the slabs");

@@ -34,8 +34,8 @@ def test_waves_meet_with_no_lds_access_on_its_way(source, kernels, tmp_path):
                     break
 
 
-def test_half_results_of_low_tiles_go_straight_to_memory(tmp_path):
-    """Tiles of 32 rows and less with rows of C that are no whole 128-byte lines; 32 columns of halves never are."""
+def test_half_results_of_small_tiles_go_straight_to_memory(tmp_path):
+    """Rows of 32 halves are never whole lines of 128 bytes; a small tile does not earn the barrier and the round trip back."""
     bodies = dict(re.findall(r"^_ZN8sparsert11mfma_kernelI(\w+?)EEEvNS_8MfmaArgsE:.*?$(.*?)^\.Lfunc_end", _assembly("mfma.hip", tmp_path), re.S | re.M))
     assert "ds_write" not in bodies["Li0ELi2ELi2ELi1ELi1ELi2ELi4"] and "ds_write" in bodies["Li0ELi2ELi2ELi2ELi2ELi2ELi4"]
 
