@@ -1154,7 +1154,7 @@ static int gap_between_blocks(int64_t code_bytes, int64_t blocks) {
 
 // Stage 4a, emission of everything before the blocks: directives, the prologue that turns the
 // workgroup and lane ids into a block, a column and two buffer descriptors, and the jump table.
-static void emit_prologue(Gen &gen, Emitter &e, const Shape &sh, const Extents &ex, const Deal &deal, int prefetch_lines) {
+static void emit_prologue(Gen &gen, Emitter &e, const Shape &sh, const Extents &ex, const Deal &deal, int prefetch_lines, int gap) {
     const HostPlan &h = gen.h;
     SpecPlan &sp = gen.sp;
     const bool lds = sh.lds;
@@ -1297,7 +1297,8 @@ static void emit_prologue(Gen &gen, Emitter &e, const Shape &sh, const Extents &
         // block are masked off, so nothing outside this block's code is read): the misses overlap
         // each other and the first fetches of B.  The destination register is one no block uses.
         const int stride = 128 * prefetch_lines;
-        e.line("\ts_sub_u32 s%d, s%d, s%d", kSgprEntry + 1, kSgprEntry + 1, kSgprEntry);   // bytes of code in this block
+        e.line("\ts_sub_u32 s%d, s%d, s%d", kSgprEntry + 1, kSgprEntry + 1, kSgprEntry);   // from this block to the next
+        if (gap) e.line("\ts_sub_u32 s%d, s%d, 0x%x", kSgprEntry + 1, kSgprEntry + 1, (unsigned)gap);   // bytes of code in this block
         e.line("\ts_mov_b64 exec, -1");
         e.line("\tv_mbcnt_lo_u32_b32 v%d, -1, 0", kVgprAcc0);
         e.line("\tv_mbcnt_hi_u32_b32 v%d, -1, v%d", kVgprAcc0, kVgprAcc0);              // lane id
@@ -1316,7 +1317,7 @@ static void emit_prologue(Gen &gen, Emitter &e, const Shape &sh, const Extents &
     e.line("\t.p2align 2");
     e.line(".Ltable:");
     for (int g = 0; g < n_blocks; ++g) e.line("\t.long .Lg%d-.Ltable", g);
-    e.line("\t.long .Lfunc_end-.Ltable");   // end of the last block
+    e.line("\t.long .Lfunc_end-.Ltable+%d", gap);   // where a block behind the last one would be
 
 }
 
@@ -1559,7 +1560,8 @@ int build_spec_plan(HostPlan &h, const sparsert_options &opt, std::string &err) 
         longest = std::max(longest, e.lines - before);
         block_bytes.push_back(e.bytes - bytes_before);
     }
-    if (const int gap = gap_between_blocks(e.bytes, sp.n_blocks)) {
+    const int gap = gap_between_blocks(e.bytes, sp.n_blocks);
+    if (gap) {
         char text[24];
         const int n = snprintf(text, sizeof(text), "\t.space %8d", gap);
         for (size_t at : gaps) e.s.replace(at, (size_t)n, text);
@@ -1571,7 +1573,7 @@ int build_spec_plan(HostPlan &h, const sparsert_options &opt, std::string &err) 
     const int prefetch_lines = !opt.spec_prefetch ? 0 : (int)std::min<int64_t>(32, (longest * 8 + 64 * 128 - 1) / (64 * 128));
     sp.prefetch_lines = prefetch_lines;
     Emitter head;
-    emit_prologue(gen, head, sh, ex, deal, prefetch_lines);
+    emit_prologue(gen, head, sh, ex, deal, prefetch_lines, gap);
     e.s.insert(0, head.s);
 
     if (const char *dump = getenv("SPARSERT_DUMP_ASM")) {

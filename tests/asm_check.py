@@ -102,7 +102,8 @@ def check(text: str, info: dict, esz: int, osz: int):
     # under a mask `length - 128 j > i * stride`; the loads must come in that order, each right after its
     # mask, their offsets must equal what has been subtracted from the length so far, and the
     # lines of one lane must not run into the next lane's
-    pf_sub, pf_stride, pf_masked, pf_loads = 0, None, False, 0
+    # the length is from block to block less what lies between two, so nothing behind a block's end is read
+    pf_sub, pf_stride, pf_masked, pf_loads, pf_between = 0, None, False, 0, 0
     for l in body[:first_block]:
         m = re.match(r"v_mul_u32_u24_e32 v4, (0x[0-9a-f]+|\d+), v4$", l)
         if m:
@@ -111,6 +112,8 @@ def check(text: str, info: dict, esz: int, osz: int):
             pf_masked = True
         elif re.match(r"s_sub_u32 s55, s55, 128$", l):
             pf_sub += 128
+        elif m := re.match(r"s_sub_u32 s55, s55, (0x[0-9a-f]+|\d+)$", l):
+            pf_between += _imm(m.group(1))
         elif l.startswith("global_load_dword"):
             m = re.match(r"global_load_dword v2, v4, s\[18:19\] offset:(\d+)$", l)
             if not m:
@@ -123,6 +126,10 @@ def check(text: str, info: dict, esz: int, osz: int):
             problems.append(f"prologue: exec changed inside the code prefetch: `{l}`")
     if pf_loads and (pf_stride is None or pf_stride < 128 * pf_loads):
         problems.append("prologue: the prefetch lines of neighbouring lanes overlap")
+    between = {int(l.split()[1]) for l in body if l.startswith(".space")}
+    end = next(int(l.partition("+")[2] or 0) for l in body[:first_block] if l.startswith(".long .Lfunc_end-.Ltable"))
+    if pf_loads and (between != {pf_between} or end != pf_between):
+        problems.append(f"prologue: the code prefetch takes blocks to be {pf_between} bytes apart, {end} behind the last one; they are {sorted(between)}")
     table = [l for l in body[:first_block] if l.startswith(".long .Lg")]
     n_blocks = sum(1 for l in body if re.match(r"\.Lg\d+:$", l))
     if len(table) != n_blocks:

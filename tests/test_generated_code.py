@@ -67,6 +67,16 @@ def test_code_prefetch_is_checked(tmp_path):
     assert any("not covered by its length mask" in p for p in asm_check.check(bad, info, 4, 4)[0])
 
 
+def test_code_prefetch_stops_at_the_end_of_its_block(tmp_path):
+    """Also where blocks are moved apart: what lies between them is never run."""
+    csr = synth.uniform_csr(1024, 1024, 0.9, 4)
+    text, info = _generated(csr, 832, tmp_path, spec_rows=54, spec_ksplit=8, spec_prefetch=1)
+    gap = {int(l.split()[1]) for l in text.splitlines() if ".space" in l}
+    assert len(gap) == 1 and min(gap) > 0 and asm_check.check(text, info, 4, 4)[0] == []
+    bad = text.replace("\ts_sub_u32 s55, s55, 0x%x\n" % min(gap), "", 1)
+    assert any("bytes apart" in p for p in asm_check.check(bad, info, 4, 4)[0])
+
+
 @pytest.mark.parametrize("N,vec,dtype", [(64, 2, np.float16), (130, 2, np.float16), (64, 4, np.int8), (260, 4, np.int8)])
 @pytest.mark.parametrize("ks", [1, 4])
 def test_packed_columns_stay_in_bounds(N, vec, dtype, ks, tmp_path):
