@@ -264,13 +264,22 @@ def graph_us(torch, fn, inner=20, replays=20):
     return e0.elapsed_time(e1) * 1e3 / (replays * inner)
 
 
+def traffic_bounds(fetch, write, factor, code):
+    """(least, most) bytes that left the L2s, of what the counters show.  FETCH_SIZE counts 128-byte data requests as 64
+    bytes but 64-byte instruction fetches in full, so scaling all of it is an upper bound.  How much of it is instructions
+    depends on how the plan deals its workgroups to the XCDs: every one of the eight L2s pulls all of the generated code or
+    a part of it, and a plan that prefetches brings it in through data requests.  All of it in every L2, as instructions,
+    gives the lower bound."""
+    instructions = min(fetch, 8.0 * code)
+    out = write * factor["WRITE_SIZE"]
+    return (instructions + (fetch - instructions) * factor["FETCH_SIZE"] + out, fetch * factor["FETCH_SIZE"] + out)
+
+
 def measure_traffic(args, layers, plan_path):
     """Bytes that leave the L2 caches per launch of every layer, from two rocprofv3 --pmc child
     runs of this script in --pmc-mode (FETCH_SIZE, then WRITE_SIZE; one counter set per run) with
     the plans of this run.  Each counter is scaled by what it reads for the 256 MiB device copy
-    that --pmc-mode issues first.  FETCH_SIZE counts 128-byte data requests as 64 bytes (the copy
-    factor is 2) but 64-byte instruction fetches in full, so the plainly scaled figure counts the
-    generated code twice; `refined` takes the code (once per XCD, eight XCDs) out before scaling.
+    that --pmc-mode issues first (traffic_bounds says what that leaves open).
     Returns None where the profiler is not available or a child run fails."""
     import csv
     import glob
@@ -311,19 +320,10 @@ def measure_traffic(args, layers, plan_path):
                 return None
             kib = {c: sum(vals[c][0][-10:]) / len(vals[c][0][-10:]) for c in counted}   # the last launches: steady state
             fetch, write = kib["FETCH_SIZE"] * 1024.0, kib["WRITE_SIZE"] * 1024.0
-            code = 8.0 * L.info["spec_code_bytes"]
-            # waves that prefetch their code bring most of it in through data requests, which the counter
-            # halves like any other: there the plain scaling is the estimate (an upper one: what still
-            # arrives as instruction fetches is counted in full)
-            split = code > 0 and fetch > code and not L.info.get("spec_prefetch")
-            refined = (code + (fetch - code) * factor["FETCH_SIZE"]) if split else fetch * factor["FETCH_SIZE"]
+            least, most = traffic_bounds(fetch, write, factor, L.info["spec_code_bytes"])
             res["layers"].append({"layer": L.case.name, "kernel": name,
-                                  "refined_how": "instruction fetches (8 x code, counted in full) taken out before scaling" if split
-                                                 else "scaled plainly",
-
                                   "fetch_counted_bytes": fetch, "write_counted_bytes": write,
-                                  "plain_scaled_bytes": fetch * factor["FETCH_SIZE"] + write * factor["WRITE_SIZE"],
-                                  "refined_bytes": refined + write * factor["WRITE_SIZE"]})
+                                  "least_bytes": least, "plain_scaled_bytes": most})
         return res
     except Exception as e:   # a profiler that is missing a counter, an unreadable file: no figure rather than no benchmark
         print(f"bench.py: traffic measurement skipped: {e}", file=sys.stderr)
@@ -622,7 +622,7 @@ def main():
         finally:
             os.unlink(f.name)
         if traffic_detail:
-            traffic = traffic_detail["layers"][dom]["refined_bytes"]
+            traffic = traffic_detail["layers"][dom]["plain_scaled_bytes"]   # the upper bound
     alg_all = sum(L.algorithmic_bytes for L in layers) / len(layers)
     roofline = {
         "bound": bound,
