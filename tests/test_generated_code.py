@@ -219,13 +219,14 @@ def _dealt(prologue, x, y, z):
     """(column tile, code block, problem) that the prologue computes for a workgroup of the launch."""
     s, scc = {"s2": x, "s3": y, "s52": z}, False
     value = lambda tok: s[tok] if tok in s else int(tok, 0)
-    ops = {"s_and_b32": lambda a, b: a & b, "s_lshr_b32": lambda a, b: a >> b, "s_mul_i32": lambda a, b: a * b & 0xFFFFFFFF, "s_min_u32": min,
-           "s_mul_hi_u32": lambda a, b: a * b >> 32, "s_add_u32": lambda a, b: a + b & 0xFFFFFFFF, "s_sub_u32": lambda a, b: a - b & 0xFFFFFFFF}
+    ops = {"s_and_b32": lambda a, b: (a & b, a & b != 0), "s_lshr_b32": lambda a, b: (a >> b, a >> b != 0), "s_min_u32": lambda a, b: (min(a, b), a <= b),
+           "s_add_u32": lambda a, b: (a + b & 0xFFFFFFFF, a + b > 0xFFFFFFFF), "s_sub_u32": lambda a, b: (a - b & 0xFFFFFFFF, a < b),
+           "s_mul_i32": lambda a, b: (a * b & 0xFFFFFFFF, scc), "s_mul_hi_u32": lambda a, b: (a * b >> 32, scc)}   # result, condition bit
     for l in prologue:
         op, _, rest = l.partition(" ")
         args = [a.strip() for a in rest.split(",")]
         if op in ops:
-            s[args[0]] = ops[op](value(args[1]), value(args[2]))
+            s[args[0]], scc = ops[op](value(args[1]), value(args[2]))
         elif op == "s_mov_b32":
             s[args[0]] = value(args[1])
         elif op == "s_cmp_eq_u32":

@@ -54,8 +54,9 @@ def test_many_tiles_are_dealt_once_each(tile, dtype):
         csr = _ints(rng, M, K, 0.2, dtype)
         B = rng.integers(-4, 5, size=(K, N)).astype(dtype)
         want = ref.spmm(M, K, N, csr.row_ptr, csr.col_idx, csr.vals, B)[0]
-        got, pad_ok, _ = run_spmm_strided(csr, np.stack([B, -B]), N, N + 32, **_opts(tile))
-        assert pad_ok and np.array_equal(got.astype(np.float64), np.stack([want, -want])), (M, K, N)
+        for ldc in (N + 32, (N + 127) // 64 * 64):   # the second: a multiple of 128 bytes for either type, with a gap behind N
+            got, pad_ok, _ = run_spmm_strided(csr, np.stack([B, -B]), N, ldc, **_opts(tile))
+            assert pad_ok and np.array_equal(got.astype(np.float64), np.stack([want, -want])), (M, K, N, ldc)
 
 
 @pytest.mark.parametrize("tile", [TILES[0], TILES[5]])
