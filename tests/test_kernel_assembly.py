@@ -40,6 +40,14 @@ def test_half_results_of_small_tiles_go_straight_to_memory(tmp_path):
     assert "ds_write" not in bodies["Li0ELi2ELi2ELi1ELi1ELi2ELi4"] and "ds_write" in bodies["Li0ELi2ELi2ELi2ELi2ELi2ELi4"]
 
 
+def test_half_results_stay_in_the_caches_for_the_next_layer(tmp_path):
+    """Only int32 results, which an element-wise kernel reads next, are stored with the hint that nothing reads them soon."""
+    bodies = re.findall(r"^_ZN8sparsert11mfma_kernelILi(\d)E\w+:.*?$(.*?)^\.Lfunc_end", _assembly("mfma.hip", tmp_path), re.S | re.M)
+    assert len(bodies) == 18
+    for dtype, body in bodies:
+        assert (re.search(r"buffer_store\S* .* nt\b", body) is not None) == (dtype == "1")
+
+
 def _pulled(M, K, N, ldb, esz, tm, tn, per):
     """Bytes of A and B, B in lines of 128 bytes, that the eight XCDs pull with the tiles in parts of `per` along M."""
     m_tiles, n_tiles = -(-M // tm), -(-N // tn)
