@@ -348,17 +348,22 @@ __global__ __launch_bounds__(WM *WN *kWave, mfma_waves_per_simd(WM *MF * 16, WN 
             uint32_t off = (uint32_t)(tile_m * TM + r0) * row_bytes + (uint32_t)column(n) * (uint32_t)sizeof(out_t);
             const bool columns = (n & -EPC) < a.N;
             const char *from = lds + r0 * PITCH + tid % CHUNKS * 16;
-            // Half results stay where they are for the layer that reads them next: stored as not to be read again, 3072 x 768 x 1024 alone
-            // takes 8.3 us instead of 8.6, but with 768 x 3072 x 1024 behind it 27.6 instead of 22.9 (three sets of operands taking turns: 25.8
-            // and 20.6).  Int32 results go through an element-wise kernel first, which does not mind (35 products each with one behind it:
-            // 0.995 times as fast); alone 35 products are 1.03 times faster for it, 1.1 with operands that no cache holds.
-            constexpr int kPolicy = DT == 0 ? 0 : 2;
+            auto store = [&](auto policy) {
 #pragma unroll
-            for (int r = 0; r < TM; r += ROWS, off += ROWS * row_bytes) {
-                const int4v v = *reinterpret_cast<const int4v *>(from + r * PITCH);
-                const bool stored = columns & (tile_m * TM + r + r0 < a.M) & (TM % ROWS == 0 || r + r0 < TM);
-                __builtin_amdgcn_raw_buffer_store_b128(v, rout, stored ? (int)off : kRefused, 0, kPolicy);
-            }
+                for (int r = 0; r < TM; r += ROWS, off += ROWS * row_bytes) {
+                    const int4v v = *reinterpret_cast<const int4v *>(from + r * PITCH);
+                    const bool stored = columns & (tile_m * TM + r + r0 < a.M) & (TM % ROWS == 0 || r + r0 < TM);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, rout, stored ? (int)off : kRefused, 0, policy);
+                }
+            };
+            // Whole lines of half results go through the L2 on their way (sc1), so that the launch's end has nothing left to write back, and
+            // the caches behind it keep them for the layer that reads them next.  3072 x 768 x 1024, operands taking turns: plain 8.36 us, sc1
+            // 7.83, not to be kept (nt) 8.07; with 768 x 3072 x 1024 behind it 20.7, 20.1 and 25.8, two square layers 1024 x 1024 x 4096
+            // 23.4, 22.2 and 23.5.  39 drawn products: 1.03 times faster than plain; 26 whose lines are not whole up to 0.87 times, so those stay plain.
+            // Int32 results are nt: an element-wise kernel reads them first, which takes as long behind it as behind plain stores
+            // (35 products, to 0.5 %); alone they are 1.03 times faster for it, 1.1 with operands that no cache holds.
+            if (lines) store(std::integral_constant<int, DT == 0 ? 16 : 2>());
+            else store(std::integral_constant<int, 0>());
             return;
         }
     }

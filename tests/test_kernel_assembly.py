@@ -41,11 +41,15 @@ def test_half_results_of_small_tiles_go_straight_to_memory(tmp_path):
 
 
 def test_half_results_stay_in_the_caches_for_the_next_layer(tmp_path):
-    """Only int32 results, which an element-wise kernel reads next, are stored with the hint that nothing reads them soon."""
+    """Only int32 results, which an element-wise kernel reads next, are stored with the hint that nothing reads them soon;
+    whole lines of half results go through to the caches behind the L2, others are stored plainly."""
     bodies = re.findall(r"^_ZN8sparsert11mfma_kernelILi(\d)E\w+:.*?$(.*?)^\.Lfunc_end", _assembly("mfma.hip", tmp_path), re.S | re.M)
     assert len(bodies) == 18
     for dtype, body in bodies:
-        assert (re.search(r"buffer_store\S* .* nt\b", body) is not None) == (dtype == "1")
+        stores = re.findall(r"buffer_store\S* (.*)", body)
+        assert any(re.search(r"\bnt\b", l) for l in stores) == (dtype == "1")
+        assert any(re.search(r"\bsc1\b", l) for l in stores) == (dtype == "0" and "ds_write" in body)
+        assert any(not re.search(r"\b(nt|sc1)\b", l) for l in stores)
 
 
 def _pulled(M, K, N, ldb, esz, tm, tn, per):
