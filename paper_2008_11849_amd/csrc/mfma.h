@@ -96,7 +96,9 @@ inline int mfma_rows_per_part(const MfmaConfig &c, int64_t M, int64_t K, int64_t
 
 // Time of an M x K x N product with this tile, from the constants above: they reproduce 122 measured shapes
 // (M 64 ... 4000, K 64 ... 3867, N 49 ... 4096, both storage types) to about 9 %, and the tile they choose is
-// within 1 % of the best one on average, 10 % at most.
+// within 1 % of the best one on average, 10 % at most.  That was before results left through LDS and tiles were dealt in
+// blocks; the kernel as it is: 10 % root mean square over 700 drawn products for which this and the generated kernel's first estimate are within
+// 0.45 to 1.5 of each other.
 inline double mfma_microseconds(const MfmaConfig &c, int64_t M, int64_t K, int64_t N, int64_t batch, int elem_size, int out_size) {
     const int64_t slab = (int64_t)c.steps * mfma_step(elem_size), slabs = (K + slab - 1) / slab;
     const int64_t wgs = (M + c.tm - 1) / c.tm * ((N + c.tn - 1) / c.tn) * batch;

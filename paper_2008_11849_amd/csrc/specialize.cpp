@@ -1423,7 +1423,8 @@ static int mfma_best_tile(const HostPlan &h, double *microseconds) {
 // zeros, 50 of them with fitted rows: 15 % root mean square, and the kernel that this estimate and mfma_microseconds
 // choose takes 0.9 % more than the faster of the two on average (8 times the slower one, 1.33 times at most).  The
 // fitted rows in the formula: 15 % as well, but 2.2 % (12 times, 1.47), because the products whose choice changes
-// take longer than either figure says.
+// take longer than either figure says.  Those products were timed in launch order.  As workgroups are dealt now: 18 % (int8) and 20 %
+// (half) over 700 drawn products near the line (this and mfma_microseconds within 0.45 to 1.5 of each other).
 static double generated_microseconds(const HostPlan &h) {
     const double tiles = (double)((h.N + kWave - 1) / kWave) * h.batch, density = (double)h.nnz / ((double)h.M * h.K);
     const int ks = h.K >= 512 ? 8 : 1;
@@ -1434,9 +1435,11 @@ static double generated_microseconds(const HostPlan &h) {
 
 // Second estimates of both, which look at more than the two above: a product that they put clearly on the generated
 // kernel's side stays there.  Fitted, 9 % and 15 % root mean square, to 840 half and int8 products (M, K and N up to 4096,
-// 80 % to 98 % zeros, uniform and skewed rows, odd sizes, batches), each timed with both kernels.
+// 80 % to 98 % zeros, uniform and skewed rows, odd sizes, batches), each timed with both kernels; with the kernels as they are now 9 %
+// and 14 % (int8) to 16 % (half) over those 700.
 // The matrix-core plan's time: the L2s fill up slower than the slabs are multiplied where the tiles that an XCD has in
-// hand share little; rows of C that do not begin on 8 bytes are stored in pieces, rows of B that do not begin on 4 bytes
+// hand share little (in the better one of the two simple orders of tiles; the order the kernel takes, mfma_rows_per_part, shares
+// as much or more); rows of C that do not begin on 8 bytes are stored in pieces, rows of B that do not begin on 4 bytes
 // are copied in pieces; and a large C leaves the caches.
 static double matrix_core_microseconds(const HostPlan &h, int tile, double first_estimate) {
     static const double fit[2][5] = {{0.946, 0.326, 0.179, 0.0267, 0.223}, {0.952, 0.356, 0.0306, 0.0557, 0.0228}};   // half, int8
@@ -1502,6 +1505,8 @@ int mfma_preferred(const HostPlan &h, const sparsert_options &opt, const void *v
     // 1.1: of the 562 of those products that the first estimates give to the matrix cores, those more than 5 % slower there than generated
     // fall from 19 (1.57 times at most: half 1384 x 128 x 3489, batch 4, at 85 %, 30.0 against 19.1 us) to 8 (1.25), and
     // two that were faster there by 7 % and 8 % are given up; a factor of 1 gives up ten, 1.32 times faster at most.
+    // (With the kernels of that time.  Now, of the 700 near the line both tests give 448 to the matrix cores, 57 of them more than 5 % slower there, 1.32
+    // times at most; of the rest 49 would be more than 5 % faster there, 2.2 times at most; all in all 3.1 % over the faster of the two each.)
     // (Where no code is generated the row-walk kernel would take over, which is further behind.)
     if (h.nnz <= kAutoSpecNnz && spec_available() && matrix_core_microseconds(h, tile, t) > 1.1 * generated_shape_microseconds(h, opt)) return -1;
     return all_finite(h, vals) ? tile : -1;

@@ -22,8 +22,10 @@ struct StagedRows {
 };
 
 // The estimates below are fits to 230 products drawn from M, K <= 4096, N from 49 to 4096 and 80 % to 98 %
-// zeros (126 fp32, the rest half and int8; a quarter of them with skewed rows): 8 % to 10 % root mean square
-// for the staged kernel, 22 % for the plain one.  Microseconds.
+// zeros (126 fp32, the rest half and int8; a quarter of them with skewed rows), timed with steps of four pairs and a v_dot4
+// per row and column.  Microseconds.  Against the kernels as they are (700 products drawn from the same ranges whose first two estimates
+// are within 0.35 to 1.5 of each other, each timed with both kernels), root mean square: staged fp32 12 % to 20 %, half 10 %,
+// int8 30 % (1.24 times too long), plain 22 % to 25 %.
 
 // Staged: a start, then per round of workgroups a fixed cost per chunk (barrier, first loads), the copied
 // bytes and the operands read from LDS; the longest row as one wave's serial
@@ -57,7 +59,8 @@ inline double plain_rows_microseconds(const HostPlan &h, int32_t longest) {
 }
 
 // Second estimates of both, fitted to 5303 products of the same ranges that the first ones give to the staged kernel, each
-// timed with both kernels: 6 % and 13 % root mean square.  The plain kernel's loads cost by columns per lane, and more where
+// timed with both kernels, also before the steps of eight: 6 % and 13 % root mean square then; over the 700 above staged fp32 7 % to 15 %,
+// half 11 %, int8 32 % (1.27 times too long), plain 13 % to 15 %.  The plain kernel's loads cost by columns per lane, and more where
 // rows of B do not begin on 64 bytes; every wave costs something of its own.
 inline bool staged_rows_confirmed(const HostPlan &h, const StagedRows &s, int32_t longest) {
     static const double staged[5][6] = {{2.26, 0.81, 5.68, 3.64, 14.1, 0.219}, {2.41, 1.40, 2.92, 3.88, 7.12, 0.183}, {2.57, 0.847, 3.68, 2.82, 4.91, 0.176},
@@ -86,7 +89,9 @@ inline bool staged_rows_fits(const HostPlan &h, const StagedRows &s) {
 // kernel's time over the products above), so it is taken where it is estimated to need less than 0.8 of the
 // plain kernel's time and the second estimates do not contradict that.  Of 5303 drawn products that pass the first test
 // 5138 pass the second; they gain 1.51 times on average, 133 lose more than 5 % (0.80 times the plain kernel's speed
-// at worst; 263 and 0.62 with the first test alone), and 8 that gained more than 5 % are given up.
+// at worst; 263 and 0.62 with the first test alone), and 8 that gained more than 5 % are given up.  (With the kernel of that time.
+// The present one loses less: of the 700, 252 are taken, two of them 11 % slower at most; and of the rest 152 would gain more
+// than 5 %, 74 of them int8, 31 half, 1.31 times on average and 3.4 times at most, fp32 with skewed rows.)
 inline StagedRows staged_rows_shape(const HostPlan &h) {
     StagedRows best;
     if (h.kernel != SPARSERT_KERNEL_ROWS || h.conv || h.plain_rows) return best;

@@ -6,7 +6,8 @@
 // rows of B into LDS once, chunk by chunk (two buffers, the next chunk travels while one is worked on), for
 // all of its 64 or 128 rows of A, and every nonzero reads its operand there.  LDS, 128 bytes per clock, is
 // the bound: for the same product 87 us of operand reads (49 of 64 lanes own columns), 5 % of pairs that
-// only fill up, 25 us of copies into it; measured 137 us.  Half and int8 move fewer bytes per nonzero and
+// only fill up, and copies, 3.2 MB per compute unit: 10 us as writes to LDS, 25 us on the vector-memory path
+// beside them; measured 137 us.  Half and int8 move fewer bytes per nonzero and
 // are bound by the instructions per nonzero and by the waits between them (2048 x 2048 at 95 %, 784 columns: half
 // 39.2 us in the plain kernel, 25.9 us here in fours; int8 41.0 us, 24.7 us in fours with a v_dot4 per row and column).
 //
