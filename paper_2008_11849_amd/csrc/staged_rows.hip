@@ -4,10 +4,12 @@
 // every nonzero and column tile, and that path delivers about 30 bytes per clock and compute unit: on
 // 4096 x 4096 at 90 % with 784 columns it was all of the 287 us.  Here a workgroup copies the column tile's
 // rows of B into LDS once, chunk by chunk (two buffers, the next chunk travels while one is worked on), for
-// all of its 64 or 128 rows of A, and every nonzero reads its operand there.  LDS, 128 bytes per clock, is
-// the bound: for the same product 87 us of operand reads (49 of 64 lanes own columns), 5 % of pairs that
-// only fill up, and copies, 3.2 MB per compute unit: 10 us as writes to LDS, 25 us on the vector-memory path
-// beside them; measured 137 us.  Half and int8 move fewer bytes per nonzero and
+// all of its 64 or 128 rows of A, and every nonzero reads its operand there.  A read of 8 or
+// 16 bytes per lane takes LDS 2.2 or 4.1 clocks (250 bytes per clock; one of 4 bytes 2.3), so for the same product (49 of 64
+// lanes own columns, 5 % of pairs only fill up) operand reads are 46 us, multiply-adds and addresses 50 us of every SIMD, and copies,
+// 3.2 MB per compute unit, 18 us as writes to LDS and 25 us on the vector-memory path.  No one of them is the bound: without
+// multiply-adds, reads or copies 106 to 118 us are left of 124, because the parts of a wave's step follow each other and
+// the waves meet at every chunk's end.  Half and int8 move fewer bytes per nonzero and
 // are bound by the instructions per nonzero and by the waits between them (2048 x 2048 at 95 %, 784 columns: half
 // 39.2 us in the plain kernel, 25.9 us here in fours; int8 41.0 us, 24.7 us in fours with a v_dot4 per row and column).
 //
@@ -50,16 +52,29 @@ struct StagedShortArgs : StagedArgs {};   // of plans whose rows have few pairs 
 // Bytes of one of the two LDS buffers: a chunk's rows and one row of zeros, in whole copies.
 __host__ __device__ constexpr int staged_buffer_bytes(int chunk, int pitch) { return ((chunk + 1) * pitch + 1023) & ~1023; }
 
+// A value of the stream in a vector register.  A v_fma_f32 with a scalar operand keeps its SIMD for four clocks, one with vector
+// registers only (or a literal) for two where a second wave takes turns with it (4.2 and 2.2 measured with two to eight waves), so a
+// move of four clocks pays from three multiply-adds on: 4096 x 4096 x 784 at 90 % 135.9 -> 124.3 us, 3000 x 2048 x 784, batch 4, at
+// 84.7 % 260 -> 232 us; at 98 % (4096 x 4096 x 784, 63.4 us) nothing changes.  Half stays with the scalar operand: its products widen
+// the operand as they go (v_fma_mix_f32), four clocks in any case.  (Assembly: the compiler would fold the move away.)
+__device__ __forceinline__ float in_vector(uint32_t bits) {
+    float f;
+    asm("v_mov_b32 %0, %1" : "=v"(f) : "s"(bits));
+    return f;
+}
+
 // Operands, multiply-adds and results of one storage type at V columns per lane.
 template <typename T, int V> struct StagedOps {
     typedef float acc_t;
     typedef T out_t;
     typedef T opd_t __attribute__((ext_vector_type(V)));
     static __device__ __forceinline__ void mad2(float (&acc)[V], uint32_t w0, uint32_t w1, const opd_t &b0, const opd_t &b1) {
+        float f0 = __uint_as_float(w0), f1 = __uint_as_float(w1);
+        if constexpr (std::is_same<T, float>::value) { f0 = in_vector(w0); f1 = in_vector(w1); }
 #pragma unroll
-        for (int j = 0; j < V; ++j) acc[j] = __builtin_fmaf(__uint_as_float(w0), (float)b0[j], acc[j]);
+        for (int j = 0; j < V; ++j) acc[j] = __builtin_fmaf(f0, (float)b0[j], acc[j]);
 #pragma unroll
-        for (int j = 0; j < V; ++j) acc[j] = __builtin_fmaf(__uint_as_float(w1), (float)b1[j], acc[j]);
+        for (int j = 0; j < V; ++j) acc[j] = __builtin_fmaf(f1, (float)b1[j], acc[j]);
     }
 };
 // The four packed columns stay in their dword.  Two operand rows are interleaved, so that one v_dot4 does a column of both;
