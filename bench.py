@@ -118,7 +118,7 @@ class Layer:
     def plan_options(self):
         """The options that make this plan again."""
         opts = {k: self.info[k] for k in self.PLAN_KEYS}
-        if self.info["staged_vec"]:   # the LDS-staged row-walk kernel: taken where these are not set
+        if self.info["staged_vec"] or self.info["blocked_rows"]:   # row-walk kernels that are taken where these are not set
             opts["vec"] = opts["split_threshold"] = 0
         return opts
 

@@ -65,8 +65,9 @@ typedef enum sparsert_kernel {
                                   problem (EUNSUPPORTED / ECOMPILE) */
     SPARSERT_KERNEL_ROWS = 1,  /* a fixed kernel that walks the rows' nonzeros: one wave per row, B read straight from
                                   L2/HBM.  SpMM plans with none of vec, split_threshold and natural_order set run a
-                                  variant that copies B to LDS where that is estimated to be faster
-                                  (SPARSERT_INFO_STAGED_VEC); setting one of them keeps the plain kernel */
+                                  variant that copies B to LDS (SPARSERT_INFO_STAGED_VEC) or, fp32, one that keeps a
+                                  block of rows in registers (SPARSERT_INFO_BLOCKED_ROWS) where that is estimated to
+                                  be faster; setting one of them keeps the plain kernel */
     SPARSERT_KERNEL_SPEC = 2   /* per-matrix generated gfx950 code with the nonzeros of A as
                                   instruction constants (Section 3.5); with spec_mode = SPARSERT_SPEC_MFMA the
                                   matrix-core kernel, for which nothing is generated */
@@ -242,7 +243,7 @@ int sparsert_conv3x3(const sparsert_plan *plan, const void *X_dev, void *Y_dev, 
  */
 #define SPARSERT_TUNE_MAX 64
 typedef struct sparsert_tune_entry {
-    /* the options that make the plan again; vec and split_threshold are 0 for the LDS-staged row-walk kernel */
+    /* the options that make the plan again; vec and split_threshold are 0 for the LDS-staged and the blocked row-walk kernel */
     int32_t kernel, vec, split_threshold, spec_mode, spec_rows, spec_tiles, spec_ksplit, spec_lanes, spec_swizzle, spec_vec;
     float microseconds;      /* per launch, back-to-back launches of this plan; negative if the candidate failed */
     float cold_microseconds; /* per launch when a cache-displacing fill runs before every launch (the fill's own
@@ -355,9 +356,10 @@ enum {
     SPARSERT_INFO_LDB,            /* elements between consecutive rows of B (N unless options.ldb) */
     SPARSERT_INFO_LDC,            /* elements between consecutive rows of C (N unless options.ldc) */
     SPARSERT_INFO_SPEC_PREFETCH,  /* SPEC plans: 128-byte lines of its block's code every lane touches ahead (0 = no prefetch) */
-    SPARSERT_INFO_STAGED_VEC,     /* row-walk plans that run the LDS-staged kernel: its columns per lane; 0 = the plan runs
-                                     the plain kernel, which VEC ... N_WG_ROWS describe */
+    SPARSERT_INFO_STAGED_VEC,     /* row-walk plans that run the LDS-staged kernel: its columns per lane; 0 = the plan runs the
+                                     plain kernel, which VEC ... N_WG_ROWS describe, or the blocked one */
     SPARSERT_INFO_STAGED_ROWS,    /* ... and its rows per wave */
+    SPARSERT_INFO_BLOCKED_ROWS,   /* row-walk plans that run the kernel with a block of rows in registers: rows per block; else 0 */
     SPARSERT_INFO_COUNT = 48      /* remaining entries are zero */
 };
 

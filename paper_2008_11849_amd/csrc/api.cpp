@@ -129,6 +129,7 @@ int sparsert_plan_export(const sparsert_plan *plan, int32_t field, void *buf, si
             info[SPARSERT_INFO_STAGED_VEC] = s.V;
             info[SPARSERT_INFO_STAGED_ROWS] = s.rows_per_wave;
         }
+        info[SPARSERT_INFO_BLOCKED_ROWS] = sparsert::blocked_rows_shape(h).rows;
         src = info; bytes = sizeof(info);
         break;
     case SPARSERT_FIELD_ROW_NNZ: vec32(h.row_nnz); break;
@@ -148,6 +149,8 @@ int sparsert_plan_export(const sparsert_plan *plan, int32_t field, void *buf, si
     case SPARSERT_FIELD_KERNEL_NAME:
         if (h.kernel == SPARSERT_KERNEL_SPEC) {
             name = h.spec.symbol;
+        } else if (const sparsert::BlockedRows b = sparsert::blocked_rows_shape(h); b.rows) {
+            name = "void sparsert::blocked_rows_kernel<" + std::to_string(b.parts) + ">(sparsert::BlockedArgs)";
         } else if (const sparsert::StagedRows s = sparsert::staged_rows_shape(h); s.V) {
             const std::string shape = "Li" + std::to_string(s.V) + "ELi" + std::to_string(s.rows_per_wave) + "EEEvNS_10StagedArgsE";
             name = h.dtype == SPARSERT_F16 ? "_ZN8sparsert18staged_rows_kernelIDF16_" + shape

@@ -387,6 +387,15 @@ int upload_plan(const HostPlan &h, DevicePlan &d, std::string &err) {
     HIP_TRY(hipGetDevice(&d.device));
     if (int rc = to_device(h.p_row_ptr.data(), h.p_row_ptr.size(), &d.p_row_ptr, err)) return rc;
     if (int rc = to_device(h.perm.data(), h.perm.size(), &d.perm, err)) return rc;
+    if (const BlockedRows s = blocked_rows_shape(h); s.rows) {
+        BlockedPack pack;
+        blocked_rows_pack(h, s, pack);
+        if (int rc = to_device(pack.stream.data(), pack.stream.size(), &d.stream, err)) return rc;
+        d.staged_stream_bytes = pack.stream.size() * sizeof(uint32_t);
+        if (int rc = to_device(pack.starts.data(), pack.starts.size(), &d.staged_starts, err)) return rc;
+        if (int rc = to_device(pack.rows.data(), pack.rows.size(), &d.staged_rows, err)) return rc;
+        return prepare_blocked_rows(h, s, d, err);
+    }
     if (staged_rows_shape(h).V) {
         StagedPack pack;
         staged_rows_pack(h, pack);

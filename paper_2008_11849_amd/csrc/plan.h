@@ -84,7 +84,7 @@ struct DevicePlan {
     uint32_t *stream = nullptr;
     int32_t *conv_seg = nullptr;
     int32_t *segments = nullptr;
-    uint8_t *staged_counts = nullptr;   // staged row-walk plans (staged_rows.hip)
+    uint8_t *staged_counts = nullptr;   // staged row-walk plans (staged_rows.hip); the next three also blocked ones (blocked_rows.hip)
     size_t staged_stream_bytes = 0;
     int32_t *staged_starts = nullptr, *staged_rows = nullptr;
     int32_t *inv_perm = nullptr;    // MFMA plans
@@ -150,6 +150,14 @@ struct StagedPack {
 };
 void staged_rows_pack(const HostPlan &h, StagedPack &out);   // (pack.cpp)
 int prepare_staged_rows(const HostPlan &h, DevicePlan &d, std::string &err);   // fills d.launch
+// Row-walk kernel that keeps a block of rows in registers (blocked_rows.hip); its shape: blocked_rows.h.
+struct BlockedRows;
+struct BlockedPack {
+    std::vector<uint32_t> stream;
+    std::vector<int32_t> starts, rows;
+};
+void blocked_rows_pack(const HostPlan &h, const BlockedRows &s, BlockedPack &out);   // (pack.cpp)
+int prepare_blocked_rows(const HostPlan &h, const BlockedRows &s, DevicePlan &d, std::string &err);   // fills d.launch
 // Matrix-core executor (mfma.hip).
 void mfma_pack(const HostPlan &h, std::vector<uint8_t> &out);   // (pack.cpp)
 int prepare_mfma(const HostPlan &h, DevicePlan &d, std::string &err);   // fills d.launch

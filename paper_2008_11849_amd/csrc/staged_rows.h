@@ -1,8 +1,10 @@
-// Which plans take the staged row-walk kernel (staged_rows.hip), and in what shape.  Host code only.
+// Which plans take the staged row-walk kernel (staged_rows.hip) or the blocked one (blocked_rows.hip), and the shape of the staged one.
+// Host code only.
 #pragma once
 #include <algorithm>
 #include <cstdint>
 
+#include "blocked_rows.h"
 #include "plan.h"
 
 namespace sparsert {
@@ -62,18 +64,23 @@ inline double plain_rows_microseconds(const HostPlan &h, int32_t longest) {
 // timed with both kernels, also before the steps of eight: 6 % and 13 % root mean square then; over the 700 above staged fp32 7 % to 15 %,
 // half 11 %, int8 32 % (1.27 times too long), plain 13 % to 15 %.  The plain kernel's loads cost by columns per lane, and more where
 // rows of B do not begin on 64 bytes; every wave costs something of its own.
-inline bool staged_rows_confirmed(const HostPlan &h, const StagedRows &s, int32_t longest) {
-    static const double staged[5][6] = {{2.26, 0.81, 5.68, 3.64, 14.1, 0.219}, {2.41, 1.40, 2.92, 3.88, 7.12, 0.183}, {2.57, 0.847, 3.68, 2.82, 4.91, 0.176},
-                                        {2.23, 0.984, 1.70, 5.78, 11.0, 0.275}, {2.54, 0.803, 4.89, 14.9, 10.9, 0.170}};
+inline double staged_rows_microseconds_again(const HostPlan &h, const StagedRows &s, int32_t longest) {
+    static const double fit[5][6] = {{2.26, 0.81, 5.68, 3.64, 14.1, 0.219}, {2.41, 1.40, 2.92, 3.88, 7.12, 0.183}, {2.57, 0.847, 3.68, 2.82, 4.91, 0.176},
+                                     {2.23, 0.984, 1.70, 5.78, 11.0, 0.275}, {2.54, 0.803, 4.89, 14.9, 10.9, 0.170}};
+    return staged_rows_microseconds(h, s, longest, fit);
+}
+inline double plain_rows_microseconds_again(const HostPlan &h, int32_t longest) {
     static const double plain[3][9] = {{1.84, 0.856, 2.71, 3.09, 0.00, 0.167, 2.77, 16.1, 0.0412},    // fp32: launch, loads at 1, 2, 4, 8 columns per lane,
                                        {1.69, 0.760, 0.887, 2.67, 3.28, 0.176, 2.81, 17.8, 0.0},      // half  off 64 bytes, the longest chain, waves, results
                                        {2.04, 0.754, 0.00, 1.39, 0.00, 0.138, 2.33, 17.9, 0.062}};    // int8
     const double *f = plain[h.dtype == SPARSERT_F32 ? 0 : h.dtype == SPARSERT_F16 ? 1 : 2];
     const double chain = longest < h.split_threshold ? longest : longest / (double)kGy, loads = 1e-5 * (double)h.nnz * h.n_tiles * h.batch;
     const int v = h.vec == 1 ? 1 : h.vec == 2 ? 2 : h.vec == 4 ? 3 : 4;
-    const double t = f[0] + loads * (f[v] + ((int64_t)h.ldb * h.elem_size() % 64 ? f[5] : 0.0)) + 1e-2 * f[6] * chain
-                   + 1e-5 * f[7] * h.M * h.n_tiles * (double)h.batch + 1e-6 * f[8] * h.M * h.N * (double)h.batch * h.out_elem_size();
-    return staged_rows_microseconds(h, s, longest, staged) < t + 1.4;   // (what the two are off by at 10 to 20 us)
+    return f[0] + loads * (f[v] + ((int64_t)h.ldb * h.elem_size() % 64 ? f[5] : 0.0)) + 1e-2 * f[6] * chain
+         + 1e-5 * f[7] * h.M * h.n_tiles * (double)h.batch + 1e-6 * f[8] * h.M * h.N * (double)h.batch * h.out_elem_size();
+}
+inline bool staged_rows_confirmed(const HostPlan &h, const StagedRows &s, int32_t longest) {
+    return staged_rows_microseconds_again(h, s, longest) < plain_rows_microseconds_again(h, longest) + 1.4;   // (what the two are off by at 10 to 20 us)
 }
 
 // What the kernel's addressing holds: the pair stream, with at most one filler per row and chunk and the padding
@@ -92,14 +99,11 @@ inline bool staged_rows_fits(const HostPlan &h, const StagedRows &s) {
 // at worst; 263 and 0.62 with the first test alone), and 8 that gained more than 5 % are given up.  (With the kernel of that time.
 // The present one loses less: of the 700, 252 are taken, two of them 11 % slower at most; and of the rest 152 would gain more
 // than 5 %, 74 of them int8, 31 half, 1.31 times on average and 3.4 times at most, fp32 with skewed rows.)
-inline StagedRows staged_rows_shape(const HostPlan &h) {
+inline StagedRows staged_rows_candidate(const HostPlan &h, int32_t longest) {
     StagedRows best;
-    if (h.kernel != SPARSERT_KERNEL_ROWS || h.conv || h.plain_rows) return best;
     const int esz = h.elem_size();
     // 4-byte accesses past the operand's end are dropped whole: the copies need rows that end on 4 bytes.
     if ((int64_t)h.ldb * esz % 4 || (int64_t)h.N * esz % 4 || (int64_t)h.K * h.ldb * esz >= (1ll << 31)) return best;
-    int32_t longest = 0;
-    for (int32_t i = 0; i < h.M; ++i) longest = std::max(longest, h.p_row_ptr[i + 1] - h.p_row_ptr[i]);
     static const int shapes[3][2] = {{4, 4}, {2, 4}, {2, 8}};   // V, rows per wave; the last two: fp32 only
     for (int i = 0; i < (esz == 4 ? 3 : 1); ++i) {
         StagedRows s;
@@ -126,6 +130,36 @@ inline StagedRows staged_rows_shape(const HostPlan &h) {
     // 4096 x 3072 x 516 at 92.4 % (8.8) 73.7 and 72.1.  Half and int8 lose nothing with as few as 5.4 (0.5 % within the noise).
     best.short_shares = best.V && esz == 4 && (int64_t)h.nnz < 8 * (int64_t)h.M * best.chunks;
     return best;
+}
+
+// ---- the kernel of a row-walk plan: blocked, staged, or neither.
+struct RowsChoice { StagedRows staged; BlockedRows blocked; };
+
+// The blocked kernel is held against the one of the other two that the rules above choose, both by estimates.  60 fp32 products drawn from
+// M, K <= 4096, N from 49 to 4096, mostly 80 % to 98 % zeros, a third with skewed rows, were timed with both: it takes 24 of them, all faster
+// for it (1.38 times on average, 2.9 at most: 2816 x 630 x 128 at 84 %, skewed, 33.6 -> 11.5 us), and leaves eight that would gain 5 to 40 %, four
+// of them with skewed rows, which the plain kernel's estimate makes too little of.  Of ten within 0.77 to 0.97 of the staged kernel's estimate
+// five gain 5 to 19 % and one loses 10 %; below 0.77 none of fourteen loses.  (The staged estimate leaves its longest row
+// out here: a single long one, which it counts in full, would make up for what is missing to 0.77.)  The plain kernel's estimate is further off, but where it is
+// above 15 us what it leaves out makes that kernel slower.
+inline RowsChoice rows_choice(const HostPlan &h) {
+    RowsChoice c;
+    if (h.kernel != SPARSERT_KERNEL_ROWS || h.conv || h.plain_rows) return c;
+    int32_t longest = 0;
+    for (int32_t i = 0; i < h.M; ++i) longest = std::max(longest, h.p_row_ptr[i + 1] - h.p_row_ptr[i]);
+    c.staged = staged_rows_candidate(h, longest);
+    c.blocked = blocked_rows_candidate(h);
+    if (c.blocked.rows == 0) return c;
+    const double limit = c.staged.V ? 0.77 * staged_rows_microseconds_again(h, c.staged, 0) : 0.9 * plain_rows_microseconds_again(h, longest);
+    if (c.blocked.microseconds < limit) c.staged.V = 0;
+    else c.blocked.rows = 0;
+    return c;
+}
+inline StagedRows staged_rows_shape(const HostPlan &h) { return rows_choice(h).staged; }
+inline BlockedRows blocked_rows_shape(const HostPlan &h) {
+    BlockedRows s = rows_choice(h).blocked;
+    if (s.rows) s.per_part = blocked_rows_per_part(h, s);
+    return s;
 }
 
 }  // namespace sparsert

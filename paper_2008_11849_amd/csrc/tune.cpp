@@ -174,7 +174,8 @@ static int tune_impl(const int32_t *row_ptr, const int32_t *col_idx, const void 
         if (!report || report->count >= SPARSERT_TUNE_MAX) return;
         sparsert_tune_entry &t = report->entries[report->count++];
         const sparsert::HostPlan &h = p->host;
-        const bool staged = sparsert::staged_rows_shape(h).V != 0;   // taken where these two are not set
+        const sparsert::RowsChoice rows = sparsert::rows_choice(h);
+        const bool staged = rows.staged.V || rows.blocked.rows;   // taken where these two are not set
         t.kernel = h.kernel; t.vec = staged ? 0 : h.vec; t.split_threshold = staged ? 0 : h.split_threshold;
         t.spec_mode = h.spec.mode; t.spec_rows = h.spec.rows_per_group; t.spec_tiles = h.kernel == SPARSERT_KERNEL_SPEC ? h.spec.tiles_per_wg : 0;
         t.spec_ksplit = h.kernel == SPARSERT_KERNEL_SPEC ? h.spec.ksplit : 0;

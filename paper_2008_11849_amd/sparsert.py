@@ -27,7 +27,8 @@ INFO_NAMES = ["M", "K", "N", "nnz", "dtype", "conv", "Cin", "H", "W", "kernel", 
               "lanes_per_tile", "n_tiles", "gy", "split_threshold", "n_split", "n_wg_rows",
               "n_bins", "spec_rows", "spec_groups", "spec_depth", "spec_code_bytes",
               "spec_tiles", "spec_mode", "spec_lds_bytes", "spec_ksplit", "natural_order", "spec_lanes", "spec_swizzle", "batch", "spec_vec",
-              "ldb", "ldc", "spec_prefetch", "staged_vec", "staged_rows"]
+              "ldb", "ldc", "spec_prefetch", "staged_vec", "staged_rows",
+              "blocked_rows"]
 INFO_COUNT = 48
 
 EXPORTED = ["sparsert_inspect", "sparsert_tune", "sparsert_spmm", "sparsert_conv3x3", "sparsert_compare_outputs", "sparsert_compare_outputs_static", "sparsert_plan_export",
