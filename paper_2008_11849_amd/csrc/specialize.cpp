@@ -1152,6 +1152,22 @@ static int gap_between_blocks(int64_t code_bytes, int64_t blocks) {
     return (int)(kBehind - off + 3) / 4 * 4;
 }
 
+// Does a plan with nothing set touch its code ahead (emit_prologue)?  It pays where the plans that run in between have displaced the
+// code from the L2s and a block is long: 1021 x 1027 x 771, skewed, at 90 %, four plans taking turns, 8.83 us without and 7.86 with;
+// 3072 x 768 x 1024 at 95 % 9.99 and 9.72; 2314 x 520 x 688 at 86 % 10.8 and 9.0.  It costs where one plan runs alone and the
+// code is still there: 6.75 us without and 7.14 with, 8.81 and 9.19, 8.10 and 8.55.  The limits on batch, K and nonzeros to a row of B were
+// set on 192 products and convolutions (the rule takes 43) and tried on 27 others that it takes: plans taking turns 0.925 times the
+// time on average, two of the 27 slower (817 x 2176 x 1233 at 95.5 % 1.041, 2944 x 576 x 2880 at 94 % 1.017); one
+// plan alone 1.017 on average and 1.106 at most.  A batch shares the code among its images but each image's waves touch it again
+// (3229 x 256 x 1987, batch 4, 44.6 us without and 48.1 with); a wave with many rows of B to fetch has its loads queue behind the
+// touches (744 x 4076 x 3587 48.6 and 52.0); and few nonzeros to a row leave the time in the fetches (1664 x 2112 x 1405 at 97.6 % 21.0 and 21.9).
+static bool prefetch_pays(const HostPlan &h, const sparsert_options &opt, const SpecPlan &sp, int64_t code_bytes) {
+    if (sp.mode != SPARSERT_SPEC_DIRECT || opt.spec_mode || opt.spec_rows || opt.spec_ksplit || opt.spec_tiles || opt.spec_lanes || opt.spec_depth ||
+        opt.spec_vec || opt.spec_swizzle || opt.natural_order)
+        return false;
+    return h.batch == 1 && sp.rows_per_group > 50 && code_bytes > 720000 && h.K <= 350 * sp.ksplit && (int64_t)h.nnz * sp.rows_per_group >= 3ll * h.M * h.K;
+}
+
 // Stage 4a, emission of everything before the blocks: directives, the prologue that turns the
 // workgroup and lane ids into a block, a column and two buffer descriptors, and the jump table.
 static void emit_prologue(Gen &gen, Emitter &e, const Shape &sh, const Extents &ex, const Deal &deal, int prefetch_lines, int gap) {
@@ -1575,7 +1591,8 @@ int build_spec_plan(HostPlan &h, const sparsert_options &opt, std::string &err) 
     emit_kernel_descriptor(gen, sh);
     // an instruction is at most 8 bytes; 64 lanes touch one 128-byte line each per prefetch
     // instruction, at most 32 of them (their offsets must fit the load's immediate field)
-    const int prefetch_lines = !opt.spec_prefetch ? 0 : (int)std::min<int64_t>(32, (longest * 8 + 64 * 128 - 1) / (64 * 128));
+    const bool prefetch = opt.spec_prefetch || prefetch_pays(h, opt, sp, e.bytes);
+    const int prefetch_lines = !prefetch ? 0 : (int)std::min<int64_t>(32, (longest * 8 + 64 * 128 - 1) / (64 * 128));
     sp.prefetch_lines = prefetch_lines;
     Emitter head;
     emit_prologue(gen, head, sh, ex, deal, prefetch_lines, gap);

@@ -55,6 +55,14 @@ def test_direct_and_k_split_blocks_stay_in_bounds(dtype, opts, N, tmp_path):
 
 
 
+@pytest.mark.parametrize("M,K,N,batch,opts,on", [(2314, 520, 688, 1, {}, 1), (2314, 520, 688, 4, {}, 0), (2314, 520, 688, 1, dict(spec_depth=16), 0),
+                                                 (768, 3072, 256, 1, {}, 0), (300, 300, 196, 1, {}, 0)])
+def test_long_blocks_touch_their_code_ahead(M, K, N, batch, opts, on, tmp_path):
+    csr = synth.uniform_csr(M, K, 0.856, 3)
+    info, _ = _clean(csr, N, tmp_path, batch=batch, **opts)
+    assert info["spec_mode"] == sp.SPEC_DIRECT and bool(info["spec_prefetch"]) == bool(on)
+
+
 def test_code_prefetch_is_checked(tmp_path):
     csr = synth.uniform_csr(300, 500, 0.8, 2)
     text, info = _generated(csr, 130, tmp_path, spec_rows=96, spec_ksplit=2, spec_prefetch=1)
