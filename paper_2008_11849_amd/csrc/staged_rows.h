@@ -135,13 +135,12 @@ inline StagedRows staged_rows_candidate(const HostPlan &h, int32_t longest) {
 // ---- the kernel of a row-walk plan: blocked, staged, or neither.
 struct RowsChoice { StagedRows staged; BlockedRows blocked; };
 
-// The blocked kernel is held against the one of the other two that the rules above choose, both by estimates.  60 fp32 products drawn from
-// M, K <= 4096, N from 49 to 4096, mostly 80 % to 98 % zeros, a third with skewed rows, were timed with both: it takes 24 of them, all faster
-// for it (1.38 times on average, 2.9 at most: 2816 x 630 x 128 at 84 %, skewed, 33.6 -> 11.5 us), and leaves eight that would gain 5 to 40 %, four
-// of them with skewed rows, which the plain kernel's estimate makes too little of.  Of ten within 0.77 to 0.97 of the staged kernel's estimate
-// five gain 5 to 19 % and one loses 10 %; below 0.77 none of fourteen loses.  (The staged estimate leaves its longest row
-// out here: a single long one, which it counts in full, would make up for what is missing to 0.77.)  The plain kernel's estimate is further off, but where it is
-// above 15 us what it leaves out makes that kernel slower.
+// The blocked kernel is held against the one of the other two that the rules above choose, both by estimates.  60 fp32 products, most drawn from
+// M, K <= 4096, N from 49 to 4096, 80 % to 98 % zeros, a third with skewed rows: it takes 17 of them, all faster for it
+// than without the blocked kernel (1.62 times on average, 1.25 at least; 2816 x 630 x 128 at 84 %, skewed, 32.9 -> 10.4 us), and leaves
+// ten where some number of rows and waves would have been 11 to 38 % faster than what runs.  (The staged estimate leaves its longest
+// row out here: a single long one, which it counts in full, would make up for what is missing to 0.77.)  The plain kernel's estimate is further off, but where it
+// is above 15 us what it leaves out makes that kernel slower.
 inline RowsChoice rows_choice(const HostPlan &h) {
     RowsChoice c;
     if (h.kernel != SPARSERT_KERNEL_ROWS || h.conv || h.plain_rows) return c;

@@ -54,8 +54,9 @@ __host__ __device__ constexpr int staged_buffer_bytes(int chunk, int pitch) { re
 
 // A value of the stream in a vector register.  A v_fma_f32 with a scalar operand keeps its SIMD for four clocks, one with vector
 // registers only (or a literal) for two where a second wave takes turns with it (4.2 and 2.2 measured with two to eight waves), so a
-// move of four clocks pays from three multiply-adds on: 4096 x 4096 x 784 at 90 % 135.9 -> 124.3 us, 3000 x 2048 x 784, batch 4, at
-// 84.7 % 260 -> 232 us; at 98 % (4096 x 4096 x 784, 63.4 us) nothing changes.  Half stays with the scalar operand: its products widen
+// move of four clocks pays from three multiply-adds on, so with four columns per lane: 4096 x 4096 x 784 at 90 % 135.9 -> 124.3 us, 3000 x
+// 2048 x 784, batch 4, at 84.7 % 260 -> 232 us; at 98 % (4096 x 4096 x 784, 63.4 us) nothing changes, and of 16 others with four columns one, skewed, loses
+// (4096 x 484 x 2036 at 91 % 40.0 -> 40.6).  With two columns it is not done: 1928 x 320 x 840 at 88 %, skewed, 11.4 us without, 12.4 with.  Half stays with the scalar operand: its products widen
 // the operand as they go (v_fma_mix_f32), four clocks in any case.  (Assembly: the compiler would fold the move away.)
 __device__ __forceinline__ float in_vector(uint32_t bits) {
     float f;
@@ -70,7 +71,7 @@ template <typename T, int V> struct StagedOps {
     typedef T opd_t __attribute__((ext_vector_type(V)));
     static __device__ __forceinline__ void mad2(float (&acc)[V], uint32_t w0, uint32_t w1, const opd_t &b0, const opd_t &b1) {
         float f0 = __uint_as_float(w0), f1 = __uint_as_float(w1);
-        if constexpr (std::is_same<T, float>::value) { f0 = in_vector(w0); f1 = in_vector(w1); }
+        if constexpr (std::is_same<T, float>::value && V > 2) { f0 = in_vector(w0); f1 = in_vector(w1); }
 #pragma unroll
         for (int j = 0; j < V; ++j) acc[j] = __builtin_fmaf(f0, (float)b0[j], acc[j]);
 #pragma unroll
