@@ -5,6 +5,7 @@
 #include <cstdint>
 #include <cstring>
 #include <exception>
+#include <new>
 #include <system_error>
 #include <thread>
 #include <vector>
@@ -176,10 +177,12 @@ void blocked_rows_pack(const HostPlan &h, const BlockedRows &s, BlockedPack &out
         }
     };
     std::vector<std::thread> threads;
+    threads.reserve(shares);
     int started = 1;
     try {
         for (; started < shares; ++started) threads.emplace_back(share, started);
-    } catch (const std::system_error &) {   // no more threads: the rest is done here
+    } catch (const std::system_error &) {   // no more threads, or no memory for one: the rest is done here, and those that run are joined
+    } catch (const std::bad_alloc &) {
     }
     share(0);
     for (int i = started; i < shares; ++i) share(i);

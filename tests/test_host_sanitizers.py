@@ -33,3 +33,12 @@ def test_host_code_is_clean_under_address_and_undefined_behaviour_sanitizers(tmp
     run = subprocess.run([exe], capture_output=True, text=True, timeout=600, env=env)
     assert run.returncode == 0, (run.stdout[-2000:], run.stderr[-4000:])
     assert "0 failed expectations" in run.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_packing_threads_survive_a_failed_allocation(tmp_path):
+    exe = str(tmp_path / "failed_allocation")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-o", exe, os.path.join(HERE, "failed_allocation.cpp"),
+                    os.path.join(CSRC, "pack.cpp"), "-lpthread"], check=True, timeout=600)
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert run.returncode == 0 and " 0 failed expectations" in run.stdout, (run.returncode, run.stdout, run.stderr)
