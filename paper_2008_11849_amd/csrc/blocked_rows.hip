@@ -70,7 +70,7 @@ struct BlockedArgs {
     "v49", "v50", "v51", "v52", "v53", "v54", "v55", "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63", "v64", "v65", "v66", "v67", "v68", \
     "v69", "v70", "v71", "v156", "v157", "v242", "v243", "s36", "s37", "s38", "s39", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", \
     "s49", "s50", "s51", "s52", "s53", "s54", "s55", "s56", "s57", "s58", "s59", "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", "s68", \
-    "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "scc", "memory"
+    "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "m0", "scc", "memory"
 
 template <int PARTS>
 __global__ __launch_bounds__(PARTS *kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void blocked_rows_kernel(const BlockedArgs a) {

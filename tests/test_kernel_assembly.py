@@ -76,3 +76,20 @@ def test_order_of_tiles_pulls_few_bytes(M, K, N, ldb, esz, tm, tn, tmp_path):
     chosen = int(subprocess.run([str(tmp_path / "order")], capture_output=True, text=True, check=True).stdout)
     least = min(_pulled(M, K, N, ldb, esz, tm, tn, per) for per in {1, -(-M // tm)})
     assert _pulled(M, K, N, ldb, esz, tm, tn, chosen) < 1.05 * least
+
+
+def test_assembly_that_sets_m0_says_so():
+    """s_set_gpr_idx_* write M0; the compiler may keep an index of its own there across a block that does not name it."""
+    for name in sorted(os.listdir(entry.CSRC)):
+        if name.endswith(".hip"):
+            with open(os.path.join(entry.CSRC, name)) as f:
+                source = "".join(line.split("//")[0] for line in f)
+            for block in re.findall(r'asm volatile\(.*?\);', source, re.S):
+                text, grown = block, None
+                while text != grown:   # the file's own macros, as far as they go
+                    grown = text
+                    for macro, body in re.findall(r"#define (SP_\w+)(?:\([^)]*\))?((?:[^\n]*\\\n)*[^\n]*)", source):
+                        if re.search(rf"\b{macro}\b", text) and body not in text:
+                            text += body
+                if re.search(r"s_set_gpr_idx_(on|idx)|\bm0\b", text):
+                    assert '"m0"' in text, (name, block[:80])
