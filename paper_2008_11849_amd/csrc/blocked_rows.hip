@@ -41,7 +41,8 @@ struct BlockedArgs {
     int32_t lanes, tiles, blocks, per_part, rows_per_block;
 };
 
-// Scalar registers: a record in s[36:55] and the one after it in s[56:75] (which is which changes with every record), s76 a row number.
+// Scalar registers: a record in s[36:55] and the one after it in s[56:75] (which is which changes with every record), s76 a row number, s77 the
+// M0 to put back.
 // Vector registers: operands of every other group in v[8:23] (first column of the lane) and v[24:39] (second), of those between in
 // v[40:55] and v[56:71]; sums of the first column in v[72:156], of the second in v[158:242], the last of each for fillers.
 #define SP_X "36"
@@ -70,7 +71,7 @@ struct BlockedArgs {
     "v49", "v50", "v51", "v52", "v53", "v54", "v55", "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63", "v64", "v65", "v66", "v67", "v68", \
     "v69", "v70", "v71", "v156", "v157", "v242", "v243", "s36", "s37", "s38", "s39", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", \
     "s49", "s50", "s51", "s52", "s53", "s54", "s55", "s56", "s57", "s58", "s59", "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", "s68", \
-    "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "m0", "scc", "memory"
+    "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "s77", "scc", "memory"
 
 template <int PARTS>
 __global__ __launch_bounds__(PARTS *kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void blocked_rows_kernel(const BlockedArgs a) {
@@ -105,8 +106,9 @@ __global__ __launch_bounds__(PARTS *kWave) __attribute__((amdgpu_waves_per_eu(2,
     float4v a3, b3;
     int left, next;
     uint32_t at = 0;
+    // (s_set_gpr_idx_* write M0, which the compiler may use for an index of its own and does not take as clobbered: it is put back)
     asm volatile(
-        SP_FETCH(SP_X) SP_FETCH(SP_Y) ".set sparsert_i, 0\n\t.rept 171\n\tv_mov_b32 v[72+sparsert_i], 0\n\t.set sparsert_i, sparsert_i+1\n\t.endr\n\t"
+        "s_mov_b32 s77, m0\n\t" SP_FETCH(SP_X) SP_FETCH(SP_Y) ".set sparsert_i, 0\n\t.rept 171\n\tv_mov_b32 v[72+sparsert_i], 0\n\t.set sparsert_i, sparsert_i+1\n\t.endr\n\t"
         "s_waitcnt lgkmcnt(0)\n\ts_mov_b32 %[left], s[" SP_X "+16]\n\ts_mov_b32 %[next], s[" SP_Y "+16]\n\t"
         SP_OPERANDS(SP_X, "8", "%[off0]") SP_OPERANDS(SP_X, "24", "%[off1]") SP_TOUCH SP_OPERANDS(SP_Y, "40", "%[off0]")
         "s_waitcnt vmcnt(17)\n\t" SP_OPERANDS(SP_Y, "56", "%[off1]") SP_FETCH(SP_X)
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(PARTS *kWave) __attribute__((amdgpu_waves_per_eu(2,
         SP_GROUP("8", "24", SP_Y, SP_X, "py", "px", "qy")
         SP_GROUP("40", "56", SP_X, SP_Y, "qx", "qy", "px")
         SP_GROUP("40", "56", SP_Y, SP_X, "qy", "qx", "py")
-        "Lsp_end_%=:\n\ts_set_gpr_idx_off\n\ts_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 4\n\t"
+        "Lsp_end_%=:\n\ts_set_gpr_idx_off\n\ts_mov_b32 m0, s77\n\ts_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 4\n\t"
         : "=&{v[72:103]}"(a0), "=&{v[104:135]}"(a1), "=&{v[136:151]}"(a2), "=&{v[152:155]}"(a3),
           "=&{v[158:189]}"(b0), "=&{v[190:221]}"(b1), "=&{v[222:237]}"(b2), "=&{v[238:241]}"(b3),
           [left] "=&s"(left), [next] "=&s"(next), [at] "+&s"(at)

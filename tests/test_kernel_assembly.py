@@ -78,18 +78,13 @@ def test_order_of_tiles_pulls_few_bytes(M, K, N, ldb, esz, tm, tn, tmp_path):
     assert _pulled(M, K, N, ldb, esz, tm, tn, chosen) < 1.05 * least
 
 
-def test_assembly_that_sets_m0_says_so():
-    """s_set_gpr_idx_* write M0; the compiler may keep an index of its own there across a block that does not name it."""
-    for name in sorted(os.listdir(entry.CSRC)):
-        if name.endswith(".hip"):
-            with open(os.path.join(entry.CSRC, name)) as f:
-                source = "".join(line.split("//")[0] for line in f)
-            for block in re.findall(r'asm volatile\(.*?\);', source, re.S):
-                text, grown = block, None
-                while text != grown:   # the file's own macros, as far as they go
-                    grown = text
-                    for macro, body in re.findall(r"#define (SP_\w+)(?:\([^)]*\))?((?:[^\n]*\\\n)*[^\n]*)", source):
-                        if re.search(rf"\b{macro}\b", text) and body not in text:
-                            text += body
-                if re.search(r"s_set_gpr_idx_(on|idx)|\bm0\b", text):
-                    assert '"m0"' in text, (name, block[:80])
+def test_assembly_that_sets_m0_puts_it_back(tmp_path):
+    """s_set_gpr_idx_* write M0, where the compiler may keep an index of its own across the block."""
+    blocks = [b for b in re.findall(r";;#ASMSTART(.*?);;#ASMEND", _assembly("blocked_rows.hip", tmp_path), re.S) if "s_set_gpr_idx" in b]
+    assert len(blocks) == 2
+    for b in blocks:
+        lines = [l for l in (l.split(";")[0].strip() for l in b.splitlines()) if l]
+        first, last = (next(i for i in order if re.search(r"s_set_gpr_idx|\bm0\b", lines[i])) for order in (range(len(lines)), range(len(lines) - 1, -1, -1)))
+        saved = re.fullmatch(r"s_mov_b32 (s\d+), m0", lines[first]).group(1)
+        assert lines[last] == f"s_mov_b32 m0, {saved}"
+        assert not any(re.search(rf"\b{saved}\b", l) for l in lines[first + 1:last])
