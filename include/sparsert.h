@@ -150,7 +150,8 @@ typedef struct sparsert_options {
                                 that other layers have displaced overlap instead of following each other
                                 (costs about 0.5 us when the code is still in the L2, gains more than that
                                 when it is not; the tuner tries it on its winner); 0 = off, except that a plan with
-                                no spec_* field and no natural_order set does so where that was measured to pay (info says) */
+                                no spec_* field and no natural_order set does so where that was measured to pay (info
+                                says); -1 = off there too, and nothing else about the plan changes */
     int32_t reserved[2];     /* must be zero */
 } sparsert_options;
 

@@ -1513,7 +1513,7 @@ static bool all_finite(const HostPlan &h, const void *vals) {
 
 int mfma_preferred(const HostPlan &h, const sparsert_options &opt, const void *vals) {
     if (opt.kernel != SPARSERT_KERNEL_AUTO || opt.vec || opt.split_threshold || opt.spec_mode || opt.spec_rows || opt.spec_depth || opt.spec_tiles ||
-        opt.spec_ksplit || opt.spec_lanes || opt.spec_swizzle || opt.spec_vec || opt.spec_prefetch || opt.natural_order || !mfma_applies(h))
+        opt.spec_ksplit || opt.spec_lanes || opt.spec_swizzle || opt.spec_vec || opt.spec_prefetch > 0 || opt.natural_order || !mfma_applies(h))
         return -1;
     double t = 0;
     const int tile = mfma_best_tile(h, &t);
@@ -1591,7 +1591,7 @@ int build_spec_plan(HostPlan &h, const sparsert_options &opt, std::string &err) 
     emit_kernel_descriptor(gen, sh);
     // an instruction is at most 8 bytes; 64 lanes touch one 128-byte line each per prefetch
     // instruction, at most 32 of them (their offsets must fit the load's immediate field)
-    const bool prefetch = opt.spec_prefetch || prefetch_pays(h, opt, sp, e.bytes);
+    const bool prefetch = opt.spec_prefetch > 0 || (opt.spec_prefetch == 0 && prefetch_pays(h, opt, sp, e.bytes));
     const int prefetch_lines = !prefetch ? 0 : (int)std::min<int64_t>(32, (longest * 8 + 64 * 128 - 1) / (64 * 128));
     sp.prefetch_lines = prefetch_lines;
     Emitter head;

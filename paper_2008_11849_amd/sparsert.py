@@ -187,7 +187,8 @@ def inspect(row_ptr, col_idx, vals, M: int, K: int, N: int, *, dtype: Optional[i
             spec_mode: int = 0, spec_ksplit: int = 0, natural_order: bool = False,
             spec_lanes: int = 0, spec_swizzle: bool = False, spec_vec: int = 0,
             ldb: int = 0, ldc: int = 0, spec_prefetch: int = 0) -> Plan:
-    """sparsert_inspect.  `vals` must already be float32, float16 or int8; it is not converted."""
+    """sparsert_inspect.  `vals` must already be float32, float16 or int8; it is not converted.
+    spec_prefetch: 1 has generated code touched ahead, -1 never, 0 leaves it to the inspector."""
     row_ptr = np.ascontiguousarray(row_ptr, dtype=np.int32)
     col_idx = np.ascontiguousarray(col_idx, dtype=np.int32)
     vals = np.ascontiguousarray(vals)

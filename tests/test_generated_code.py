@@ -63,6 +63,19 @@ def test_long_blocks_touch_their_code_ahead(M, K, N, batch, opts, on, tmp_path):
     assert info["spec_mode"] == sp.SPEC_DIRECT and bool(info["spec_prefetch"]) == bool(on)
 
 
+def test_the_touches_can_be_switched_off():
+    """A caller that runs one plan alone, whose code stays in the caches, gets the plan without them and no other change."""
+    csr = synth.uniform_csr(2314, 520, 0.856, 3)
+    on, off, plain = ({k: p.info()[k] for k in p.info()} for p in (sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, 2314, 520, 688, host_only=True, **o)
+                                                                   for o in ({}, dict(spec_prefetch=-1), dict(spec_depth=16))))
+    assert on["spec_prefetch"] > 0 and off["spec_prefetch"] == 0
+    assert {k for k in on if on[k] != off[k]} <= {"spec_prefetch", "spec_code_bytes"} and off["spec_code_bytes"] == plain["spec_code_bytes"]
+    half = synth.uniform_csr(1024, 1024, 0.8, 3, dtype=np.float16)   # a plan without generated code stays one
+    assert sp.inspect(half.row_ptr, half.col_idx, half.vals, 1024, 1024, 512, host_only=True, spec_prefetch=-1).info()["spec_mode"] == sp.SPEC_MFMA
+    with pytest.raises(sp.SparseRTError):
+        sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, 2314, 520, 688, host_only=True, spec_prefetch=-2)
+
+
 def test_code_prefetch_is_checked(tmp_path):
     csr = synth.uniform_csr(300, 500, 0.8, 2)
     text, info = _generated(csr, 130, tmp_path, spec_rows=96, spec_ksplit=2, spec_prefetch=1)
