@@ -149,7 +149,7 @@ typedef struct sparsert_options {
                                 loads before it runs into it, so that the L2 misses of straight-line code
                                 that other layers have displaced overlap instead of following each other
                                 (costs about 0.5 us when the code is still in the L2, gains more than that
-                                when it is not; the tuner tries it on its winner); 0 = off, except that a plan with
+                                when it is not; the tuner tries its winner both ways); 0 = off, except that a plan with
                                 no spec_* field and no natural_order set does so where that was measured to pay (info
                                 says); -1 = off there too, and nothing else about the plan changes */
     int32_t reserved[2];     /* must be zero */

@@ -171,4 +171,13 @@ std::vector<sparsert_options> tune_candidates(int32_t M, int32_t K, int32_t N, i
     return cands;
 }
 
+sparsert_options options_again(const HostPlan &h, const sparsert_options &b) {
+    const SpecPlan &w = h.spec;
+    sparsert_options o = b;
+    o.kernel = SPARSERT_KERNEL_SPEC; o.spec_mode = w.mode; o.spec_rows = w.rows_per_group;
+    o.spec_tiles = w.tiles_per_wg; o.spec_ksplit = w.ksplit; o.spec_vec = w.vec; o.spec_swizzle = w.swizzle;
+    o.spec_prefetch = w.prefetch_lines > 0 ? 1 : -1;   // (a plan with nothing set may have the touches)
+    return o;
+}
+
 }  // namespace sparsert

@@ -129,6 +129,8 @@ int rows_without_thin_round(int32_t M, int R, int groups_per_wg, int64_t wg_colu
 int mfma_preferred(const HostPlan &h, const sparsert_options &opt, const void *vals);
 // What the autotuner times besides its first candidate (candidates.cpp); b: the caller's options, tuning fields cleared.
 std::vector<sparsert_options> tune_candidates(int32_t M, int32_t K, int32_t N, int64_t nnz, const sparsert_options &b);
+// The options that make a generated plan again, whatever of it was chosen and not asked for.
+sparsert_options options_again(const HostPlan &h, const sparsert_options &b);
 bool spec_available();   // can generated kernels be assembled in this process (is the code object manager loadable)?
 
 // Records the thread-local error message behind sparsert_last_error (api.cpp); returns `code`.

@@ -260,10 +260,8 @@ static int tune_impl(const int32_t *row_ptr, const int32_t *col_idx, const void 
     // Last candidate: the winner's configuration with its blocks formed by similarity (row swizzle).
     if (key(best_t) > 0.0f && best->host.kernel == SPARSERT_KERNEL_SPEC && best->host.spec.rows_per_group > 1 &&
         best->host.spec.mode != SPARSERT_SPEC_MFMA && !b.natural_order) {
-        const sparsert::SpecPlan &w = best->host.spec;
-        sparsert_options o = b;
-        o.kernel = SPARSERT_KERNEL_SPEC; o.spec_mode = w.mode; o.spec_rows = w.rows_per_group;
-        o.spec_tiles = w.tiles_per_wg; o.spec_ksplit = w.ksplit; o.spec_vec = w.vec; o.spec_swizzle = 1;
+        sparsert_options o = sparsert::options_again(best->host, b);
+        o.spec_swizzle = 1;
         sparsert_plan *p = nullptr;
         if (sparsert_inspect(row_ptr, col_idx, vals, M, K, N, &o, &p) == SPARSERT_OK) {
             const Timing t = measure(p);
@@ -276,28 +274,28 @@ static int tune_impl(const int32_t *row_ptr, const int32_t *col_idx, const void 
             }
         }
     }
-    // ... and the winner with its waves prefetching their code: kept if it is worth at least 1.5 %
-    // under the condition the ranking uses (it costs time while the code is still in the L2)
+    // ... and the winner with its waves prefetching their code, or without where it has that already: the version that
+    // prefetches is kept if it is worth at least 1.5 % under the condition the ranking uses (it costs time while the code
+    // is still in the L2)
     if (key(best_t) > 0.0f && best->host.kernel == SPARSERT_KERNEL_SPEC && best->host.spec.mode != SPARSERT_SPEC_MFMA) {
-        const sparsert::SpecPlan &w = best->host.spec;
-        sparsert_options o = b;
-        o.kernel = SPARSERT_KERNEL_SPEC; o.spec_mode = w.mode; o.spec_rows = w.rows_per_group;
-        o.spec_tiles = w.tiles_per_wg; o.spec_ksplit = w.ksplit; o.spec_vec = w.vec; o.spec_swizzle = w.swizzle;
-        o.spec_prefetch = 1;
+        const bool has = best->host.spec.prefetch_lines > 0;
+        sparsert_options o = sparsert::options_again(best->host, b);
+        o.spec_prefetch = has ? -1 : 1;
         sparsert_plan *p = nullptr;
         if (sparsert_inspect(row_ptr, col_idx, vals, M, K, N, &o, &p) == SPARSERT_OK) {
             Timing t = measure(p);
             log(p, t);
             // the two are a few percent apart, which is what two timings of one plan minutes apart
             // can differ by: both are timed twice more, alternating, and the best of each counts
-            float with = key(t), without = key(best_t);
-            for (int i = 0; i < 2 && with > 0.0f; ++i) {
+            float other = key(t), mine = key(best_t);
+            for (int i = 0; i < 2 && other > 0.0f; ++i) {
                 const float a = rank_cold ? bench.cold(best) : bench.warm(best);
                 const float c = rank_cold ? bench.cold(p) : bench.warm(p);
-                if (a > 0.0f) without = std::min(without, a);
-                if (c > 0.0f) with = std::min(with, c);
+                if (a > 0.0f) mine = std::min(mine, a);
+                if (c > 0.0f) other = std::min(other, c);
             }
-            if (with > 0.0f && with < 0.985f * without) {
+            const float with = has ? mine : other, without = has ? other : mine;
+            if (other > 0.0f && (with < 0.985f * without) != has) {
                 sparsert_plan_destroy(best);
                 best = p; best_t = t;
             } else {

@@ -137,6 +137,27 @@ sparsert::HostPlan host_plan(const Csr &c, int M, int K, int N, sparsert_options
     return h;
 }
 
+// What the tuner builds to try its winner with and without the touches differs from the winner in nothing else, also where
+// the winner is the plan with nothing set, which may have them.
+void winners_are_tried_both_ways(Rng &r) {
+    const struct { int M, K, N; double density; bool touches; } shapes[] = {{2314, 520, 688, 0.144, true}, {300, 300, 196, 0.1, false}};
+    for (const auto &s : shapes) {
+        const Csr c = make(s.M, s.K, s.density, 4, r, false);
+        sparsert_options b;
+        std::memset(&b, 0, sizeof(b));
+        const sparsert::HostPlan h = host_plan(c, s.M, s.K, s.N, b);
+        EXPECT(h.kernel == SPARSERT_KERNEL_SPEC && (h.spec.prefetch_lines > 0) == s.touches);
+        sparsert_options o = sparsert::options_again(h, b);
+        const sparsert::HostPlan same = host_plan(c, s.M, s.K, s.N, o);
+        EXPECT(same.spec.code == h.spec.code && same.spec.prefetch_lines == h.spec.prefetch_lines);
+        o.spec_prefetch = -o.spec_prefetch;
+        const sparsert::HostPlan other = host_plan(c, s.M, s.K, s.N, o);
+        EXPECT((other.spec.prefetch_lines > 0) == !s.touches && other.spec.group_of_slot == h.spec.group_of_slot);
+        EXPECT(other.spec.mode == h.spec.mode && other.spec.rows_per_group == h.spec.rows_per_group && other.spec.ksplit == h.spec.ksplit &&
+               other.spec.tiles_per_wg == h.spec.tiles_per_wg && other.spec.vec == h.spec.vec && other.spec.lanes_per_tile == h.spec.lanes_per_tile);
+    }
+}
+
 // Fragments of every matrix-core tile: each weight once, at the place its row, step and lane give, zeros elsewhere.
 int mfma_layout_holds_every_weight_once(Rng &r) {
     int plans = 0;
@@ -226,6 +247,7 @@ int main() {
     Rng r{20081184ull};
     const int shapes[][3] = {{1, 1, 1}, {7, 5, 3}, {64, 48, 100}, {70, 150, 196}, {33, 260, 65}};
     int plans = 0;
+    winners_are_tried_both_ways(r);
     plans += mfma_layout_holds_every_weight_once(r);
     plans += staged_layout_walks_every_row(r);
     for (const auto &s : shapes) {
