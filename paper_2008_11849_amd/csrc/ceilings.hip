@@ -24,13 +24,17 @@ __global__ __launch_bounds__(256) void copy_kernel(const float4 *__restrict__ sr
 
 constexpr int kAcc = 32;   // independent accumulators per lane: no multiply-add waits for another
 
+// Both factors in vector registers, as an operand of B and a literal or moved value of A are: a multiply-add with a scalar
+// operand keeps its SIMD for four clocks, one without for two.  (Assembly: the compiler would fold the moves away.)
 __global__ __launch_bounds__(256) void fma_kernel(float *out, int iters, float a, float b) {
     float acc[kAcc];
+    asm volatile("v_mov_b32 %0, %1" : "=v"(a) : "s"(a));
+    asm volatile("v_mov_b32 %0, %1" : "=v"(b) : "s"(b));
 #pragma unroll
     for (int j = 0; j < kAcc; ++j) acc[j] = (float)(threadIdx.x + j);
     for (int i = 0; i < iters; ++i) {
 #pragma unroll
-        for (int j = 0; j < kAcc; ++j) acc[j] = __builtin_fmaf(acc[j], a, b);
+        for (int j = 0; j < kAcc; ++j) acc[j] = __builtin_fmaf(a, b, acc[j]);
     }
     float s = 0.0f;
 #pragma unroll

@@ -1155,16 +1155,22 @@ static int gap_between_blocks(int64_t code_bytes, int64_t blocks) {
 // Does a plan with nothing set touch its code ahead (emit_prologue)?  It pays where the plans that run in between have displaced the
 // code from the L2s and a block is long: 1021 x 1027 x 771, skewed, at 90 %, four plans taking turns, 8.83 us without and 7.86 with;
 // 3072 x 768 x 1024 at 95 % 9.99 and 9.72; 2314 x 520 x 688 at 86 % 10.8 and 9.0.  It costs where one plan runs alone and the
-// code is still there: 6.75 us without and 7.14 with, 8.81 and 9.19, 8.10 and 8.55.  The limits on batch, K and nonzeros to a row of B were
-// set on 192 products and convolutions (the rule takes 43) and tried on 27 others that it takes: plans taking turns 0.925 times the
-// time on average, two of the 27 slower (817 x 2176 x 1233 at 95.5 % 1.041, 2944 x 576 x 2880 at 94 % 1.017); one
-// plan alone 1.017 on average and 1.106 at most.  A batch shares the code among its images but each image's waves touch it again
-// (3229 x 256 x 1987, batch 4, 44.6 us without and 48.1 with); a wave with many rows of B to fetch has its loads queue behind the
-// touches (744 x 4076 x 3587 48.6 and 52.0); and few nonzeros to a row leave the time in the fetches (1664 x 2112 x 1405 at 97.6 % 21.0 and 21.9).
+// code is still there: 6.75 us without and 7.14 with, 8.81 and 9.19, 8.10 and 8.55 (spec_prefetch = -1 leaves it out).  75 products that the
+// rule takes and that did not set it, three plans each taking turns: 0.927 times the time on average, five slower by more than 1 % (3520 x 658 x
+// 2344 at 91 % 1.039); one plan alone 1.021 and 1.086 at most.  What each limit leaves out (the limits set on 192 others):
+// - blocks of 21 to 50 rows: 0.93 over 11, but three of them slower, 1.041 at most; code of 500 to 720 kB: 0.95 over nine, two slower, 1.078
+//   at most; both: 1.00 over nine, five slower.
+// - convolutions: fp32 0.96 over 25, but eight slower, 1.070 at most, and 1.09 alone; half 0.98 over 12, six slower, 1.093 at most; int8 1.06 over
+//   12, eleven slower.
+// - half and int8 in fewer than four parts: 1.02 over seven, four slower (2173 x 560 x 3968, half, 20.9 us without and 23.2 with).
+// - a batch shares the code among its images but each image's waves touch it again (3229 x 256 x 1987, batch 4, 44.6 and 48.1); a wave
+//   with many rows of B to fetch has its loads queue behind the touches (744 x 4076 x 3587 48.6 and 52.0); few nonzeros to a row
+//   of B leave the time in the fetches (1664 x 2112 x 1405 at 97.6 % 21.0 and 21.9).
 static bool prefetch_pays(const HostPlan &h, const sparsert_options &opt, const SpecPlan &sp, int64_t code_bytes) {
     if (sp.mode != SPARSERT_SPEC_DIRECT || opt.spec_mode || opt.spec_rows || opt.spec_ksplit || opt.spec_tiles || opt.spec_lanes || opt.spec_depth ||
         opt.spec_vec || opt.spec_swizzle || opt.natural_order)
         return false;
+    if (h.conv || (h.dtype != SPARSERT_F32 && sp.ksplit < 4)) return false;
     return h.batch == 1 && sp.rows_per_group > 50 && code_bytes > 720000 && h.K <= 350 * sp.ksplit && (int64_t)h.nnz * sp.rows_per_group >= 3ll * h.M * h.K;
 }
 

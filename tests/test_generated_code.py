@@ -63,6 +63,18 @@ def test_long_blocks_touch_their_code_ahead(M, K, N, batch, opts, on, tmp_path):
     assert info["spec_mode"] == sp.SPEC_DIRECT and bool(info["spec_prefetch"]) == bool(on)
 
 
+@pytest.mark.parametrize("dtype,M,K,N,sparsity,img,on", [
+    (np.float32, 384, 1008, 2209, 0.818, 47, 0), (np.float16, 408, 1152, 2704, 0.85, 52, 0), (np.int8, 392, 1152, 2601, 0.835, 51, 0),
+    (np.float16, 2173, 560, 3968, 0.919, 0, 0), (np.int8, 3584, 216, 3400, 0.803, 0, 0), (np.float16, 1258, 780, 728, 0.821, 0, 1),
+    (np.int8, 1420, 942, 888, 0.852, 0, 1), (np.float32, 2759, 320, 1307, 0.8, 0, 1)])
+def test_what_touching_code_ahead_slows_down_does_not(dtype, M, K, N, sparsity, img, on):
+    """Convolutions, half and int8 products in few parts: long blocks and much code, and slower for the touches all the same."""
+    csr = synth.int8_csr(M, K, sparsity, 3) if dtype == np.int8 else synth.uniform_csr(M, K, sparsity, 3, dtype=dtype)
+    info = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, kernel=sp.KERNEL_SPEC, **(dict(conv=(K // 9, img, img)) if img else {})).info()
+    assert info["spec_mode"] == sp.SPEC_DIRECT and info["spec_rows"] > 50 and info["spec_code_bytes"] > 720000
+    assert bool(info["spec_prefetch"]) == bool(on)
+
+
 def test_the_touches_can_be_switched_off():
     """A caller that runs one plan alone, whose code stays in the caches, gets the plan without them and no other change."""
     csr = synth.uniform_csr(2314, 520, 0.856, 3)

@@ -88,3 +88,13 @@ def test_assembly_that_sets_m0_puts_it_back(tmp_path):
         saved = re.fullmatch(r"s_mov_b32 (s\d+), m0", lines[first]).group(1)
         assert lines[last] == f"s_mov_b32 m0, {saved}"
         assert not any(re.search(rf"\b{saved}\b", l) for l in lines[first + 1:last])
+
+
+def test_the_multiply_add_ceiling_is_the_fast_form(tmp_path):
+    """Multiply-adds of the ceiling kernel read vector registers only, as those of the kernels held against it; a scalar operand halves their rate."""
+    command = entry.ceilings_command(str(tmp_path / "ceilings.s"))
+    flags = [a for a in command if not a.startswith(entry.CSRC) and a not in ("-shared", "-fPIC")]
+    subprocess.run(flags + ["--offload-device-only", "-S", os.path.join(entry.CSRC, "ceilings.hip")], check=True, capture_output=True)
+    body = re.search(r"^_ZN\w*fma_kernel\w*:.*?$(.*?)^\.Lfunc_end", (tmp_path / "ceilings.s").read_text(), re.S | re.M).group(1)
+    mads = re.findall(r"v_(?:fma|fmac|pk_fma)_f32\S* (.*)", body)
+    assert len(mads) == 32 and all(re.fullmatch(r"v\d+(, v\d+)+", m.split(";")[0].strip()) for m in mads)
