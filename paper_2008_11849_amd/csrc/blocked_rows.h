@@ -59,15 +59,18 @@ inline int blocked_rows_per_part(const HostPlan &h, const BlockedRows &s) {
     return best;
 }
 
-// The shape that is expected to take the least, its per_part still open.  fp32, and no more than a fifth of A kept: what the products
-// that the estimate was fitted to are like.
+// The shape that is expected to take the least, its per_part still open.  fp32, no more than a fifth of A kept, at least 64 rows and 49
+// columns: what the products that the estimate was fitted to are like.  Below, the choice would not hold: of eleven products of 1 to 20 rows four
+// were slower blocked (1 x 12870 x 229, batch 64, at 82 % 57.3 -> 73.7 us), of sixteen of 1 to 48 columns two, 1.9 times (136 x 10639 x 8, batch
+// 64, at 89 % 88.7 -> 165.8 us).  Beyond 4096 rows or columns of A, or a batch of 4, it does: fourteen of 372 to 3218 rows, K from 4996 to
+// 14174, batches of up to 64, 0.75 times the time on average and 1.02 at most.
 inline BlockedRows blocked_rows_candidate(const HostPlan &h) {
     BlockedRows best;
-    if (h.dtype != SPARSERT_F32 || (int64_t)h.nnz * 5 > (int64_t)h.M * h.K || (int64_t)h.nnz >= 1 << 28) return best;
+    if (h.dtype != SPARSERT_F32 || h.M < 64 || h.N < 49 || (int64_t)h.nnz * 5 > (int64_t)h.M * h.K || (int64_t)h.nnz >= 1 << 28) return best;
     BlockedRows s;
     s.tiles = (h.N + 2 * kWave - 1) / (2 * kWave);
     s.lanes = ((h.N + s.tiles - 1) / s.tiles + 1) / 2;
-    for (int rows = std::min<int>(kBlockedRows, h.M), last = 0; rows >= std::min<int>(16, h.M); --rows) {
+    for (int rows = std::min<int>(kBlockedRows, h.M), last = 0; rows >= 16; --rows) {
         s.blocks = (h.M + rows - 1) / rows;
         if (s.blocks == last) continue;
         last = s.blocks;

@@ -138,7 +138,8 @@ struct RowsChoice { StagedRows staged; BlockedRows blocked; };
 // The blocked kernel is held against the one of the other two that the rules above choose, both by estimates.  60 fp32 products, most drawn from
 // M, K <= 4096, N from 49 to 4096, 80 % to 98 % zeros, a third with skewed rows: it takes 17 of them, all faster for it
 // than without the blocked kernel (1.62 times on average, 1.25 at least; 2816 x 630 x 128 at 84 %, skewed, 32.9 -> 10.4 us), and leaves
-// ten where some number of rows and waves would have been 11 to 38 % faster than what runs.  (The staged estimate leaves its longest
+// ten where some number of rows and waves would have been 11 to 38 % faster than what runs.  Of 33 others drawn alike that it takes two
+// are slower for it, both skewed (1342 x 2956 x 77 at 92.5 % 24.8 -> 26.4 us, the other 1.3 %); 0.71 times the time on average.  (The staged estimate leaves its longest
 // row out here: a single long one, which it counts in full, would make up for what is missing to 0.77.)  The plain kernel's estimate is further off, but where it
 // is above 15 us what it leaves out makes that kernel slower.
 inline RowsChoice rows_choice(const HostPlan &h) {

@@ -706,6 +706,19 @@ def test_row_walk_plans_that_staging_would_slow_down_stay_plain(M, K, N, batch, 
     assert info["kernel"] == sp.KERNEL_ROWS and info["staged_vec"] == 0
 
 
+@pytest.mark.parametrize("M,K,N,batch,sparsity,blocked", [
+    (1, 12870, 229, 64, 0.816, False),           # 73.7 us blocked | 57.3 plain
+    (16, 5642, 439, 64, 0.878, False),           # 199.7 | 179.1
+    (136, 10639, 8, 64, 0.889, False),           # 165.8 | 88.7
+    (63, 1500, 2400, 4, 0.9, False), (64, 1500, 2400, 4, 0.9, True),     # the edges of what its estimate was fitted to
+    (3000, 3000, 48, 4, 0.9, False), (3000, 3000, 49, 4, 0.9, True),
+])
+def test_row_walk_plans_outside_the_blocked_kernels_range_keep_their_kernel(M, K, N, batch, sparsity, blocked):
+    csr = synth.uniform_csr(M, K, sparsity, 6)
+    info = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, host_only=True, kernel=sp.KERNEL_ROWS, batch=batch).info()
+    assert info["kernel"] == sp.KERNEL_ROWS and bool(info["blocked_rows"]) == blocked
+
+
 @pytest.mark.parametrize("opts,staged", [(dict(), True), (dict(vec=1), False), (dict(split_threshold=65), False), (dict(natural_order=True), False),
                                          (dict(kernel=sp.KERNEL_SPEC, spec_rows=64, spec_ksplit=1), False)])
 def test_plans_saved_in_the_previous_format_load(opts, staged):
