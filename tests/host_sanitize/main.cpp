@@ -239,6 +239,65 @@ int staged_layout_walks_every_row(Rng &r) {
     return plans;
 }
 
+// The blocked kernel's records walked as a wave does: every nonzero once, in its row's place and its column's group, fillers with the
+// value zero and the row that nobody reads, headers that name the columns of a group and its layers, and nothing the wave
+// reads ahead of its place lies behind the stream.
+int blocked_records_hold_every_nonzero_once(Rng &r) {
+    int plans = 0;
+    const struct { int M, K, N, ldb, rows, parts; double density; bool skew; } shapes[] = {
+        {300, 300, 640, 640, 75, 4, 0.0, false},  {300, 300, 640, 640, 75, 4, 0.004, false},  {64, 1500, 130, 133, 22, 8, 0.12, false},
+        {200, 90, 49, 49, 84, 4, 0.2, true},      {1000, 700, 200, 200, 84, 8, 0.19, false},  {1, 40, 64, 64, 1, 4, 0.2, false},
+        {85, 3, 64, 64, 43, 4, 0.2, false},       {2048, 1024, 784, 784, 57, 4, 0.15, false}, {997, 1500, 300, 317, 16, 4, 0.05, true}};
+    for (const auto &t : shapes) {
+        const Csr c = make(t.M, t.K, t.density, 4, r, t.skew);
+        sparsert_options o;
+        std::memset(&o, 0, sizeof(o));
+        o.kernel = SPARSERT_KERNEL_ROWS; o.ldb = o.ldc = t.ldb;
+        const sparsert::HostPlan h = host_plan(c, t.M, t.K, t.N, o);
+        sparsert::BlockedRows s;
+        s.blocks = (t.M + t.rows - 1) / t.rows; s.rows = (t.M + s.blocks - 1) / s.blocks; s.parts = t.parts;
+        sparsert::BlockedPack pack;
+        sparsert::blocked_rows_pack(h, s, pack);
+        const int R = sparsert::kBlockedRows, W = sparsert::kBlockedRecord, G = sparsert::kBlockedColumns;
+        EXPECT((int)pack.starts.size() == s.blocks * s.parts && (int)pack.rows.size() == s.blocks * R && pack.stream.size() % W == 0);
+        const size_t records = pack.stream.size() / W;
+        std::vector<int> seen_row(t.M, 0), seen(h.nnz, 0);
+        for (int b = 0; b < s.blocks; ++b) {
+            for (int i = 0; i < R; ++i)
+                if (pack.rows[b * R + i] >= 0) { EXPECT(i < s.rows); ++seen_row[pack.rows[b * R + i]]; }
+            for (int part = 0; part < s.parts; ++part) {
+                size_t at = pack.starts[b * s.parts + part];
+                const uint32_t *header = &pack.stream[at * W], *next = &pack.stream[(at + 1) * W];
+                for (at += 2; (int32_t)header[G] >= 0;) {
+                    for (int layer = 0; layer <= (int32_t)header[G]; ++layer, ++at) {
+                        EXPECT(at + 1 < records);   // (the record behind is fetched while this one is worked on)
+                        for (int i = 0; i < G; ++i) {
+                            const uint32_t value = pack.stream[at * W + i], place = pack.stream[at * W + G + i / 4] >> (8 * (i % 4)) & 255;
+                            if (place == (uint32_t)R) { EXPECT(value == 0); continue; }
+                            EXPECT((int)place < s.rows && header[i] % (4 * t.ldb) == 0);
+                            const int row = pack.rows[b * R + place], column = (int)(header[i] / (4 * t.ldb));
+                            EXPECT(row >= 0);
+                            int p = c.row_ptr[row];
+                            while (p < c.row_ptr[row + 1] && c.col[p] != column) ++p;
+                            EXPECT(p < c.row_ptr[row + 1] && std::memcmp(&value, &c.vals[(size_t)p * 4], 4) == 0);
+                            if (p < c.row_ptr[row + 1]) ++seen[p];
+                        }
+                    }
+                    for (int i = 0; i < G; ++i) EXPECT(header[i] / 4 <= (uint32_t)((t.K - 1) * t.ldb));
+                    header = next;
+                    next = &pack.stream[at++ * W];
+                }
+                // the wave ends on a group that is not there; it has fetched that one's header, the next one's and a record more
+                EXPECT(at < records);
+            }
+        }
+        for (int v : seen_row) EXPECT(v == 1);
+        for (int v : seen) EXPECT(v == 1);
+        ++plans;
+    }
+    return plans;
+}
+
 }  // namespace
 
 int main() {
@@ -250,6 +309,7 @@ int main() {
     winners_are_tried_both_ways(r);
     plans += mfma_layout_holds_every_weight_once(r);
     plans += staged_layout_walks_every_row(r);
+    plans += blocked_records_hold_every_nonzero_once(r);
     for (const auto &s : shapes) {
         const int M = s[0], K = s[1], N = s[2];
         for (int dtype = SPARSERT_F32; dtype <= SPARSERT_I8; ++dtype) {

@@ -1,6 +1,6 @@
 """The row-walk kernel that keeps a block of rows in registers, against the CPU oracle: small integers, so that any order gives
 the same bits; column tiles with idle lanes and a ragged last one, blocks with empty slots, groups of columns that fillers
-complete, parts without a column, empty and long rows, batches and row pitches."""
+complete, parts with no group of columns, one and two, empty and long rows, the fewest rows and columns, batches and row pitches."""
 import numpy as np
 import pytest
 
@@ -42,6 +42,8 @@ CASES = [
     (2664, 1500, 198, 0.076, 4, 5, False, 8),
     (2816, 630, 128, 0.16, 1, 0, True, 4),      # blocks of sixteen rows
     (186, 3320, 2062, 0.1, 4, 0, False, 8),
+    (64, 1500, 2400, 0.12, 4, 0, False, 4),     # the fewest rows
+    (3000, 3000, 49, 0.1, 4, 0, False, 8),      # the fewest columns
 ]
 
 
@@ -55,6 +57,22 @@ def test_spmm_against_the_oracle(case):
     want = np.stack([ref.spmm(M, K, N, csr.row_ptr, csr.col_idx, csr.vals, b)[0] for b in B])
     got, pad_ok, _ = run_spmm_strided(csr, B, N + pad, N + pad, **ROWS) if pad else (run_spmm(csr, B, **ROWS)[0], True, None)
     assert pad_ok and np.array_equal(got.astype(np.float64), want)
+
+
+@pytest.mark.parametrize("columns", [0, 1, 2, 40, 160])
+def test_parts_with_few_groups_of_columns(columns):
+    """Four waves share the columns that a block has nonzeros in, sixteen to a group: none, one or two of the waves have a column at all,
+    each has one group, each has two."""
+    M, K, N, batch = 300, 300, 640, 64
+    rng = np.random.default_rng(columns)
+    mask = np.zeros((M, K), dtype=bool)
+    mask[:, np.linspace(1, K - 1, columns).astype(int)] = rng.random((M, columns)) < min(0.19, 1.75 / max(1, columns))
+    csr = synth.csr_from_mask(rng.choice([-2.0, -1.0, 1.0, 2.0], size=(M, K)).astype(np.float32), mask)
+    B = rng.integers(-2, 3, size=(batch, K, N)).astype(np.float32)
+    plan = sp.inspect(csr.row_ptr, csr.col_idx, csr.vals, M, K, N, batch=batch, host_only=True, **ROWS)
+    assert plan.kernel_name() == "void sparsert::blocked_rows_kernel<4>(sparsert::BlockedArgs)"
+    want = np.stack([ref.spmm(M, K, N, csr.row_ptr, csr.col_idx, csr.vals, b)[0] for b in B])
+    assert np.array_equal(run_spmm(csr, B, **ROWS)[0].astype(np.float64), want)
 
 
 def test_non_finite_operands_stay_where_they_are():
