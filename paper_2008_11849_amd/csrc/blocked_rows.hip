@@ -7,7 +7,7 @@
 // a workgroup split a block's columns and their sums meet in LDS, in wave order.
 //
 // The columns of a wave's part are sorted by how many nonzeros they have in the block and taken in groups of sixteen, so that the
-// group's nonzeros come in layers of one per column, of which hardly any is a filler (7 % at 90 % zeros and 57 rows): the
+// group's nonzeros come in layers of one per column, of which hardly any is a filler (2 % at 90 % zeros and 57 rows): the
 // operand registers are then the same in every layer.  The wave's stream holds, in the order it is walked, the group's layers as
 // records of 80 bytes (sixteen values, sixteen row numbers in bytes) and, behind a group's last one, the header of the group after
 // the next (sixteen byte offsets into B, and the number of layers less one; -1 behind the last group).  A filler multiplies zero by

@@ -21,14 +21,14 @@
 // element of B (or weight of A) leaves a non-finite sum in every row of its column, so sums that are
 // all finite prove that nothing of the kind was involved; a wave that finds one that is not redoes
 // the columns that hold one from the nonzero stream alone, as the row-walk kernel would.
-// 1024 x 1024 x 4096 half at 80 %, 11 us: with one infinity in B 38 us, with 64 of them scattered 64 us, with a
+// 1024 x 1024 x 4096 half at 80 %, 10 us: with one infinity in B 38 us, with 64 of them scattered 64 us, with a
 // whole row of B not a number 406 us (1.84, 1.96 and 2.29 ms when the wave redid all of its part, one lane one element
 // at a time); latency of the fetches is what it spends the time on.
 // What bounds it, from builds with one ingredient left out (128 x 128 tile, K = 2048, one tile per compute unit):
 // LDS reads alone need 0.27 us per slab, matrix instructions alone 0.21 us, both 0.36 us, and 0.5 us with
 // the copies, which also write LDS.  Eight waves instead of four were worth 1.1x (a wave issues an instruction
 // every four clocks at best, and a slab is a hundred of them), addresses kept in the descriptor's scalar
-// offset instead of vector adds 1.15x.  1024 x 1024 x 4096 half at 80 %: 45.2 us generated, 11.1 us here (operands and plans taking
+// offset instead of vector adds 1.15x.  1024 x 1024 x 4096 half at 80 %: 45.2 us generated, 10.2 us here (operands and plans taking
 // turns, as in the next two); 3072 x 768 x 1024 half at 95 %: 11.3 and 8.1 us; 768 x 3072 x 1024 int8 at 95 %: 13.9 and 9.4 us.  Measured slower: a ring of
 // eight slabs, or K split over two or four groups of waves with a ring each (before a wave multiplies it issues its part of
 // the ring: 128 KiB take a compute unit 1 us; 768 x 1574 x 172 int8: 3.9 -> 4.9 us), and two slabs before the first turn with the

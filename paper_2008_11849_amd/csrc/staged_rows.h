@@ -62,7 +62,9 @@ inline double plain_rows_microseconds(const HostPlan &h, int32_t longest) {
 
 // Second estimates of both, fitted to 5303 products of the same ranges that the first ones give to the staged kernel, each
 // timed with both kernels, also before the steps of eight: 6 % and 13 % root mean square then; over the 700 above staged fp32 7 % to 15 %,
-// half 11 %, int8 32 % (1.27 times too long), plain 13 % to 15 %.  The plain kernel's loads cost by columns per lane, and more where
+// half 11 %, int8 32 % (1.27 times too long), plain 13 % to 15 %.  (fp32 at V = 4 is of the kernel whose values reached the multiply-adds in scalar
+// registers: over 60 products that take it the estimate is 1.11 times too long for the present one, 12 % root mean square, so that some that staging would
+// gain stay plain; of the 60 one is slower for being staged, 1.1 times, 0.49 times the plain kernel's time on average.)  The plain kernel's loads cost by columns per lane, and more where
 // rows of B do not begin on 64 bytes; every wave costs something of its own.
 inline double staged_rows_microseconds_again(const HostPlan &h, const StagedRows &s, int32_t longest) {
     static const double fit[5][6] = {{2.26, 0.81, 5.68, 3.64, 14.1, 0.219}, {2.41, 1.40, 2.92, 3.88, 7.12, 0.183}, {2.57, 0.847, 3.68, 2.82, 4.91, 0.176},

@@ -56,7 +56,9 @@ __host__ __device__ constexpr int staged_buffer_bytes(int chunk, int pitch) { re
 // registers only (or a literal) for two where a second wave takes turns with it (4.2 and 2.2 measured with two to eight waves), so a
 // move of four clocks pays from three multiply-adds on, so with four columns per lane: 4096 x 4096 x 784 at 90 % 135.9 -> 124.3 us, 3000 x
 // 2048 x 784, batch 4, at 84.7 % 260 -> 232 us; at 98 % (4096 x 4096 x 784, 63.4 us) nothing changes, and of 16 others with four columns one, skewed, loses
-// (4096 x 484 x 2036 at 91 % 40.0 -> 40.6).  With two columns it is not done: 1928 x 320 x 840 at 88 %, skewed, 11.4 us without, 12.4 with.  Half stays with the scalar operand: its products widen
+// (4096 x 484 x 2036 at 91 % 40.0 -> 40.6); of 60 more, at 50 % to 95 %, 48 gain over 3 %, 0.935 times the time on average, and two lose, with
+// skewed rows again (602 x 2898 x 1983 at 69 % 99.3 -> 104.2, 920 x 1308 x 1136 at 61 % 45.3 -> 46.5): there a wave with a row far longer than
+// the others' has its SIMD to itself, which takes five clocks for either form, and the move comes on top.  With two columns it is not done: 1928 x 320 x 840 at 88 %, skewed, 11.4 us without, 12.4 with.  Half stays with the scalar operand: its products widen
 // the operand as they go (v_fma_mix_f32), four clocks in any case.  (Assembly: the compiler would fold the move away.)
 __device__ __forceinline__ float in_vector(uint32_t bits) {
     float f;
