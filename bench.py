@@ -380,7 +380,7 @@ def measure_ceilings(torch, footprint_bytes, stream):
     out = torch.empty(wgs * 256, dtype=torch.float32, device=dev)
     t = timed(lambda: lib.sparsert_ceiling_fma(out.data_ptr(), wgs, iters, stream), 5, 2)
     res["fma_TFLOPs"] = wgs * 256.0 * iters * lib.sparsert_ceiling_fma_flops_per_thread_iter() / t / 1e12
-    res["fma_what"] = "independent v_fma_f32 on registers, 16 waves per compute unit and more; no packed instructions"
+    res["fma_what"] = "independent v_fma_f32 on vector registers, 16 waves per compute unit and more; no packed instructions"
     rows, pitch, tiles, wg2, reps = 3072, 1024, 16, 512, 4
     m = torch.empty(rows * pitch, dtype=torch.float32, device=dev).normal_()
     out2 = torch.empty(wg2 * 256, dtype=torch.float32, device=dev)
@@ -604,8 +604,8 @@ def main():
     peak_tf = {"f32": FP32_VECTOR_PEAK_TF}.get(args.dtype, FP32_VECTOR_PEAK_TF)   # sums are fp32 multiply-adds in every storage type but int8
     intensity = D.flops / D.algorithmic_bytes
     ridge_published = peak_tf * 1e12 / (HBM_PEAK_GBS * 1e9)
-    # the ridge this build can reach: packed fp32 instructions are never emitted, so the ALU side
-    # is what the multiply-add ceiling kernel measures
+    # the ridge that can be reached: the ALU side is what the multiply-add ceiling kernel measures
+    # (vector-register operands; packed fp32 instructions are never emitted)
     ridge_reachable = (ceilings["fma_TFLOPs"] * 1e12 / (HBM_PEAK_GBS * 1e9)) if ceilings else ridge_published
     bound = "alu" if intensity >= ridge_reachable else "hbm"
     t_dom = dom_row["in_step_us"] * 1e-6

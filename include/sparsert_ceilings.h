@@ -20,7 +20,7 @@ extern "C" {
 /* dst[0..bytes) = src[0..bytes); bytes a multiple of 16, buffers 16-byte aligned, not overlapping. */
 int sparsert_ceiling_copy(const void *src_dev, void *dst_dev, size_t bytes, void *stream);
 
-/* `workgroups` x 256 threads each run `iters` x 32 independent fp32 multiply-adds on registers;
+/* `workgroups` x 256 threads each run `iters` x 32 independent fp32 multiply-adds on vector registers;
  * out_dev receives workgroups*256 floats.  Flops = workgroups*256*iters*sparsert_ceiling_fma_flops_per_thread_iter(). */
 int sparsert_ceiling_fma(void *out_dev, int32_t workgroups, int32_t iters, void *stream);
 int32_t sparsert_ceiling_fma_flops_per_thread_iter(void);
