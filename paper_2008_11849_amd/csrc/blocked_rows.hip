@@ -19,6 +19,7 @@
 // the scalar cache 92: three parts of 60 to 75 us each that two waves per SIMD do not hide well behind each other.  Measured slower: one
 // column per lane with four waves per SIMD (117 us; the stream is read twice as often), groups of eight columns with three
 // waves (101), the next header asked for ahead of its place (100), fetches one by one between the last layer's multiply-adds (105).
+// Error against sums in 64 bits: 0.63 times the plain kernel's over 43 products, 1.007 times at most (the sums of four or eight waves meet last).
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
